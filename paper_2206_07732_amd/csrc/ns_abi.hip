@@ -40,6 +40,7 @@ struct ns_ctx {
   double *partials;
   double *scal;
   int nparts;
+  int nres;           // partials of the last residual norm
   int L;
   Level lev[32];
   double* host;       // pinned, coherent host mirror of the scalars
@@ -544,13 +545,17 @@ void launch_tail(ns_ctx* X, int l0, const T* b, T* e, size_t bytes) {
 // above the tail work on colour-split b and e; the first sweep of level 0
 // reads b0 in natural order and writes its split copy, and the last red pass
 // of level 0 writes e0 in natural order.
-// The flexible CG's next two products (r z, r z_old) requested of an FP64
-// V-cycle: its last kernel computes them when it is the finest level's last
-// red pass (nparts: the partials it left; 0 when the cycle had no such pass).
-struct DotsReq {
+// The CG loop's call of a V-cycle: its last kernel writes the FP64 result z
+// and, with dots, the partials of r z the flexible CG needs next, when it is the
+// finest level's last red pass (nparts: the partials it left; 0 when the
+// cycle had no such pass).  split: r and z are colour-split (cg_split), the
+// cycle's first kernel reads r in that order, and an FP64 cycle works on r
+// and z themselves.
+struct CgReq {
   const double* r;
-  const double* zold;
-  double* z;     // the cycle's FP64 result, natural order
+  double* z;
+  bool dots;
+  bool split;
   int nparts;
 };
 
@@ -558,7 +563,7 @@ struct DotsReq {
 // by its first kernel in place of b0 (the levels below the finest, the
 // tail, and a cycle without pre-smoothing read b0)
 template <typename T>
-void vcycle(ns_ctx* X, int l, const T* b0, T* e0, DotsReq* dq = nullptr, const double* b0d = nullptr) {
+void vcycle(ns_ctx* X, int l, const T* b0, T* e0, CgReq* dq = nullptr, const double* b0d = nullptr) {
   const ns_params& P = X->P;
   const Level& L = X->lev[l];
   hipStream_t st = X->st;
@@ -568,6 +573,13 @@ void vcycle(ns_ctx* X, int l, const T* b0, T* e0, DotsReq* dq = nullptr, const d
   }
   T* b = LV<T>::b(L);   // split
   T* e = LV<T>::e(L);   // split
+  const bool cgs = dq && dq->split;   // (level 0 only)
+  if constexpr (sizeof(T) == 8) {
+    if (cgs) {
+      b = const_cast<double*>(dq->r);
+      e = dq->z;
+    }
+  }
   const T *bx = LV<T>::bx(L), *by = LV<T>::by(L), *bz = LV<T>::bz(L);
   KTimer* kt = (l == 0 && X->timed_kernel == NS_TIME_SMOOTH0) ? &X->kt : nullptr;
   const size_t nsplit = 2 * (size_t)((L.n.nx + 1) / 2) * L.n.ny * L.n.nz;
@@ -575,8 +587,12 @@ void vcycle(ns_ctx* X, int l, const T* b0, T* e0, DotsReq* dq = nullptr, const d
   // products fused, into the FP64 z, when they are requested (no kernel
   // timer on it), else into e0
   auto last_red = [&]() {
-    if (dq && !kt) {
-      dq->nparts = launch_gs_last_dots<T>(L, bx, by, bz, b, e, dq->z, dq->r, dq->zold, X->partials, st);
+    if (cgs) {
+      dq->nparts = launch_gs_last_dots_split<T>(L, bx, by, bz, b, e, dq->z, dq->r, X->partials, st);
+      return;
+    }
+    if (dq && dq->dots && !kt) {
+      dq->nparts = launch_gs_last_dots<T>(L, bx, by, bz, b, e, dq->z, dq->r, X->partials, st);
       return;
     }
     launch_gs<T>(L, bx, by, bz, b, e, 0, st, kt, e0);
@@ -584,6 +600,10 @@ void vcycle(ns_ctx* X, int l, const T* b0, T* e0, DotsReq* dq = nullptr, const d
   // the first pre-smoothing kernel (red from zero + black); red_out false
   // where a red pass follows it, which overwrites the red values unread
   auto first = [&](T* bcopy, bool red_out) {
+    if (cgs) {
+      launch_gs_first_split<T>(L, bx, by, bz, dq->r, LV<T>::invd(L), e, sizeof(T) == 4 ? b : nullptr, st, red_out);
+      return;
+    }
     if constexpr (sizeof(T) == 4) {
       if (l == 0 && b0d) {
         launch_gs_first_nat64(L, bx, by, bz, b0d, LV<T>::invd(L), e, b, st, bcopy, red_out);
@@ -688,24 +708,34 @@ void vcycle(ns_ctx* X, int l, const T* b0, T* e0, DotsReq* dq = nullptr, const d
   }
 }
 
-// z = M r, one kernel launch at a time on the context's stream.  With zold
-// the cycle's last kernel also leaves the partials of r z and r z_old in
-// X->partials when it can; returns how many (0: not fused, or not asked).
-int precond_launch(ns_ctx* X, const double* r, double* z, const double* zold = nullptr) {
-  DotsReq dq{r, zold, z, 0};
+// Whether the solve keeps its vectors colour-split: where the finest level's
+// wide passes apply and the cycle starts and ends with them (its finest level
+// is above the tail and not its last one, smooths on the way down and up, and
+// does not run the fused sweep, which wants a third plane behind e)
+bool use_split(const ns_ctx* X) {
+  const int tail = X->P.prec == NS_PREC_FP64 ? X->tail64 : X->tail32;
+  return cg_split(X->lev[0].n) && tail > 0 && X->L > 1 && X->P.nu_pre > 0 && X->P.nu_post > 0 && !X->fine_rb;
+}
+
+// z = M r, one kernel launch at a time on the context's stream.  With dots
+// the cycle's last kernel also leaves the partials of r z in X->partials when
+// it can; returns how many (0: not fused, or not asked).  split: r and z are
+// colour-split (use_split).
+int precond_launch(ns_ctx* X, const double* r, double* z, bool dots = false, bool split = false) {
+  CgReq dq{r, z, dots, split, 0};
   if (X->P.prec == NS_PREC_FP64) {
-    vcycle<double>(X, 0, r, z, zold ? &dq : nullptr);
-    return dq.nparts;
+    vcycle<double>(X, 0, r, z, &dq);
+    return dots ? dq.nparts : 0;
   }
   // FP32 cycle: its first kernel reads r itself, rounding it to FP32, where
   // the finest level is above the tail and pre-smooths; its last kernel
-  // writes z in FP64 with the products when it can
+  // writes z in FP64 with the product when it can
   Level& L0 = X->lev[0];
   const bool direct = tail_start<float>(X) > 0 && X->P.nu_pre > 0;
   if (!direct) launch_d2f(r, L0.bfn, X->nc, X->st);
-  vcycle<float>(X, 0, L0.bfn, L0.efn, zold ? &dq : nullptr, direct ? r : nullptr);
-  if (dq.nparts > 0) return dq.nparts;
-  if (zold) return launch_f2d_dots(L0.efn, z, X->nc, r, zold, X->partials, X->st);
+  vcycle<float>(X, 0, L0.bfn, L0.efn, &dq, direct ? r : nullptr);
+  if (dq.nparts > 0) return dots ? dq.nparts : 0;
+  if (dots) return launch_f2d_dots(L0.efn, z, X->nc, r, X->partials, X->st);
   launch_f2d(L0.efn, z, X->nc, X->st);
   return 0;
 }
@@ -793,7 +823,8 @@ void prepare_hierarchy(ns_ctx* X) {
 double host_total(const ns_ctx* X, int nv, int q, int mirror_slot) {
   if (!X->hpart) return X->host[mirror_slot];
   double s = 0.0;
-  for (int b = 0; b < X->nparts; ++b) s += X->hpart[(size_t)nv * b + q];
+  const int np = nv == 2 ? X->nres : X->nparts;   // the residual's partials, or the update's
+  for (int b = 0; b < np; ++b) s += X->hpart[(size_t)nv * b + q];
   return s;
 }
 
@@ -841,22 +872,22 @@ ns_status pcg(ns_ctx* X, ns_stats* stats) {
   double* dn = X->d2;
   // segments: z = M r then rho = <r, z>; zn = M r then beta and rho;
   // then d = z + beta d, q = A d, alpha, x += alpha d, r -= alpha q, ||r||^2
-  auto precond_rho = [&](double* zz) {
-    return issue(X, SEG_PRECOND_RHO, zz, nullptr, nullptr, 0, [&] {
-      precond_launch(X, X->r, zz);
-      launch_dot_rho(n, X->r, zz, cs, X->st);
-    });
-  };
-  auto precond_beta = [&](double* znew, const double* zold) {
-    return issue(X, SEG_PRECOND_BETA, znew, zold, nullptr, 0, [&] {
-      // the products come with the cycle's last kernel when it can give them
-      const int np = precond_launch(X, X->r, znew, zold);
+  const bool split = use_split(X);   // the layout of r, z, d and q
+  // split: the running solution, in the finest level's own b, which a cycle
+  // on the split vectors leaves alone
+  double* xs = split ? L0.b : nullptr;
+  auto precond = [&](int kind, int mode, double* zz) {
+    return issue(X, kind, zz, nullptr, nullptr, 0, [&] {
+      // the product comes with the cycle's last kernel when it can give it
+      const int np = precond_launch(X, X->r, zz, true, split);
       if (np > 0)
-        launch_finalize_beta(cs, np, X->st);
+        launch_finalize_dot(cs, np, mode, X->st);
       else
-        launch_dots_beta(n, X->r, znew, zold, cs, X->st);
+        launch_dot(n, X->r, zz, cs, mode, X->st);
     });
   };
+  auto precond_rho = [&](double* zz) { return precond(SEG_PRECOND_RHO, FIN_RHO, zz); };
+  auto precond_beta = [&](double* zz) { return precond(SEG_PRECOND_BETA, FIN_BETA, zz); };
   // (four kernels: launched directly, a graph launch would cost the device
   // more than it saves the host).  x += alpha d is applied one iteration
   // late, by the next direction update, which reads d anyway: the vector
@@ -866,18 +897,19 @@ ns_status pcg(ns_ctx* X, ns_stats* stats) {
   bool xpend = false;
   auto dir_update = [&](const double* zz, const double* dold, double* dnew, int first) {
     launch_dir_spmv(n, h, L0.bx, L0.by, L0.bz, zz, dold, dnew, X->q, first, cs, X->st,
-                    X->timed_kernel == NS_TIME_SPMV ? &X->kt : nullptr, xpend ? x : nullptr, face_tab(L0, L0.bx));
+                    X->timed_kernel == NS_TIME_SPMV ? &X->kt : nullptr, !xpend ? nullptr : split ? xs : x, face_tab(L0, L0.bx), split);
     launch_cg_update(n, X->q, X->r, cs, X->st);
     xpend = true;
     HIPCHK(X, hipGetLastError());
     return NS_OK;
   };
   auto sync_x = [&](const double* dcur) {
-    if (xpend) launch_x_update(n, dcur, x, cs, X->st);
+    if (xpend) launch_x_update(n, dcur, x, cs, X->st, xs);
     xpend = false;
   };
   prepare_hierarchy(X);
-  launch_resid_norm(n, h, L0.bx, L0.by, L0.bz, X->b, x, X->r, cs, FIN_RESID0, st, face_tab(L0, L0.bx));
+  X->nres = launch_resid_norm(n, h, L0.bx, L0.by, L0.bz, X->b, x, X->r, cs, FIN_RESID0, st, face_tab(L0, L0.bx), split,
+                              xs);
   HIPCHK(X, hipEventRecord(X->ev_rr, st));
   // first direction d = z = M r, rho = <r, z>, queued before the host has
   // seen ||b|| and ||r||; unused if b = 0 or the guess already converges
@@ -915,7 +947,7 @@ ns_status pcg(ns_ctx* X, ns_stats* stats) {
     // last one, against 10x the tolerance (100x in the squares)
     const bool likely_done = rr_prev > 0.0 && rr * (rr / rr_prev) <= 100.0 * tol2;
     const bool ahead = it < P.max_iters && !likely_done;
-    if (ahead && (s = precond_beta(zn, z)) != NS_OK) return s;
+    if (ahead && (s = precond_beta(zn)) != NS_OK) return s;
     HIPCHK(X, hipEventSynchronize(X->ev_rr));
     rr_prev = rr;
     rr = host_total(X, 1, 0, S_RR);
@@ -928,7 +960,8 @@ ns_status pcg(ns_ctx* X, ns_stats* stats) {
     if (rr <= tol2) {
       // confirm on the true residual; restart from it when it fails
       sync_x(d);
-      launch_resid_norm(n, h, L0.bx, L0.by, L0.bz, X->b, x, X->r, cs, FIN_RESID0, st, face_tab(L0, L0.bx));
+      X->nres =
+          launch_resid_norm(n, h, L0.bx, L0.by, L0.bz, X->b, x, X->r, cs, FIN_RESID0, st, face_tab(L0, L0.bx), split, xs);
       if ((s = wait_host(X)) != NS_OK) return s;
       rr = true_rr = host_total(X, 2, 0, S_RR);
       S.rel_resid = std::sqrt(rr) / bnorm;
@@ -943,13 +976,13 @@ ns_status pcg(ns_ctx* X, ns_stats* stats) {
       continue;
     }
     if (it >= P.max_iters) break;
-    if (!ahead && (s = precond_beta(zn, z)) != NS_OK) return s;
+    if (!ahead && (s = precond_beta(zn)) != NS_OK) return s;
     std::swap(z, zn);
   }
   sync_x(d);
   if (!conv) {
     // true residual at exit (into q, leaving r as the recursion left it)
-    launch_resid_norm(n, h, L0.bx, L0.by, L0.bz, X->b, x, X->q, cs, FIN_TRR, st, face_tab(L0, L0.bx));
+    X->nres = launch_resid_norm(n, h, L0.bx, L0.by, L0.bz, X->b, x, X->q, cs, FIN_TRR, st, face_tab(L0, L0.bx), split);
     if ((s = wait_host(X)) != NS_OK) return s;
     true_rr = host_total(X, 2, 0, S_TRR);
   }
@@ -1261,7 +1294,7 @@ ns_status ns_time_kernel(ns_ctx* X, int kernel, int reps, double* avg_ms) {
       }
     } else {
       launch_dir_spmv(n, X->P.h, L0.bx, L0.by, L0.bz, X->zn, X->d, X->d2, X->q, 1, cs, X->st, nullptr, nullptr,
-                      face_tab(L0, L0.bx));
+                      face_tab(L0, L0.bx), use_split(X));
     }
   }
   (void)hipEventRecord(b, X->st);
@@ -1477,7 +1510,7 @@ ns_status projection_solve(ns_ctx* X, double dt, ns_stats* stats) {
     if (trial) {
       // ||b - A p_prev||: the residual the step would start from without the network
       const CgScratch cs{X->partials, X->scal, X->host_dev, X->hpart_dev};
-      launch_resid_norm(L0.n, X->P.h, L0.bx, L0.by, L0.bz, X->b, pprev, X->r, cs, FIN_RESID0, st);
+      X->nres = launch_resid_norm(L0.n, X->P.h, L0.bx, L0.by, L0.bz, X->b, pprev, X->r, cs, FIN_RESID0, st);
       HIPCHK(X, hipEventRecord(X->ax.ev[0], st));
     }
     launch_apply_A(L0.n, X->P.h, L0.bx, L0.by, L0.bz, pprev, net_Ap(N), st);

@@ -47,10 +47,10 @@ __device__ __forceinline__ Tile xcd_tile_order(int band) {
   return t;
 }
 __device__ __forceinline__ Tile xcd_tile_flat() { return xcd_tile_order(gridDim.y); }
-__device__ __forceinline__ Tile xcd_tile() {
+__device__ __forceinline__ Tile xcd_tile(int most = kTileBand) {
   const int gy = gridDim.y;
   int band = gy;
-  for (int d = kTileBand; d >= kTileBand / 2; --d)
+  for (int d = most; d >= kTileBand / 2; --d)
     if (gy % d == 0) {
       band = d;
       break;
@@ -151,6 +151,7 @@ enum ScalIdx {
   S_FLAGS = 12, // set to 1 by the predictor when a carried face density is <= 0
   S_CNDU = 13,  // Crank-Nicolson: largest change of the last sweep
   S_CNU = 14,   //   and the largest |u*| it produced
+  S_ZQ = 15,    // <z, q> of the last direction update
   S_COUNT = 16
 };
 
@@ -304,38 +305,53 @@ void launch_vcycle_tail(const TailDesc<T>& D, size_t lds_bytes, hipStream_t st);
 void launch_d2f(const double* a, float* b, size_t n, hipStream_t st);
 void launch_f2d(const float* a, double* b, size_t n, hipStream_t st);
 // the V-cycle's last kernel (its FP64 result z in natural order) fused with
-// the flexible CG's two products (r z, r z_old): per-block partials, two per
-// block; each returns the block count
+// the flexible CG's product r z: per-block partials; each returns the block
+// count
 template <typename T>
 int launch_gs_last_dots(const Level& L, const T* bx, const T* by, const T* bz, const T* b, const T* e,
-                        double* nat, const double* r, const double* zold, double* partials, hipStream_t st);
+                        double* nat, const double* r, double* partials, hipStream_t st);
+// The finest level's first and last kernel with split CG vectors (cg_split):
+// the first reads the residual r (an FP32 cycle leaves its FP32 copy in bs);
+// the last writes z, colour-split, and the product's partials (FP64: e == z)
+template <typename T>
+void launch_gs_first_split(const Level& L, const T* bx, const T* by, const T* bz, const double* r, const T* invd, T* e,
+                           T* bs, hipStream_t st, bool red_out);
+template <typename T>
+int launch_gs_last_dots_split(const Level& L, const T* bx, const T* by, const T* bz, const T* b, const T* e, double* z,
+                              const double* r, double* partials, hipStream_t st);
 // the finest level's first kernel of an FP32 cycle reading its natural b in
 // FP64 (the CG residual), rounded as it is read
 void launch_gs_first_nat64(const Level& L, const float* bx, const float* by, const float* bz, const double* b,
                            const float* invd, float* e, float* bs, hipStream_t st, float* bcopy = nullptr,
                            bool red_out = true);
-int launch_f2d_dots(const float* a, double* z, size_t n, const double* r, const double* zold, double* partials,
-                    hipStream_t st);
+int launch_f2d_dots(const float* a, double* z, size_t n, const double* r, double* partials, hipStream_t st);
 
 int cg_blocks(const Dims& n);
-void launch_resid_norm(const Dims& n, double h, const double* bx, const double* by, const double* bz,
-                       const double* b, const double* x, double* r, const CgScratch& cs, int mode,
-                       hipStream_t st, const FaceTab<double>& ft = FaceTab<double>{});
-void launch_dot_rho(const Dims& n, const double* r, const double* z, const CgScratch& cs, hipStream_t st);
-// beta and rho from two-valued partials already in cs.partials
-void launch_finalize_beta(const CgScratch& cs, int nparts, hipStream_t st);
-void launch_dots_beta(const Dims& n, const double* r, const double* zn, const double* z,
-                      const CgScratch& cs, hipStream_t st);
+// Whether a finest level of these extents keeps the CG vectors r, z, d and q
+// colour-split (cells by colour and pair index, as the V-cycle's vectors): the
+// levels of the wide passes.  nx is even there, so both layouts have one entry
+// per cell.
+bool cg_split(const Dims& n);
+// r = b - A x and ||r||^2, ||b||^2; split: r colour-split, and into xs, when
+// set, x colour-split; returns the partials it leaves
+int launch_resid_norm(const Dims& n, double h, const double* bx, const double* by, const double* bz, const double* b,
+                      const double* x, double* r, const CgScratch& cs, int mode, hipStream_t st,
+                      const FaceTab<double>& ft = FaceTab<double>{}, bool split = false, double* xs = nullptr);
+// <r, z> (one layout for both), as rho (FIN_RHO) or for beta (FIN_BETA)
+void launch_dot(const Dims& n, const double* r, const double* z, const CgScratch& cs, int mode, hipStream_t st);
+// the same from its partials, already in cs.partials
+void launch_finalize_dot(const CgScratch& cs, int nparts, int mode, hipStream_t st);
 // d = z + beta d_old and q = A d; with x, also the previous iteration's
-// pending x += alpha d_old
+// pending x += alpha d_old (split: z, d, q and x colour-split)
 void launch_dir_spmv(const Dims& n, double h, const double* bx, const double* by, const double* bz,
                      const double* zn, const double* dold, double* dnew, double* q, int first,
                      const CgScratch& cs, hipStream_t st, KTimer* kt = nullptr, double* x = nullptr,
-                     const FaceTab<double>& ft = FaceTab<double>{});
+                     const FaceTab<double>& ft = FaceTab<double>{}, bool split = false);
 // r -= alpha q and ||r||^2; x += alpha d is left pending
 void launch_cg_update(const Dims& n, const double* q, double* r, const CgScratch& cs, hipStream_t st);
-// the pending x += alpha d
-void launch_x_update(const Dims& n, const double* d, double* x, const CgScratch& cs, hipStream_t st);
+// the pending x += alpha d; with xs, x = xs + alpha d from colour-split xs and d
+void launch_x_update(const Dims& n, const double* d, double* x, const CgScratch& cs, hipStream_t st,
+                     const double* xs = nullptr);
 void launch_apply_A(const Dims& n, double h, const double* bx, const double* by, const double* bz,
                     const double* x, double* y, hipStream_t st);
 

@@ -485,23 +485,21 @@ __global__ void __launch_bounds__(256) k_gs_c1(Dims n, T h2, const T* __restrict
 
 // The last red pass of the finest level, writing the V-cycle's result z in
 // natural order and in FP64 (as k_gs with nat; an FP32 cycle's values are
-// widened exactly), fused with the two products the flexible CG needs next:
-// per block, sum over its cells of r z and r z_old, red cell then black cell
-// of each pair, in tile order.  Every thread reaches the block reduction (no
+// widened exactly), fused with the product r z the flexible CG needs next:
+// its per-block sums, red cell then black cell of each pair, in tile order.  Every thread reaches the block reduction (no
 // early return).
 template <typename T>
 __global__ void __launch_bounds__(256) k_gs_last_dots(Dims n, T h2, const T* __restrict__ bx,
                                                       const T* __restrict__ by, const T* __restrict__ bz,
                                                       const T* __restrict__ b, const T* __restrict__ e,
                                                       double* __restrict__ nat, const double* __restrict__ r,
-                                                      const double* __restrict__ zold,
                                                       double* __restrict__ partials, FaceTab<T> ft) {
   const Tile tl = xcd_tile();
   const int ti = tl.x * blockDim.x + threadIdx.x;
   const int j = tl.y * blockDim.y + threadIdx.y;
   const int k = tl.z * blockDim.z + threadIdx.z;
   const SplitGeo sg = split_geo(n);
-  double v[2] = {0.0, 0.0};
+  double v[1] = {0.0};
   const bool live = j < n.ny && k < n.nz && ti < sg.hx;
   const size_t pos = live ? (size_t)ti + (size_t)sg.hx * (j + (size_t)n.ny * k) : 0;
   const T* eo = e + sg.P;   // the black plane
@@ -529,13 +527,12 @@ __global__ void __launch_bounds__(256) k_gs_last_dots(Dims n, T h2, const T* __r
   T ex = 0;   // the row-end lanes' x neighbour from outside the wavefront
   if (live && lane == 0 && par == 0 && ir > 0) ex = eo[pos - 1];
   if (live && lane == 63 && par == 1 && ir < n.nx - 1) ex = eo[pos + 1];
-  const double rr = r[row + ir], zr = zold[row + ir], rq = r[row + iq], zq = zold[row + iq];
+  const double rr = r[row + ir], rq = r[row + iq];
   __builtin_amdgcn_sched_barrier(0);
   F.get(n, ir, g.bw, g.be, g.bs, g.bn, g.bd, g.bu);
   const T ebl = __shfl_up(eb, 1, 64), ebr = __shfl_down(eb, 1, 64);
   // formed on every lane from in-grid values, then kept by selects: a use
-  // under a branch would let the compiler sink r's and z_old's loads past
-  // the shuffles
+  // under a branch would let the compiler sink r's loads past the shuffles
   T vw = eb, ve = eb;   // par 1: west is this pair's black; par 0: east is
   if (par == 0 && ir > 0) vw = lane > 0 ? ebl : ex;
   if (par == 1 && ir < n.nx - 1) ve = lane < 63 ? ebr : ex;
@@ -544,8 +541,7 @@ __global__ void __launch_bounds__(256) k_gs_last_dots(Dims n, T h2, const T* __r
   if (red_ok) nat[row + i] = z;
   if (black_ok) nat[row + io] = zb;
   v[0] = (red_ok ? rr * z : 0.0) + (black_ok ? rq * zb : 0.0);
-  v[1] = (red_ok ? rr * zr : 0.0) + (black_ok ? rq * zq : 0.0);
-  block_partials<2>(v, partials, tl.lin);
+  block_partials<1>(v, partials, tl.lin);
 }
 
 // red pass from a zero guess followed by the black pass, in one launch: the
@@ -772,6 +768,329 @@ __global__ void __launch_bounds__(256) k_gs_prolong_c1(Dims n, T h2, const T* __
                                                        int syc, int szc, int csplit, const T* __restrict__ ec,
                                                        T* __restrict__ bcopy, FaceTab<T> ft) {
   gs_prolong_body<T, true, gs_planes<T>(true)>(n, h2, bx, by, bz, b, e, nc, sxc, syc, szc, csplit, ec, bcopy, ft);
+}
+
+// ---------------------------------------------------------- wide passes
+// The smoothing passes of a level with long rows (wide_pairs), V adjacent
+// pairs of a row per lane.  What bounds the one-pair passes on a large level
+// is the vector L1's address rate, not HBM: measured with loads that hit it,
+// a wavefront's 8-byte-per-lane load takes 16 clocks (32 B/clk per compute
+// unit), and so does a 16-byte one (64 B/clk; a 4-byte load takes 5, a
+// strided 4-byte one 16).  A one-pair FP64 pass issues eight 8-byte
+// instructions per 64 pairs, up to twenty where a line is not one value, and
+// kept the address unit busy most of the time at 3.5 TB/s of traffic.  With
+// V = 2 in FP64 and 4 in FP32 every access of a row is one 16-byte load or
+// store per lane.  (512 x 256 x 256, one finest colour pass: FP64 150 ->
+// 126 us, with faces all one value 132 -> 83; 256 x 128 x 128: 18.3 -> 13.3.)
+
+// V consecutive values, by loads and stores of up to 16 bytes per lane
+template <typename T, int V>
+__device__ __forceinline__ void vload(T (&d)[V], const T* __restrict__ p) {
+  typedef T VT __attribute__((ext_vector_type(V)));
+  typedef VT VU __attribute__((aligned(sizeof(T))));   // a caller's field array is only 8-byte aligned
+  const VU v = *reinterpret_cast<const VU*>(p);
+#pragma unroll
+  for (int q = 0; q < V; ++q) d[q] = v[q];
+}
+template <typename T, int V>
+__device__ __forceinline__ void vstore(T* __restrict__ p, const T (&d)[V]) {
+  typedef T VT __attribute__((ext_vector_type(V)));
+  typedef VT VU __attribute__((aligned(sizeof(T))));
+  VU v;
+#pragma unroll
+  for (int q = 0; q < V; ++q) v[q] = d[q];
+  *reinterpret_cast<VU*>(p) = v;
+}
+// the same for values no other wavefront touches: not kept in the L2, which
+// the values that neighbouring rows and planes share then have to themselves
+template <typename T, int V>
+__device__ __forceinline__ void vload_once(T (&d)[V], const T* __restrict__ p) {
+  typedef T VT __attribute__((ext_vector_type(V)));
+  typedef VT VU __attribute__((aligned(sizeof(T))));
+  const VU v = __builtin_nontemporal_load(reinterpret_cast<const VU*>(p));
+#pragma unroll
+  for (int q = 0; q < V; ++q) d[q] = v[q];
+}
+template <typename T, int V>
+__device__ __forceinline__ void vstore_once(T* __restrict__ p, const T (&d)[V]) {
+  typedef T VT __attribute__((ext_vector_type(V)));
+  typedef VT VU __attribute__((aligned(sizeof(T))));
+  VU v;
+#pragma unroll
+  for (int q = 0; q < V; ++q) v[q] = d[q];
+  __builtin_nontemporal_store(v, reinterpret_cast<VU*>(p));
+}
+
+// The faces of the V cells i0, i0 + 2, .. of one row, the cells of one colour
+// of V adjacent pairs; i0 = 2 tp + par, tp the first pair.  As FaceLd: load()
+// under scalar branches, get() once every load is in flight.  In FP32 the y
+// and z faces are read as whole rows of 2 V faces from the even column 2 tp
+// (two or four times fewer instructions than strided 4-byte loads) and the
+// cells' own picked by par; in FP64 the whole row would cost as much as the
+// cells' own.
+template <typename T, int V>
+struct FaceLdV {
+  static constexpr bool ROW = sizeof(T) == 4;
+  static constexpr int NF = ROW ? 2 * V : V;
+  T t[5];
+  bool u[5];
+  T lx[2 * V], ls[NF], ln[NF], ld[NF], lu[NF];
+  int par;
+  __device__ __forceinline__ void row(T (&d)[NF], const T* __restrict__ p) const {   // p: the face at column i0
+    if constexpr (ROW) {
+      vload<T, NF>(d, p - par);
+    } else {
+#pragma unroll
+      for (int q = 0; q < V; ++q) d[q] = p[2 * q];
+    }
+  }
+  __device__ __forceinline__ T pick(const T (&d)[NF], int q) const {
+    if constexpr (ROW)
+      return par ? d[2 * q + 1] : d[2 * q];
+    else
+      return d[q];
+  }
+  __device__ __forceinline__ void load(const Dims& n, const FaceTab<T>& ft, const T* __restrict__ bx,
+                                       const T* __restrict__ by, const T* __restrict__ bz, int ju, int ku, int p,
+                                       int i0, int j, int k) {
+    par = p;
+    u[0] = line_val(ft.x, ju + n.ny * ku, t[0]);
+    u[1] = line_val(ft.y, ju + (n.ny + 1) * ku, t[1]);
+    u[2] = line_val(ft.y, ju + 1 + (n.ny + 1) * ku, t[2]);
+    u[3] = line_val(ft.z, ju + n.ny * ku, t[3]);
+    u[4] = line_val(ft.z, ju + n.ny * (ku + 1), t[4]);
+    const size_t fy = i0 + (size_t)n.nx * (j + (size_t)(n.ny + 1) * k);
+    const size_t fz = i0 + (size_t)n.nx * (j + (size_t)n.ny * k);
+    if (!u[0]) vload<T, 2 * V>(lx, bx + i0 + (size_t)(n.nx + 1) * (j + (size_t)n.ny * k));
+    if (!u[1]) row(ls, by + fy);
+    if (!u[2]) row(ln, by + fy + n.nx);
+    if (!u[3]) row(ld, bz + fz);
+    if (!u[4]) row(lu, bz + fz + (size_t)n.nx * n.ny);
+  }
+  // the faces of the q-th cell, in column i
+  __device__ __forceinline__ void get(const Dims& n, int i, int q, T& bw, T& be, T& bs, T& bn, T& bd, T& bu) const {
+    bw = u[0] ? (i > 0 ? t[0] : (T)0) : lx[2 * q];
+    be = u[0] ? (i < n.nx - 1 ? t[0] : (T)0) : lx[2 * q + 1];
+    bs = u[1] ? t[1] : pick(ls, q);
+    bn = u[2] ? t[2] : pick(ln, q);
+    bd = u[3] ? t[3] : pick(ld, q);
+    bu = u[4] ? t[4] : pick(lu, q);
+  }
+};
+
+// The lane's place: pairs tp .. tp + V - 1 of row j of plane k (a 64 x 4
+// block), pos the first one's pair index.  A level of the wide passes has an
+// even nx and a multiple of V pairs per row, so a lane's pairs are all in the
+// row or all past its end; such a lane, or one in a row past the last,
+// works on pairs inside the grid (tp, j clamped) and stores nothing.  A tile
+// holds more of a row here, so the band of tile rows is wider where the grid
+// has enough of them: at 512 x 256 x 256 sixteen (64 rows) took a projection
+// from 38.6 to 36.6 ms (FP32 cycle 29.6 to 28.3), thirty-two 37.2; at 256 x
+// 128 x 128 eight 5.12 ms, sixteen 5.17.
+#define WIDE_INDEX                                                                     \
+  const Tile tl = xcd_tile(max(kTileBand, min(2 * kTileBand, (int)gridDim.y >> 2)));   \
+  const int lane = threadIdx.x, hx = n.nx >> 1;                                        \
+  const int tpr = V * (tl.x * 64 + lane), jr = tl.y * 4 + (int)threadIdx.y, k = tl.z;  \
+  const bool live = tpr < hx && jr < n.ny;                                             \
+  const int tp = min(tpr, hx - V), j = min(jr, n.ny - 1);                              \
+  [[maybe_unused]] const int ju = __builtin_amdgcn_readfirstlane(j);                   \
+  const size_t P = (size_t)hx * n.ny * n.nz, sz = (size_t)hx * n.ny;                   \
+  const size_t pos = (size_t)tp + (size_t)hx * (j + (size_t)n.ny * k);                 \
+  const bool S = j > 0, N = j < n.ny - 1, D = k > 0, U = k < n.nz - 1;                 \
+  [[maybe_unused]] const size_t ps = S ? pos - hx : pos, pn = N ? pos + hx : pos;      \
+  [[maybe_unused]] const size_t pd = D ? pos - sz : pos, pu = U ? pos + sz : pos
+
+// The other colour's values around V cells of one colour: own pairs, rows
+// beside, planes below and above, and the pair beyond the lane's own that the
+// first (par = 0) or last (par = 1) cell has as its x neighbour.
+template <typename T, int V>
+struct WideNb {
+  T o[V], s[V], n[V], d[V], u[V], x;
+  __device__ __forceinline__ void load(const T* __restrict__ eo, size_t pos, size_t ps, size_t pn, size_t pd,
+                                       size_t pu, int tp, int hx, int par) {
+    vload<T, V>(o, eo + pos);
+    vload<T, V>(s, eo + ps);
+    vload<T, V>(n, eo + pn);
+    vload<T, V>(d, eo + pd);
+    vload<T, V>(u, eo + pu);
+    x = eo[par ? (tp + V < hx ? pos + V : pos) : (tp > 0 ? pos - 1 : pos)];
+  }
+  __device__ __forceinline__ T west(int q, int par) const { return par ? o[q] : q > 0 ? o[q > 0 ? q - 1 : 0] : x; }
+  __device__ __forceinline__ T east(int q, int par) const { return par ? (q < V - 1 ? o[q < V - 1 ? q + 1 : q] : x) : o[q]; }
+};
+
+// the Gauss-Seidel values of the lane's V cells, as gs_combine
+template <typename T, int V>
+__device__ __forceinline__ void wide_values(const Dims& n, const FaceLdV<T, V>& F, const WideNb<T, V>& w, T h2,
+                                            const T (&bc)[V], int i0, int j, int k, int par, T (&v)[V]) {
+#pragma unroll
+  for (int q = 0; q < V; ++q) {
+    GsIn<T> g;
+    const int i = i0 + 2 * q;
+    F.get(n, i, q, g.bw, g.be, g.bs, g.bn, g.bd, g.bu);
+    g.vs = w.s[q];
+    g.vn = w.n[q];
+    g.vd = w.d[q];
+    g.vu = w.u[q];
+    v[q] = gs_combine<T>(n, g, h2, bc[q], i, j, k, w.west(q, par), w.east(q, par));
+  }
+}
+
+// one colour pass (as k_gs)
+template <typename T, int V>
+__global__ void __launch_bounds__(256) k_gs_wide(Dims n, T h2, const T* __restrict__ bx, const T* __restrict__ by,
+                                                 const T* __restrict__ bz, const T* __restrict__ b,
+                                                 T* __restrict__ e, int colour, FaceTab<T> ft) {
+  WIDE_INDEX;
+  const int par = (j + k + colour) & 1, i0 = 2 * tp + par;
+  WideNb<T, V> w;
+  w.load(e + (size_t)(1 - colour) * P, pos, ps, pn, pd, pu, tp, hx, par);
+  T bc[V], v[V];
+  vload<T, V>(bc, b + (size_t)colour * P + pos);
+  FaceLdV<T, V> F;
+  F.load(n, ft, bx, by, bz, ju, k, par, i0, j, k);
+  __builtin_amdgcn_sched_barrier(0);
+  wide_values<T, V>(n, F, w, h2, bc, i0, j, k, par, v);
+  if (live) vstore<T, V>(e + (size_t)colour * P + pos, v);
+}
+
+// The V-cycle's first kernel on such a level (as k_gs_first), b colour-split:
+// the level's own b, or on the finest level the CG residual, which split CG
+// vectors keep colour-split.  An FP32 cycle reads it in FP64 and leaves its
+// FP32 copy in bs for the passes that follow; an FP64 cycle reads the
+// residual itself in all of them.
+template <typename T, int V, typename TB>
+__global__ void __launch_bounds__(256) k_gs_first_wide(Dims n, T h2, const T* __restrict__ bx,
+                                                       const T* __restrict__ by, const T* __restrict__ bz,
+                                                       const TB* __restrict__ b, const T* __restrict__ invd,
+                                                       T* __restrict__ e, T* __restrict__ bs, T* __restrict__ bcopy,
+                                                       FaceTab<T> ft, int red_out) {
+  constexpr bool COPY = sizeof(TB) != sizeof(T);
+  WIDE_INDEX;
+  const int par = (j + k) & 1, i0 = 2 * tp + 1 - par;   // the first black cell
+  // b and 1/D of the lane's red cells and of the red neighbours of its black
+  // ones, whose values from zero are h^2 b / D
+  WideNb<TB, V> rb;
+  WideNb<T, V> w;
+  rb.load(b, pos, ps, pn, pd, pu, tp, hx, 1 - par);
+  w.load(invd, pos, ps, pn, pd, pu, tp, hx, 1 - par);
+  TB bb[V];
+  vload<TB, V>(bb, b + P + pos);
+  FaceLdV<T, V> F;
+  F.load(n, ft, bx, by, bz, ju, k, 1 - par, i0, j, k);
+  __builtin_amdgcn_sched_barrier(0);
+  T red[V], black[V], v[V];
+#pragma unroll
+  for (int q = 0; q < V; ++q) {
+    red[q] = (T)rb.o[q];
+    black[q] = (T)bb[q];
+    w.o[q] = h2 * red[q] * w.o[q];
+    w.s[q] = h2 * (T)rb.s[q] * w.s[q];
+    w.n[q] = h2 * (T)rb.n[q] * w.n[q];
+    w.d[q] = h2 * (T)rb.d[q] * w.d[q];
+    w.u[q] = h2 * (T)rb.u[q] * w.u[q];
+  }
+  w.x = h2 * (T)rb.x * w.x;
+  wide_values<T, V>(n, F, w, h2, black, i0, j, k, 1 - par, v);
+  if (!live) return;
+  if (red_out) vstore<T, V>(e + pos, w.o);
+  if constexpr (COPY) {
+    vstore<T, V>(bs + pos, red);
+    vstore<T, V>(bs + P + pos, black);
+  }
+  vstore<T, V>(e + P + pos, v);
+  if (bcopy) vstore<T, V>(bcopy + pos, v);
+}
+
+// The last red pass of the finest level with the product r z the flexible CG
+// needs next (as k_gs_last_dots), z and r colour-split.  An FP64 cycle works
+// in z itself (e == z: its black values are final, so only the red ones are
+// stored) and has r for its b; an FP32 cycle writes both colours, widened.
+template <typename T, int V>
+__global__ void __launch_bounds__(256) k_gs_last_dots_wide(Dims n, T h2, const T* __restrict__ bx,
+                                                           const T* __restrict__ by, const T* __restrict__ bz,
+                                                           const T* __restrict__ b, const T* e, double* z,
+                                                           const double* __restrict__ r,
+                                                           double* __restrict__ partials, FaceTab<T> ft) {
+  constexpr bool WIDEN = sizeof(T) != sizeof(double);
+  WIDE_INDEX;
+  const int par = (j + k) & 1, i0 = 2 * tp + par;
+  WideNb<T, V> w;
+  w.load(e + P, pos, ps, pn, pd, pu, tp, hx, par);
+  T bc[V], v[V];
+  vload<T, V>(bc, b + pos);
+  double rr[V], rk[V];
+  if constexpr (WIDEN) vload<double, V>(rr, r + pos);
+  vload<double, V>(rk, r + P + pos);
+  FaceLdV<T, V> F;
+  F.load(n, ft, bx, by, bz, ju, k, par, i0, j, k);
+  __builtin_amdgcn_sched_barrier(0);
+  wide_values<T, V>(n, F, w, h2, bc, i0, j, k, par, v);
+  double s[1] = {0.0}, zr[V], zk[V];
+#pragma unroll
+  for (int q = 0; q < V; ++q) {
+    zr[q] = (double)v[q];
+    zk[q] = (double)w.o[q];
+    if constexpr (!WIDEN) rr[q] = bc[q];
+  }
+  if (live) {
+    vstore<double, V>(z + pos, zr);
+    if constexpr (WIDEN) vstore<double, V>(z + P + pos, zk);
+#pragma unroll
+    for (int q = 0; q < V; ++q) s[0] += rr[q] * zr[q] + rk[q] * zk[q];
+  }
+  block_partials<1>(s, partials, tl.lin);
+}
+
+// prolongation + black (as k_gs_prolong).  A red neighbour's parent is the
+// cell's own, or, for one neighbour each along x, y and z, the next one's, so
+// four parents are read per cell instead of six.
+template <typename T, int V>
+__global__ void __launch_bounds__(256) k_gs_prolong_wide(Dims n, T h2, const T* __restrict__ bx,
+                                                         const T* __restrict__ by, const T* __restrict__ bz,
+                                                         const T* __restrict__ b, T* __restrict__ e, Dims nc, int syc,
+                                                         int szc, int csplit, const T* __restrict__ ec,
+                                                         T* __restrict__ bcopy, FaceTab<T> ft) {
+  WIDE_INDEX;
+  const int par = (j + k + 1) & 1, i0 = 2 * tp + par;
+  const int chx = (nc.nx + 1) >> 1, cP = chx * nc.ny * nc.nz;
+  auto cidx = [&](int I, int J, int K) {
+    return csplit ? ((I + J + K) & 1) * cP + (I >> 1) + chx * (J + nc.ny * K) : I + nc.nx * (J + nc.ny * K);
+  };
+  // the parents' rows: the cell's own, and the one that holds its neighbour
+  // across the coarse cell's y or z face
+  const int J = j >> syc, K = k >> szc;
+  const int js = (S ? j - 1 : j) >> syc, jn = (N ? j + 1 : j) >> syc;
+  const int kd = (D ? k - 1 : k) >> szc, ku = (U ? k + 1 : k) >> szc;
+  const int xI = par ? min(tp + V, hx - 1) : max(tp - 1, 0);
+  WideNb<T, V> w;
+  w.load(e, pos, ps, pn, pd, pu, tp, hx, par);
+  T bc[V], v[V], co[V], cy[V], cz[V];
+  const int jy = js != J ? js : jn, kz = kd != K ? kd : ku;
+#pragma unroll
+  for (int q = 0; q < V; ++q) {
+    co[q] = ec[cidx(tp + q, J, K)];
+    cy[q] = ec[cidx(tp + q, jy, K)];
+    cz[q] = ec[cidx(tp + q, J, kz)];
+  }
+  const T cx = ec[cidx(xI, J, K)];
+  vload<T, V>(bc, b + P + pos);
+  FaceLdV<T, V> F;
+  F.load(n, ft, bx, by, bz, ju, k, par, i0, j, k);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < V; ++q) {
+    w.o[q] += co[q];
+    w.s[q] += js != J ? cy[q] : co[q];
+    w.n[q] += jn != J ? cy[q] : co[q];
+    w.d[q] += kd != K ? cz[q] : co[q];
+    w.u[q] += ku != K ? cz[q] : co[q];
+  }
+  w.x += cx;
+  wide_values<T, V>(n, F, w, h2, bc, i0, j, k, par, v);
+  if (!live) return;
+  vstore<T, V>(e + P + pos, v);
+  if (bcopy) vstore<T, V>(bcopy + pos, v);
 }
 
 // A red pass then a black pass of Gauss-Seidel in one launch, on a level
@@ -1157,15 +1476,21 @@ __global__ void __launch_bounds__(kRbfLanes * (TY + 3)) k_gs_rb_fine(Dims n, T h
   }
 }
 
-// the residual b - A x of one cell from its value, its neighbours' (a wall
-// neighbour given as the cell's own value) and its six faces; up: the cell
-// is below the top row (else the open top's ghost term 2 beta_top x_c)
+// A x (without 1/h^2) and the residual b - A x of one cell from its value,
+// its neighbours' (a wall neighbour given as the cell's own value) and its six
+// faces; up: the cell is below the top row (else the open top's ghost term
+// 2 beta_top x_c)
+template <typename T>
+__device__ __forceinline__ T cell_A(T xc, T xw, T xe, T xs, T xn, T xd, T xu, T cw, T ce, T cs, T cn, T cd, T bu,
+                                    bool up) {
+  T acc = cw * (xc - xw) + ce * (xc - xe) + cs * (xc - xs) + cn * (xc - xn) + cd * (xc - xd);
+  acc += up ? bu * (xc - xu) : (T)2 * bu * xc;
+  return acc;
+}
 template <typename T>
 __device__ __forceinline__ T cell_resid(T bcell, T ih2, T xc, T xw, T xe, T xs, T xn, T xd, T xu, T cw, T ce, T cs,
                                         T cn, T cd, T bu, bool up) {
-  T acc = cw * (xc - xw) + ce * (xc - xe) + cs * (xc - xs) + cn * (xc - xn) + cd * (xc - xd);
-  acc += up ? bu * (xc - xu) : (T)2 * bu * xc;
-  return bcell - ih2 * acc;
+  return bcell - ih2 * cell_A<T>(xc, xw, xe, xs, xn, xd, xu, cw, ce, cs, cn, cd, bu, up);
 }
 
 // coarse rhs = mean over the children of the fine residual b - A e (fine b,
@@ -1331,6 +1656,133 @@ __global__ void __launch_bounds__(256) k_resid_restrict_pairs(Dims nf, T ih2, co
   const int chx = (nc.nx + 1) >> 1, cP = chx * nc.ny * nc.nz;
   const int ci = csplit ? ((I + J + K) & 1) * cP + (I >> 1) + chx * (J + nc.ny * K) : I + nc.nx * (J + nc.ny * K);
   bc[ci] = sum * inv;
+}
+
+// Both cells of V adjacent pairs of a row and what the operator reads around
+// them, for the wide kernels.  A is a pair's first cell (even column, colour
+// par = (j + k) & 1), B its second; pa, pb: their entries in v's two planes.
+// A's y and z neighbours have B's colour, and B's have A's; a wall neighbour
+// reads the cell's own entry.
+template <typename T, int V>
+struct PairNb {
+  T a[V], b[V], as[V], an[V], ad[V], au[V], bs[V], bn[V], bd[V], bu[V], w, e;
+  __device__ __forceinline__ void load(const T* __restrict__ v, size_t pa, size_t pb, int hx, size_t sz, int tp, bool S,
+                                       bool N, bool D, bool U) {
+    vload<T, V>(a, v + pa);
+    vload<T, V>(b, v + pb);
+    vload<T, V>(as, v + (S ? pb - hx : pa));
+    vload<T, V>(an, v + (N ? pb + hx : pa));
+    vload<T, V>(ad, v + (D ? pb - sz : pa));
+    vload<T, V>(au, v + (U ? pb + sz : pa));
+    vload<T, V>(bs, v + (S ? pa - hx : pb));
+    vload<T, V>(bn, v + (N ? pa + hx : pb));
+    vload<T, V>(bd, v + (D ? pa - sz : pb));
+    vload<T, V>(bu, v + (U ? pa + sz : pb));
+    w = v[tp > 0 ? pb - 1 : pa];               // west of the first A
+    e = v[tp + V < hx ? pa + V : pb + V - 1];  // east of the last B
+  }
+};
+// Their faces: each line through its table where it is one value, else loaded
+// under a scalar branch (as FaceLd), in loads of up to 16 bytes per lane.
+template <typename T, int V>
+struct PairFaces {
+  static constexpr int W = 16 / sizeof(T) < 2 * V ? 16 / sizeof(T) : 2 * V;
+  T t[5];
+  bool u[5];
+  T x[2 * V + 1], s[2 * V], n[2 * V], d[2 * V], up[2 * V];
+  __device__ __forceinline__ static void row(T* d, const T* __restrict__ p) {
+#pragma unroll
+    for (int q = 0; q < 2 * V; q += W) vload<T, W>(*reinterpret_cast<T(*)[W]>(d + q), p + q);
+  }
+  __device__ __forceinline__ void load(const Dims& nn, const FaceTab<T>& ft, const T* __restrict__ bx,
+                                       const T* __restrict__ by, const T* __restrict__ bz, int ju, int ku, int tp,
+                                       int j, int k) {
+    u[0] = line_val(ft.x, ju + nn.ny * ku, t[0]);
+    u[1] = line_val(ft.y, ju + (nn.ny + 1) * ku, t[1]);
+    u[2] = line_val(ft.y, ju + 1 + (nn.ny + 1) * ku, t[2]);
+    u[3] = line_val(ft.z, ju + nn.ny * ku, t[3]);
+    u[4] = line_val(ft.z, ju + nn.ny * (ku + 1), t[4]);
+    const size_t fx = 2 * tp + (size_t)(nn.nx + 1) * (j + (size_t)nn.ny * k);
+    const size_t fy = 2 * tp + (size_t)nn.nx * (j + (size_t)(nn.ny + 1) * k);
+    const size_t fz = 2 * tp + (size_t)nn.nx * (j + (size_t)nn.ny * k);
+    if (!u[0]) {
+      row(x, bx + fx);
+      x[2 * V] = bx[fx + 2 * V];
+    }
+    if (!u[1]) row(s, by + fy);
+    if (!u[2]) row(n, by + fy + nn.nx);
+    if (!u[3]) row(d, bz + fz);
+    if (!u[4]) row(up, bz + fz + (size_t)nn.nx * nn.ny);
+  }
+  // A v at the p-th cell of the lane's 2 V (p = 2 q: A of pair q), without
+  // 1/h^2; i: its column (nx is even, so a pair's middle face is inside);
+  // inner: the cell is below the top row
+  __device__ __forceinline__ T apply(const Dims& nn, int p, int i, T c, T w, T e, T vs, T vn, T vd, T vu,
+                                     bool inner) const {
+    const T cw = u[0] ? (i > 0 ? t[0] : (T)0) : x[p], ce = u[0] ? (i < nn.nx - 1 ? t[0] : (T)0) : x[p + 1];
+    return cell_A<T>(c, w, e, vs, vn, vd, vu, cw, ce, u[1] ? t[1] : s[p], u[2] ? t[2] : n[p], u[3] ? t[3] : d[p],
+                     u[4] ? t[4] : up[p], inner);
+  }
+  // both cells of pair q
+  __device__ __forceinline__ void apply2(const Dims& nn, const PairNb<T, V>& v, int q, int tp, bool inner, T& a,
+                                         T& b) const {
+    const int i = 2 * (tp + q);
+    const T w = q > 0 ? v.b[q > 0 ? q - 1 : 0] : v.w, e = q < V - 1 ? v.a[q < V - 1 ? q + 1 : q] : v.e;
+    a = apply(nn, 2 * q, i, v.a[q], w, v.b[q], v.as[q], v.an[q], v.ad[q], v.au[q], inner);
+    b = apply(nn, 2 * q + 1, i + 1, v.b[q], v.a[q], e, v.bs[q], v.bn[q], v.bd[q], v.bu[q], inner);
+  }
+};
+
+// k_resid_restrict_pairs with V adjacent pairs per lane (the wide passes' levels)
+template <typename T, int V>
+__global__ void __launch_bounds__(256) k_resid_restrict_wide(Dims nf, T ih2, const T* __restrict__ bx,
+                                                             const T* __restrict__ by, const T* __restrict__ bz,
+                                                             const T* __restrict__ b, const T* __restrict__ e,
+                                                             Dims nc, int csplit, T inv, T* __restrict__ bc,
+                                                             FaceTab<T> ft) {
+  __shared__ T sr[2][2][2][V][64];   // [dk][dj][di][pair of the lane][lane]
+  const Tile tl = xcd_tile();
+  const int lane = threadIdx.x, dj = threadIdx.y, dk = threadIdx.z;
+  const int hx = nf.nx >> 1;
+  const int tpr = V * (tl.x * 64 + lane), j = 2 * tl.y + dj, k = 2 * tl.z + dk;
+  const bool live = tpr < hx;
+  const int tp = min(tpr, hx - V);   // a lane past the row's end stores nothing
+  const size_t P = (size_t)hx * nf.ny * nf.nz, sz = (size_t)hx * nf.ny;
+  const size_t pos = tp + (size_t)hx * (j + (size_t)nf.ny * k);
+  const int par = (j + k) & 1;
+  const size_t pa = par * P + pos, pb = (1 - par) * P + pos;
+  PairNb<T, V> v;
+  v.load(e, pa, pb, hx, sz, tp, j > 0, j < nf.ny - 1, k > 0, k < nf.nz - 1);
+  T ba[V], bb[V];
+  vload<T, V>(ba, b + pa);
+  vload<T, V>(bb, b + pb);
+  PairFaces<T, V> F;
+  F.load(nf, ft, bx, by, bz, __builtin_amdgcn_readfirstlane(j), __builtin_amdgcn_readfirstlane(k), tp, j, k);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < V; ++q) {
+    T a, c;
+    F.apply2(nf, v, q, tp, k < nf.nz - 1, a, c);
+    sr[dk][dj][0][q][lane] = ba[q] - ih2 * a;
+    sr[dk][dj][1][q][lane] = bb[q] - ih2 * c;
+  }
+  __syncthreads();
+  if ((dj | dk) || !live) return;
+  const int J = tl.y, K = tl.z;
+  const int chx = (nc.nx + 1) >> 1, cP = chx * nc.ny * nc.nz;
+#pragma unroll
+  for (int q = 0; q < V; ++q) {
+    T sum = 0;
+#pragma unroll
+    for (int qk = 0; qk < 2; ++qk)
+#pragma unroll
+      for (int qj = 0; qj < 2; ++qj)
+#pragma unroll
+        for (int qi = 0; qi < 2; ++qi) sum += sr[qk][qj][qi][q][lane];
+    const int I = tp + q;
+    const int ci = csplit ? ((I + J + K) & 1) * cP + (I >> 1) + chx * (J + nc.ny * K) : I + nc.nx * (J + nc.ny * K);
+    bc[ci] = sum * inv;
+  }
 }
 
 // colour-split fine correction += parent's coarse correction (nu_post == 0)
@@ -1851,20 +2303,17 @@ __global__ void k_f2d(const float* __restrict__ a, double* __restrict__ b, size_
 }
 
 // the FP32 V-cycle's result to FP64 z, fused with the per-block sums of r z
-// and r z_old (block order); every thread reaches the reduction
+// (block order); every thread reaches the reduction
 __global__ void __launch_bounds__(256) k_f2d_dots(const float* __restrict__ a, double* __restrict__ z, size_t n,
-                                                  const double* __restrict__ r, const double* __restrict__ zold,
-                                                  double* __restrict__ partials) {
+                                                  const double* __restrict__ r, double* __restrict__ partials) {
   const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  double v[2] = {0.0, 0.0};
+  double v[1] = {0.0};
   if (q < n) {
     const double zq = (double)a[q];
     z[q] = zq;
-    const double rv = r[q];
-    v[0] = rv * zq;
-    v[1] = rv * zold[q];
+    v[0] = r[q] * zq;
   }
-  block_partials<2>(v, partials, (int)blockIdx.x);
+  block_partials<1>(v, partials, (int)blockIdx.x);
 }
 
 // ------------------------------------------------------------------ CG (FP64)
@@ -1923,7 +2372,7 @@ __global__ void __launch_bounds__(256) k_resid_norm(Dims n, double ih2, const do
   block_partials<2>(v, partials, tl.lin);
 }
 
-// rho = <r, z>
+// <r, z>
 __global__ void __launch_bounds__(256) k_dot_rho(Dims n, const double* __restrict__ r,
                                                  const double* __restrict__ z, double* __restrict__ partials) {
   CELL_INDEX;
@@ -1931,23 +2380,9 @@ __global__ void __launch_bounds__(256) k_dot_rho(Dims n, const double* __restric
   block_partials<1>(v, partials, tl.lin);
 }
 
-// flexible (Polak-Ribiere) beta = (<r, zn> - <r, z>) / rho, then rho = <r, zn>
-__global__ void __launch_bounds__(256) k_dots_beta(Dims n, const double* __restrict__ r,
-                                                   const double* __restrict__ zn,
-                                                   const double* __restrict__ z,
-                                                   double* __restrict__ partials) {
-  CELL_INDEX;
-  double v[2] = {0.0, 0.0};
-  if (inside) {
-    const double rc = r[c];
-    v[0] = rc * zn[c];
-    v[1] = rc * z[c];
-  }
-  block_partials<2>(v, partials, tl.lin);
-}
-
 // d = zn + beta d_old, q = A d = A zn + beta q_old (first: d = zn, q = A zn);
-// alpha = rho / <d, q>.  Carrying q = A d by its recurrence keeps the
+// alpha = rho / <d, q>, and <z, q>, from which the next iteration's
+// <r, z_old> follows (see k_finalize).  Carrying q = A d by its recurrence keeps the
 // stencil on zn alone, and d_old and q_old are read pointwise: the stencil's
 // load count, not its bytes, limits this kernel.  With xupd it also applies
 // the previous iteration's x += alpha d_old (alpha still in scal, d_old
@@ -1965,7 +2400,7 @@ __global__ void __launch_bounds__(256) k_dir_spmv(Dims n, double ih2, const doub
                                                   double* __restrict__ partials, double* __restrict__ x,
                                                   int xupd, FaceTab<double> ft) {
   CELL_INDEX;
-  double v[1] = {0.0};
+  double v[2] = {0.0, 0.0};
   // Every load is issued before the shuffles wait for zc: the faces and the
   // y and z neighbours through in-range indices (a lane outside the grid
   // reads around cell 0), the row-end lanes' x neighbour, and d_old, q_old
@@ -2009,8 +2444,152 @@ __global__ void __launch_bounds__(256) k_dir_spmv(Dims n, double ih2, const doub
     dnew[c] = dc;
     q[c] = qc;
     v[0] = dc * qc;
+    v[1] = zc * qc;
   }
-  block_partials<1>(v, partials, tl.lin);
+  block_partials<2>(v, partials, tl.lin);
+}
+
+// The split CG vectors' kernels.  On a finest level of the wide passes r, z,
+// d and q are colour-split like the V-cycle's vectors, so the cycle reads r
+// and leaves z in place: no split copy of r is written (8 B per cell), the
+// last pass stores only the red half of z, and every access of these kernels
+// is a whole 16-byte load or store per lane.  b and the caller's pressure stay
+// in natural order: the residual leaves a split copy of the guess, the
+// direction updates advance it, and the last update writes the result back in
+// natural order.  A lane takes two pairs.
+//
+// d, q, alpha and <z, q> as k_dir_spmv
+__global__ void __launch_bounds__(256) k_dir_spmv_split(Dims n, double ih2, const double* __restrict__ bx,
+                                                        const double* __restrict__ by,
+                                                        const double* __restrict__ bz,
+                                                        const double* __restrict__ zn,
+                                                        const double* __restrict__ dold,
+                                                        double* __restrict__ dnew, double* __restrict__ q, int first,
+                                                        const double* __restrict__ scal,
+                                                        double* __restrict__ partials, double* __restrict__ x,
+                                                        int xupd, FaceTab<double> ft) {
+  constexpr int V = 2;
+  WIDE_INDEX;
+  const int par = (j + k) & 1;
+  const size_t pa = par * P + pos, pb = (1 - par) * P + pos;
+  PairNb<double, V> z;
+  z.load(zn, pa, pb, hx, sz, tp, S, N, D, U);
+  double da[V], db[V], qa[V], qb[V], xa[V] = {}, xb[V] = {};
+  vload_once<double, V>(da, dold + pa);
+  vload_once<double, V>(db, dold + pb);
+  vload_once<double, V>(qa, q + pa);
+  vload_once<double, V>(qb, q + pb);
+  if (xupd) {
+    vload_once<double, V>(xa, x + pa);
+    vload_once<double, V>(xb, x + pb);
+  }
+  PairFaces<double, V> F;
+  F.load(n, ft, bx, by, bz, ju, k, tp, j, k);
+  __builtin_amdgcn_sched_barrier(0);
+  double v[2] = {0.0, 0.0};
+  const double al = xupd ? scal[S_ALPHA] : 0.0, beta = first ? 0.0 : scal[S_BETA];
+  double aa[V], ab[V];
+#pragma unroll
+  for (int p = 0; p < V; ++p) F.apply2(n, z, p, tp, k < n.nz - 1, aa[p], ab[p]);
+  if (live) {
+    if (xupd) {
+#pragma unroll
+      for (int p = 0; p < V; ++p) {
+        xa[p] = xa[p] + al * da[p];
+        xb[p] = xb[p] + al * db[p];
+      }
+      vstore_once<double, V>(x + pa, xa);
+      vstore_once<double, V>(x + pb, xb);
+    }
+#pragma unroll
+    for (int p = 0; p < V; ++p) {
+      da[p] = first ? z.a[p] : z.a[p] + beta * da[p];
+      db[p] = first ? z.b[p] : z.b[p] + beta * db[p];
+      qa[p] = first ? ih2 * aa[p] : ih2 * aa[p] + beta * qa[p];
+      qb[p] = first ? ih2 * ab[p] : ih2 * ab[p] + beta * qb[p];
+      v[0] += da[p] * qa[p] + db[p] * qb[p];
+      v[1] += z.a[p] * qa[p] + z.b[p] * qb[p];
+    }
+    vstore_once<double, V>(dnew + pa, da);
+    vstore_once<double, V>(dnew + pb, db);
+    vstore_once<double, V>(q + pa, qa);
+    vstore_once<double, V>(q + pb, qb);
+  }
+  block_partials<2>(v, partials, tl.lin);
+}
+
+// r = b - A x (b, x natural, r split) and the totals, as k_resid_norm; xs, when
+// set, receives x split
+__global__ void __launch_bounds__(256) k_resid_norm_split(Dims n, double ih2, const double* __restrict__ bx,
+                                                          const double* __restrict__ by,
+                                                          const double* __restrict__ bz,
+                                                          const double* __restrict__ b,
+                                                          const double* __restrict__ x, double* __restrict__ r,
+                                                          double* __restrict__ partials, FaceTab<double> ft,
+                                                          double* __restrict__ xs_) {
+  constexpr int V = 2;
+  WIDE_INDEX;
+  const int par = (j + k) & 1;
+  const size_t sxy = (size_t)n.nx * n.ny, c = 2 * (size_t)tp + (size_t)n.nx * (j + (size_t)n.ny * k);
+  double xc[4], xs[4], xn[4], xd[4], xu[4], bc[4];
+  auto four = [](double (&d)[4], const double* __restrict__ p) {
+    vload<double, 2>(*reinterpret_cast<double(*)[2]>(&d[0]), p);
+    vload<double, 2>(*reinterpret_cast<double(*)[2]>(&d[2]), p + 2);
+  };
+  four(xc, x + c);
+  four(xs, x + (S ? c - n.nx : c));
+  four(xn, x + (N ? c + n.nx : c));
+  four(xd, x + (D ? c - sxy : c));
+  four(xu, x + (U ? c + sxy : c));
+  four(bc, b + c);
+  const double xw = x[tp > 0 ? c - 1 : c], xe = x[tp + V < hx ? c + 4 : c + 3];
+  PairFaces<double, V> F;
+  F.load(n, ft, bx, by, bz, ju, k, tp, j, k);
+  __builtin_amdgcn_sched_barrier(0);
+  double v[2] = {0.0, 0.0}, rc[4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const double a = F.apply(n, p, 2 * tp + p, xc[p], p > 0 ? xc[p > 0 ? p - 1 : 0] : xw, p < 3 ? xc[p < 3 ? p + 1 : p] : xe,
+                             xs[p], xn[p], xd[p], xu[p], k < n.nz - 1);
+    rc[p] = bc[p] - ih2 * a;
+    if (live) {
+      v[0] += rc[p] * rc[p];
+      v[1] += bc[p] * bc[p];
+    }
+  }
+  if (live) {
+    const double ra[2] = {rc[0], rc[2]}, rb[2] = {rc[1], rc[3]};
+    vstore<double, 2>(r + par * P + pos, ra);
+    vstore<double, 2>(r + (1 - par) * P + pos, rb);
+    if (xs_) {
+      const double ya[2] = {xc[0], xc[2]}, yb[2] = {xc[1], xc[3]};
+      vstore<double, 2>(xs_ + par * P + pos, ya);
+      vstore<double, 2>(xs_ + (1 - par) * P + pos, yb);
+    }
+  }
+  block_partials<2>(v, partials, tl.lin);
+}
+
+// x = xs + alpha d, xs and d split, x natural
+__global__ void __launch_bounds__(256) k_x_update_split(Dims n, const double* __restrict__ d,
+                                                        const double* __restrict__ xs, double* __restrict__ x,
+                                                        const double* __restrict__ scal) {
+  constexpr int V = 2;
+  WIDE_INDEX;
+  if (!live) return;
+  const int par = (j + k) & 1;
+  const size_t c = 2 * (size_t)tp + (size_t)n.nx * (j + (size_t)n.ny * k);
+  double da[V], db[V], xa[V], xb[V];
+  vload<double, V>(da, d + par * P + pos);
+  vload<double, V>(db, d + (1 - par) * P + pos);
+  vload<double, V>(xa, xs + par * P + pos);
+  vload<double, V>(xb, xs + (1 - par) * P + pos);
+  const double al = scal[S_ALPHA];
+#pragma unroll
+  for (int p = 0; p < V; ++p) {
+    const double y[2] = {xa[p] + al * da[p], xb[p] + al * db[p]};
+    vstore<double, 2>(x + c + 2 * p, y);
+  }
 }
 
 // r -= alpha q; ||r||^2 (the matching x += alpha d is applied by the next
@@ -2114,8 +2693,23 @@ __global__ void __launch_bounds__(1024) k_finalize(const double* __restrict__ pa
         hscal[S_TRR] = a;
         break;
       case FIN_RHO: scal[S_RHO] = a; break;
-      case FIN_BETA: scal[S_BETA] = (a - b) / scal[S_RHO]; scal[S_RHO] = a; break;
-      case FIN_ALPHA: scal[S_DQ] = a; scal[S_ALPHA] = scal[S_RHO] / a; break;
+      case FIN_BETA: {
+        // flexible (Polak-Ribiere) beta = (<r, z> - <r, z_old>) / rho, then
+        // rho = <r, z>.  r = r_old - alpha q, so <r, z_old> = rho - alpha
+        // <q, z_old>, whose product the direction update took where it had
+        // z_old and q at hand: summing r z_old here would read z_old again,
+        // 8 B per cell.  It differs from that sum by rounding of rho's size,
+        // 1e-16 in beta.
+        const double rho = scal[S_RHO];
+        scal[S_BETA] = (a - (rho - scal[S_ALPHA] * scal[S_ZQ])) / rho;
+        scal[S_RHO] = a;
+        break;
+      }
+      case FIN_ALPHA:
+        scal[S_DQ] = a;
+        scal[S_ZQ] = b;
+        scal[S_ALPHA] = scal[S_RHO] / a;
+        break;
       case FIN_RR:
         scal[S_RR] = a;
         hscal[S_RR] = a;
@@ -2128,12 +2722,43 @@ __global__ void __launch_bounds__(1024) k_finalize(const double* __restrict__ pa
 }  // namespace
 
 // ------------------------------------------------------------------ launchers
+// Pairs per lane of a level's smoothing passes: 0 where the one-pair forms
+// run.  The wide forms need whole lanes (hx a multiple of V) and rows that
+// fill most of a wavefront, and pay where the level has enough of them to keep
+// the chip busy: at 256 x 128 x 128 an FP64 colour pass takes 13.3 us against
+// 18.3 (FP32: 11.4 against 13.5), at 128 x 64 x 64, where a row fills half a
+// wavefront, 5.2 against 4.3 (FP32: 5.0 against 3.7).  FP32 takes four pairs
+// where such a row still fills a wavefront.
+template <typename T>
+static int wide_pairs(const Dims& n) {
+  const int hx = n.nx / 2;
+  if (n.ny < 4 || n.nx % 2 || (long)n.nx * n.ny * n.nz < (1L << 20)) return 0;
+  if (sizeof(T) == 4 && hx % 4 == 0 && hx / 4 >= 48) return 4;
+  return hx % 2 == 0 && hx / 2 >= 48 ? 2 : 0;
+}
+static dim3 wide_grid(const Dims& n, int V) {
+  return dim3((n.nx / 2 / V + 63) / 64, (n.ny + 3) / 4, n.nz);
+}
+bool cg_split(const Dims& n) { return wide_pairs<double>(n) == 2; }
+
 template <typename T>
 void launch_gs(const Level& L, const T* bx, const T* by, const T* bz, const T* b, T* e, int colour,
                hipStream_t st, KTimer* kt, T* nat) {
   const bool fine = (L.h == L.h0);
   const FaceTab<T> ft = face_tab(L, bx);
   const bool tab1 = !fine && ft.x != nullptr;   // a coarse level with line tables
+  if (const int V = nat ? 0 : wide_pairs<T>(L.n)) {
+    auto kern = V == 2 ? k_gs_wide<T, 2> : k_gs_wide<T, 16 / sizeof(T)>;
+    const dim3 grid = wide_grid(L.n, V), blk(64, 4);
+    if (kt && kt->n < kt->cap) {
+      hipExtLaunchKernelGGL(kern, grid, blk, 0, st, kt->ev[2 * kt->n], kt->ev[2 * kt->n + 1], 0, L.n,
+                            (T)(L.h * L.h), bx, by, bz, b, e, colour, ft);
+      ++kt->n;
+    } else {
+      hipLaunchKernelGGL(kern, grid, blk, 0, st, L.n, (T)(L.h * L.h), bx, by, bz, b, e, colour, ft);
+    }
+    return;
+  }
   const int pl = gs_planes<T>(fine || tab1);   // planes per thread
   Geo g = geo3((L.n.nx + 1) / 2, L.n.ny, (L.n.nz + pl - 1) / pl);
   auto kern = fine ? k_gs<T, true> : tab1 ? k_gs_c1<T> : k_gs<T, false>;
@@ -2153,6 +2778,12 @@ void launch_gs_first(const Level& L, const T* bx, const T* by, const T* bz, cons
   const bool fine = (L.h == L.h0);
   const FaceTab<T> ft = face_tab(L, bx);
   const bool tab1 = !fine && ft.x != nullptr && !b_natural;   // a coarse level with line tables
+  if (const int V = b_natural ? 0 : wide_pairs<T>(L.n)) {
+    auto kern = V == 2 ? k_gs_first_wide<T, 2, T> : k_gs_first_wide<T, 16 / sizeof(T), T>;
+    hipLaunchKernelGGL(kern, wide_grid(L.n, V), dim3(64, 4), 0, st, L.n, (T)(L.h * L.h), bx, by, bz, b, invd, e, bs,
+                       bcopy, ft, red_out ? 1 : 0);
+    return;
+  }
   void (*kern)(Dims, T, const T*, const T*, const T*, const T*, const T*, T*, T*, T*, FaceTab<T>, int);
   if (b_natural)
     kern = fine ? k_gs_first<T, true, true> : k_gs_first<T, false, true>;
@@ -2168,6 +2799,12 @@ void launch_gs_prolong(const Level& L, const T* bx, const T* by, const T* bz, co
   const bool fine = (L.h == L.h0);
   const FaceTab<T> ft = face_tab(L, bx);
   const bool tab1 = !fine && ft.x != nullptr;   // a coarse level with line tables
+  if (const int V = L.f[0] == 2 ? wide_pairs<T>(L.n) : 0) {
+    auto kern = V == 2 ? k_gs_prolong_wide<T, 2> : k_gs_prolong_wide<T, 16 / sizeof(T)>;
+    hipLaunchKernelGGL(kern, wide_grid(L.n, V), dim3(64, 4), 0, st, L.n, (T)(L.h * L.h), bx, by, bz, b, e, C.n,
+                       L.f[1] >> 1, L.f[2] >> 1, ec_split ? 1 : 0, ec, bcopy, ft);
+    return;
+  }
   const int pl = gs_planes<T>(fine || tab1);   // planes per thread
   Geo g = geo3((L.n.nx + 1) / 2, L.n.ny, (L.n.nz + pl - 1) / pl);
   auto kern = fine ? k_gs_prolong<T, true> : tab1 ? k_gs_prolong_c1<T> : k_gs_prolong<T, false>;
@@ -2290,6 +2927,12 @@ void launch_resid_restrict(const Level& F, const T* bx, const T* by, const T* bz
                            const T* e, const Level& C, T* bc, bool c_split, hipStream_t st) {
   const T ih2 = (T)(1.0 / (F.h * F.h));
   if (resid_pairs_fit(F)) {
+    if (const int V = wide_pairs<T>(F.n)) {
+      auto kern = V == 2 ? k_resid_restrict_wide<T, 2> : k_resid_restrict_wide<T, 16 / sizeof(T)>;
+      hipLaunchKernelGGL(kern, dim3((F.n.nx / 2 / V + 63) / 64, F.n.ny / 2, F.n.nz / 2), dim3(64, 2, 2), 0, st, F.n,
+                         ih2, bx, by, bz, b, e, C.n, c_split ? 1 : 0, (T)0.125, bc, face_tab(F, bx));
+      return;
+    }
     const dim3 grid((F.n.nx / 2 + 63) / 64, F.n.ny / 2, F.n.nz / 2);
     hipLaunchKernelGGL(k_resid_restrict_pairs<T>, grid, dim3(64, 2, 2), 0, st, F.n, ih2, bx, by, bz, b, e, C.n,
                        c_split ? 1 : 0, (T)0.125, bc, face_tab(F, bx));
@@ -2368,11 +3011,29 @@ void launch_d2f(const double* a, float* b, size_t n, hipStream_t st) {
 
 template <typename T>
 int launch_gs_last_dots(const Level& L, const T* bx, const T* by, const T* bz, const T* b, const T* e,
-                        double* nat, const double* r, const double* zold, double* partials, hipStream_t st) {
+                        double* nat, const double* r, double* partials, hipStream_t st) {
   Geo g = geo3((L.n.nx + 1) / 2, L.n.ny, L.n.nz);
   hipLaunchKernelGGL(k_gs_last_dots<T>, g.grid, g.block, 0, st, L.n, (T)(L.h * L.h), bx, by, bz, b, e, nat, r,
-                     zold, partials, face_tab(L, bx));
+                     partials, face_tab(L, bx));
   return (int)(g.grid.x * g.grid.y * g.grid.z);
+}
+
+// Two pairs per lane in both precisions: FP64 vectors take part, whose 16
+// bytes are two values (four pairs read them at a lane stride of 32 bytes).
+template <typename T>
+void launch_gs_first_split(const Level& L, const T* bx, const T* by, const T* bz, const double* r, const T* invd, T* e,
+                           T* bs, hipStream_t st, bool red_out) {
+  hipLaunchKernelGGL((k_gs_first_wide<T, 2, double>), wide_grid(L.n, 2), dim3(64, 4), 0, st, L.n, (T)(L.h * L.h), bx,
+                     by, bz, r, invd, e, bs, (T*)nullptr, face_tab(L, bx), red_out ? 1 : 0);
+}
+
+template <typename T>
+int launch_gs_last_dots_split(const Level& L, const T* bx, const T* by, const T* bz, const T* b, const T* e, double* z,
+                              const double* r, double* partials, hipStream_t st) {
+  const dim3 g = wide_grid(L.n, 2);
+  hipLaunchKernelGGL((k_gs_last_dots_wide<T, 2>), g, dim3(64, 4), 0, st, L.n, (T)(L.h * L.h), bx, by, bz, b, e, z, r,
+                     partials, face_tab(L, bx));
+  return (int)(g.x * g.y * g.z);
 }
 
 void launch_gs_first_nat64(const Level& L, const float* bx, const float* by, const float* bz, const double* b,
@@ -2382,10 +3043,9 @@ void launch_gs_first_nat64(const Level& L, const float* bx, const float* by, con
                      by, bz, b, invd, e, bs, bcopy, face_tab(L, bx), red_out ? 1 : 0);
 }
 
-int launch_f2d_dots(const float* a, double* z, size_t n, const double* r, const double* zold, double* partials,
-                    hipStream_t st) {
+int launch_f2d_dots(const float* a, double* z, size_t n, const double* r, double* partials, hipStream_t st) {
   const int nb = (int)((n + 255) / 256);
-  hipLaunchKernelGGL(k_f2d_dots, dim3(nb), dim3(256), 0, st, a, z, n, r, zold, partials);
+  hipLaunchKernelGGL(k_f2d_dots, dim3(nb), dim3(256), 0, st, a, z, n, r, partials);
   return nb;
 }
 
@@ -2399,7 +3059,7 @@ int cg_blocks(const Dims& n) {
 }
 
 static void finalize(const CgScratch& cs, int nparts, int mode, hipStream_t st) {
-  const int nv = (mode == FIN_RESID0 || mode == FIN_TRR || mode == FIN_BETA) ? 2 : 1;
+  const int nv = (mode == FIN_RESID0 || mode == FIN_TRR || mode == FIN_ALPHA) ? 2 : 1;
   const double* src = cs.partials;
   // Beyond one batch of 16 loads per thread, one workgroup walking every
   // partial waits on a chain of batches (27 us for the 131072 blocks of a
@@ -2427,43 +3087,44 @@ static void finalize(const CgScratch& cs, int nparts, int mode, hipStream_t st) 
     hipLaunchKernelGGL(k_finalize<16>, g, b, 0, st, src, nparts, nv, mode, cs.scal, cs.hscal);
 }
 
-void launch_finalize_beta(const CgScratch& cs, int nparts, hipStream_t st) { finalize(cs, nparts, FIN_BETA, st); }
+void launch_finalize_dot(const CgScratch& cs, int nparts, int mode, hipStream_t st) { finalize(cs, nparts, mode, st); }
 
-void launch_resid_norm(const Dims& n, double h, const double* bx, const double* by, const double* bz,
-                       const double* b, const double* x, double* r, const CgScratch& cs, int mode,
-                       hipStream_t st, const FaceTab<double>& ft) {
-  Geo g = geo3(n.nx, n.ny, n.nz);   // blockDim.x == 64: a wavefront per x-line
-  hipLaunchKernelGGL(k_resid_norm, g.grid, g.block, 0, st, n, 1.0 / (h * h), bx, by, bz, b, x, r,
-                     cs.hpart ? cs.hpart : cs.partials, ft);
-  if (!cs.hpart) finalize(cs, (int)(g.grid.x * g.grid.y * g.grid.z), mode, st);
+int launch_resid_norm(const Dims& n, double h, const double* bx, const double* by, const double* bz, const double* b,
+                      const double* x, double* r, const CgScratch& cs, int mode, hipStream_t st,
+                      const FaceTab<double>& ft, bool split, double* xs) {
+  // blockDim.x == 64: a wavefront per x-line
+  const Geo g = split ? Geo{wide_grid(n, 2), dim3(64, 4)} : geo3(n.nx, n.ny, n.nz);
+  double* part = cs.hpart ? cs.hpart : cs.partials;
+  if (split)
+    hipLaunchKernelGGL(k_resid_norm_split, g.grid, g.block, 0, st, n, 1.0 / (h * h), bx, by, bz, b, x, r, part, ft, xs);
+  else
+    hipLaunchKernelGGL(k_resid_norm, g.grid, g.block, 0, st, n, 1.0 / (h * h), bx, by, bz, b, x, r, part, ft);
+  const int np = (int)(g.grid.x * g.grid.y * g.grid.z);
+  if (!cs.hpart) finalize(cs, np, mode, st);
+  return np;
 }
 
-void launch_dot_rho(const Dims& n, const double* r, const double* z, const CgScratch& cs, hipStream_t st) {
+void launch_dot(const Dims& n, const double* r, const double* z, const CgScratch& cs, int mode, hipStream_t st) {
   Geo g = geo3(n.nx, n.ny, n.nz);
   hipLaunchKernelGGL(k_dot_rho, g.grid, g.block, 0, st, n, r, z, cs.partials);
-  finalize(cs, (int)(g.grid.x * g.grid.y * g.grid.z), FIN_RHO, st);
-}
-
-void launch_dots_beta(const Dims& n, const double* r, const double* zn, const double* z,
-                      const CgScratch& cs, hipStream_t st) {
-  Geo g = geo3(n.nx, n.ny, n.nz);
-  hipLaunchKernelGGL(k_dots_beta, g.grid, g.block, 0, st, n, r, zn, z, cs.partials);
-  finalize(cs, (int)(g.grid.x * g.grid.y * g.grid.z), FIN_BETA, st);
+  finalize(cs, (int)(g.grid.x * g.grid.y * g.grid.z), mode, st);
 }
 
 void launch_dir_spmv(const Dims& n, double h, const double* bx, const double* by, const double* bz,
                      const double* zn, const double* dold, double* dnew, double* q, int first,
-                     const CgScratch& cs, hipStream_t st, KTimer* kt, double* x, const FaceTab<double>& ft) {
-  Geo g = geo3(n.nx, n.ny, n.nz);   // blockDim.x == 64: a wavefront per x-line
+                     const CgScratch& cs, hipStream_t st, KTimer* kt, double* x, const FaceTab<double>& ft, bool split) {
+  // blockDim.x == 64: a wavefront per x-line
+  const Geo g = split ? Geo{wide_grid(n, 2), dim3(64, 4)} : geo3(n.nx, n.ny, n.nz);
   const int xupd = x ? 1 : 0;
+  auto kern = split ? k_dir_spmv_split : k_dir_spmv;
   if (kt && kt->n < kt->cap) {
     (void)hipStreamSynchronize(st);
-    hipExtLaunchKernelGGL(k_dir_spmv, g.grid, g.block, 0, st, kt->ev[2 * kt->n], kt->ev[2 * kt->n + 1], 0,
+    hipExtLaunchKernelGGL(kern, g.grid, g.block, 0, st, kt->ev[2 * kt->n], kt->ev[2 * kt->n + 1], 0,
                           n, 1.0 / (h * h), bx, by, bz, zn, dold, dnew, q, first, (const double*)cs.scal,
                           cs.partials, x, xupd, ft);
     ++kt->n;
   } else {
-    hipLaunchKernelGGL(k_dir_spmv, g.grid, g.block, 0, st, n, 1.0 / (h * h), bx, by, bz, zn, dold, dnew, q,
+    hipLaunchKernelGGL(kern, g.grid, g.block, 0, st, n, 1.0 / (h * h), bx, by, bz, zn, dold, dnew, q,
                        first, (const double*)cs.scal, cs.partials, x, xupd, ft);
   }
   finalize(cs, (int)(g.grid.x * g.grid.y * g.grid.z), FIN_ALPHA, st);
@@ -2476,7 +3137,11 @@ void launch_cg_update(const Dims& n, const double* q, double* r, const CgScratch
   if (!cs.hpart) finalize(cs, (int)(g.grid.x * g.grid.y * g.grid.z), FIN_RR, st);
 }
 
-void launch_x_update(const Dims& n, const double* d, double* x, const CgScratch& cs, hipStream_t st) {
+void launch_x_update(const Dims& n, const double* d, double* x, const CgScratch& cs, hipStream_t st, const double* xs) {
+  if (xs) {
+    hipLaunchKernelGGL(k_x_update_split, wide_grid(n, 2), dim3(64, 4), 0, st, n, d, xs, x, (const double*)cs.scal);
+    return;
+  }
   Geo g = geo3(n.nx, n.ny, n.nz);
   hipLaunchKernelGGL(k_x_update, g.grid, g.block, 0, st, n, d, x, (const double*)cs.scal);
 }
@@ -2491,7 +3156,11 @@ void launch_apply_A(const Dims& n, double h, const double* bx, const double* by,
   template void launch_gs<T>(const Level&, const T*, const T*, const T*, const T*, T*, int, hipStream_t,   \
                              KTimer*, T*);                                                                \
   template int launch_gs_last_dots<T>(const Level&, const T*, const T*, const T*, const T*, const T*,     \
-                                      double*, const double*, const double*, double*, hipStream_t);       \
+                                      double*, const double*, double*, hipStream_t);                      \
+  template int launch_gs_last_dots_split<T>(const Level&, const T*, const T*, const T*, const T*, const T*, \
+                                            double*, const double*, double*, hipStream_t);                \
+  template void launch_gs_first_split<T>(const Level&, const T*, const T*, const T*, const double*, const T*, T*, \
+                                         T*, hipStream_t, bool);                                          \
   template void launch_gs_first<T>(const Level&, const T*, const T*, const T*, const T*, bool, const T*,  \
                                    T*, T*, hipStream_t, T*, bool);                                        \
   template void launch_gs_prolong<T>(const Level&, const T*, const T*, const T*, const T*, T*,           \
