@@ -83,6 +83,10 @@ struct ns_ctx {
     hipEvent_t ev[2]; // around the last inference
   } ax;               // x0 = NS_X0_AUTO
   int tail64, tail32; // first level of the LDS tail per precision (L: none)
+  bool top64, top32;  // that level is held in registers
+  int mlev64, mlev32; // the tail level from which the cycle is a matrix (L: none)
+  double* mat64;      // and that matrix
+  float* mat32;
   size_t lds64, lds32;
   double* pack64;     // the tail levels' bx, by, bz, 1/D (tail kernel's LDS image)
   float* pack32;
@@ -204,32 +208,47 @@ size_t tail_pack_elems(const Level* lev, int L, int l) {
   return tot;
 }
 
-// LDS elements of the tail from level l down: the pack, then b and e per
-// level, then (when the tail restricts, i.e. has more than one level) a
-// residual scratch of level l's size
-size_t tail_elems(const Level* lev, int L, int l) {
-  size_t tot = tail_pack_elems(lev, L, l);
-  for (int q = l; q < L; ++q) {
-    const Dims n = lev[q].n;
-    tot += 2 * pad4((size_t)n.nx * n.ny * n.nz);
+// first level from l down whose cycle the tail takes as a matrix (L: none)
+int tail_matrix_level(const Level* lev, int L, int l) {
+  for (; l < L; ++l) {
+    const Dims n = lev[l].n;
+    if (n.nx * n.ny * n.nz <= kTailMatrixCells && (n.nx + 1) / 2 * n.ny * n.nz <= 128) return l;
   }
-  return tot + (l < L - 1 ? pad4((size_t)lev[l].n.nx * lev[l].n.ny * lev[l].n.nz) : 0);
+  return L;
 }
 
-// first level whose tail fits the LDS budget and the workgroup (L: none)
-int plan_tail(const Level* lev, int L, size_t w, size_t* bytes) {
+// LDS elements of a tail whose first level l is held in registers: its
+// correction's planes; of the levels below the pack (face coefficients, 1/D), b
+// and e; the matrix product's and the residual's scratch; without a matrix,
+// the coarsest level's planes
+size_t tail_top_elems(const Level* lev, int L, int l) {
+  const Dims n = lev[l].n;
+  size_t tot = pad4(reg_planes(n));
+  if (l == L - 1) return tot;
+  tot += kTailThreads + tail_pack_elems(lev, L, l + 1) + pad4((size_t)n.nx * n.ny * n.nz);
+  for (int q = l + 1; q < L; ++q) tot += 2 * pad4((size_t)lev[q].n.nx * lev[q].n.ny * lev[q].n.nz);
+  if (tail_matrix_level(lev, L, l + 1) == L) tot += pad4(reg_planes(lev[L - 1].n));
+  return tot;
+}
+
+// First level of the tail (L: none): the finest whose cycle is a matrix, or
+// whose pairs the workgroup holds in registers (*top) with the levels below in
+// LDS.
+int plan_tail(const Level* lev, int L, size_t w, size_t* bytes, bool* top) {
   for (int l = 0; l < L; ++l) {
     const Dims n = lev[l].n;
     const size_t pairs = (size_t)((n.nx + 1) / 2) * n.ny * n.nz;
-    if (pairs > 2 * (size_t)kTailThreads) continue;
     if (L - l > kTailMaxLevels) continue;
-    const size_t b = tail_elems(lev, L, l) * w;
-    if (b <= kTailLdsBytes) {
-      *bytes = b;
-      return l;
-    }
+    // (a level of the LDS image has two pairs per thread at most, its coarsest one)
+    auto below = [&](int q) { return (size_t)((lev[q].n.nx + 1) / 2) * lev[q].n.ny * lev[q].n.nz; };
+    if (l < L - 1 && (below(l + 1) > 2 * (size_t)kTailThreads || below(L - 1) > (size_t)kTailThreads)) continue;
+    *top = tail_matrix_level(lev, L, l) != l;
+    *bytes = (*top ? tail_top_elems(lev, L, l) : 2 * pad4((size_t)n.nx * n.ny * n.nz) + kTailThreads) * w;
+    const size_t per = w == sizeof(double) ? tail_top_pairs<double>() : tail_top_pairs<float>();
+    if (pairs <= per * kTailThreads && *bytes <= kTailLdsBytes) return l;
   }
   *bytes = 0;
+  *top = false;
   return L;
 }
 
@@ -287,11 +306,15 @@ size_t carve(const ns_params* P, ns_ctx* X, char* base) {
   // LDS image (bx, by, bz, 1/D per level, each padded to 4 elements), so the
   // kernel stages them with one flat copy.
   size_t lds64 = 0, lds32 = 0;
-  const int t64 = plan_tail(lev, L, sizeof(double), &lds64);
-  const int t32 = plan_tail(lev, L, sizeof(float), &lds32);
+  bool top64 = false, top32 = false;
+  const int t64 = plan_tail(lev, L, sizeof(double), &lds64, &top64);
+  const int t32 = plan_tail(lev, L, sizeof(float), &lds32, &top32);
   const size_t np64 = tail_pack_elems(lev, L, t64), np32 = tail_pack_elems(lev, L, t32);
   double* pk64 = cv.take<double>(np64);
   float* pk32 = cv.take<float>(np32);
+  const int m64 = tail_matrix_level(lev, L, t64 + top64), m32 = tail_matrix_level(lev, L, t32 + top32);
+  double* mat64 = m64 < L ? cv.take<double>((size_t)kTailMatrixCells * kTailMatrixCells) : nullptr;
+  float* mat32 = m32 < L ? cv.take<float>((size_t)kTailMatrixCells * kTailMatrixCells) : nullptr;
   size_t o64 = 0, o32 = 0;
   auto from64 = [&](size_t n) {
     double* p = pk64 ? pk64 + o64 : nullptr;
@@ -406,6 +429,12 @@ size_t carve(const ns_params* P, ns_ctx* X, char* base) {
     for (int l = 0; l < L; ++l) X->lev[l] = lev[l];
     X->tail64 = t64;
     X->tail32 = t32;
+    X->top64 = top64;
+    X->top32 = top32;
+    X->mlev64 = m64;
+    X->mlev32 = m32;
+    X->mat64 = mat64;
+    X->mat32 = mat32;
     X->lds64 = lds64;
     X->lds32 = lds32;
     X->pack64 = pk64;
@@ -477,36 +506,34 @@ size_t tail_bytes(const ns_ctx* X) {
   return sizeof(T) == 8 ? X->lds64 : X->lds32;
 }
 
-// coarse coefficients of every level from level 0, and 1/D of every level
-// (the tail stages it), in precision T: one launch per level
-template <typename T>
-void build_hierarchy(ns_ctx* X) {
-  const Level& V0 = X->lev[0];
-  launch_invdiag<T>(V0, LV<T>::bx(V0), LV<T>::by(V0), LV<T>::bz(V0), LV<T>::invd(V0), 0 < tail_start<T>(X), X->st);
-  for (int l = 1; l < X->L; ++l) {
-    const Level& F = X->lev[l - 1];
-    const Level& C = X->lev[l];
-    launch_coarsen_level<T>(F, LV<T>::bx(F), LV<T>::by(F), LV<T>::bz(F), C, LV<T>::bx(C), LV<T>::by(C),
-                            LV<T>::bz(C), LV<T>::invd(C), l < tail_start<T>(X), X->st);
-  }
-  // the first coarse level's line tables, in the cycle's precision, where
-  // its passes run outside the tail and it is large enough for them to pay
-  if (X->face_tabs && X->L > 1 && 1 < tail_start<T>(X) && face_tables_pay(X->lev[1].n)) {
-    Level& V1 = X->lev[1];
-    if constexpr (sizeof(T) == 8) {
-      launch_face_tables<double>(V1.n, V1.bx, V1.by, V1.bz, V1.tx, V1.ty, V1.tz, X->st);
-      V1.tab_ok = true;
-    } else {
-      launch_face_tables<float>(V1.n, V1.bxf, V1.byf, V1.bzf, V1.txf, V1.tyf, V1.tzf, X->st);
-      V1.tabf_ok = true;
-    }
-  }
-}
-
+// The tail's launch: the cycle from its first level l0 down, to the level from
+// which it is a matrix where there is one.  bytes 0: that matrix is formed, l0
+// being its level.
 template <typename T>
 void launch_tail(ns_ctx* X, int l0, const T* b, T* e, size_t bytes) {
   TailDesc<T> D{};
-  D.nl = X->L - l0;
+  const int lm = sizeof(T) == 8 ? X->mlev64 : X->mlev32;
+  T* M;
+  if constexpr (sizeof(T) == 8)
+    M = X->mat64;
+  else
+    M = X->mat32;
+  const bool form = bytes == 0;
+  const bool top = !form && (sizeof(T) == 8 ? X->top64 : X->top32);
+  if (top) {
+    const Level& V = X->lev[l0];
+    D.top = 1;
+    D.nt = V.n;
+    for (int d = 0; d < 3; ++d) D.ft[d] = V.f[d];
+    D.h2t = (T)(V.h * V.h);
+    D.tbx = LV<T>::bx(V);
+    D.tby = LV<T>::by(V);
+    D.tbz = LV<T>::bz(V);
+    D.tid = LV<T>::invd(V);
+    ++l0;   // the levels of the LDS image
+  }
+  D.M = !form && lm < X->L ? M : nullptr;
+  D.nl = (D.M ? lm + 1 : X->L) - l0;
   D.nu_pre = X->P.nu_pre;
   D.nu_post = X->P.nu_post;
   D.coarse_sweeps = X->P.coarse_sweeps;
@@ -523,6 +550,7 @@ void launch_tail(ns_ctx* X, int l0, const T* b, T* e, size_t bytes) {
     D.n[q] = n;
     for (int d = 0; d < 3; ++d) D.f[q][d] = V.f[d];
     D.h2[q] = (T)(V.h * V.h);
+    if (D.M && q == D.nl - 1) break;   // the matrix stands for the level's coefficients
     D.obx[q] = take((size_t)(n.nx + 1) * n.ny * n.nz);
     D.oby[q] = take((size_t)n.nx * (n.ny + 1) * n.nz);
     D.obz[q] = take((size_t)n.nx * n.ny * (n.nz + 1));
@@ -534,11 +562,50 @@ void launch_tail(ns_ctx* X, int l0, const T* b, T* e, size_t bytes) {
     D.ob[q] = take(mc);
     D.oe[q] = take(mc);
   }
-  D.ors = D.nl > 1 ? take((size_t)D.n[0].nx * D.n[0].ny * D.n[0].nz) : 0;
-  D.pack = LV<T>::bx(X->lev[l0]);   // the pack starts with the first tail level's bx
+  if (top) {
+    if (D.nl > 0) D.ors = take((size_t)D.nt.nx * D.nt.ny * D.nt.nz);
+    D.oet = take(reg_planes(D.nt));
+    if (D.nl > 0 && !D.M) D.oeb = take(reg_planes(D.n[D.nl - 1]));
+  } else {
+    D.ors = D.nl > 1 ? take((size_t)D.n[0].nx * D.n[0].ny * D.n[0].nz) : 0;
+  }
+  D.omv = take(kTailThreads);
+  D.pack = D.nl > 0 ? LV<T>::bx(X->lev[l0]) : nullptr;   // (the pack of a level starts with its bx)
+  if (form) {
+    launch_tail_matrix<T>(D, off, M, X->st);
+    return;
+  }
   D.b0 = b;
   D.ge = e;
   launch_vcycle_tail<T>(D, bytes, X->st);
+}
+
+// coarse coefficients of every level from level 0, and 1/D of every level
+// (the tail stages it), in precision T: one launch per level
+template <typename T>
+void build_hierarchy(ns_ctx* X) {
+  const Level& V0 = X->lev[0];
+  launch_invdiag<T>(V0, LV<T>::bx(V0), LV<T>::by(V0), LV<T>::bz(V0), LV<T>::invd(V0), 0 < tail_start<T>(X), X->st);
+  for (int l = 1; l < X->L; ++l) {
+    const Level& F = X->lev[l - 1];
+    const Level& C = X->lev[l];
+    launch_coarsen_level<T>(F, LV<T>::bx(F), LV<T>::by(F), LV<T>::bz(F), C, LV<T>::bx(C), LV<T>::by(C),
+                            LV<T>::bz(C), LV<T>::invd(C), l < tail_start<T>(X), X->st);
+  }
+  if ((sizeof(T) == 8 ? X->mlev64 : X->mlev32) < X->L)
+    launch_tail<T>(X, sizeof(T) == 8 ? X->mlev64 : X->mlev32, nullptr, nullptr, 0);
+  // the first coarse level's line tables, in the cycle's precision, where
+  // its passes run outside the tail and it is large enough for them to pay
+  if (X->face_tabs && X->L > 1 && 1 < tail_start<T>(X) && face_tables_pay(X->lev[1].n)) {
+    Level& V1 = X->lev[1];
+    if constexpr (sizeof(T) == 8) {
+      launch_face_tables<double>(V1.n, V1.bx, V1.by, V1.bz, V1.tx, V1.ty, V1.tz, X->st);
+      V1.tab_ok = true;
+    } else {
+      launch_face_tables<float>(V1.n, V1.bxf, V1.byf, V1.bzf, V1.txf, V1.tyf, V1.tzf, X->st);
+      V1.tabf_ok = true;
+    }
+  }
 }
 
 // e_l = V(l, b_l); level 0 takes b0 and returns e0 in natural order.  Levels

@@ -162,14 +162,23 @@ struct KTimer {
   int n;
 };
 
-// Coarse-level tail of the V-cycle run by one workgroup from LDS.
+// Coarse-level tail of the V-cycle run by one workgroup: its first level is
+// held in registers, up to tail_top_pairs cell pairs per thread (FP64 4096
+// cells, FP32 6144: as many as the registers take), the levels below are in LDS.
 constexpr int kTailMaxLevels = 12;
 constexpr int kTailThreads = 512;
+template <typename T>
+constexpr int tail_top_pairs() { return sizeof(T) == 8 ? 4 : 6; }
 constexpr size_t kTailLdsBytes = 160 * 1024;   // gfx950: 160 KB of LDS per workgroup
+
+// The cycle from the first coarse level of at most this many cells down is one
+// linear map of that level's right-hand side; a solve forms its matrix once and
+// the tail multiplies by it.
+constexpr int kTailMatrixCells = 256;
 
 template <typename T>
 struct TailDesc {
-  int nl;                                   // levels in the tail (>= 1)
+  int nl;                                   // levels of the LDS image
   int nu_pre, nu_post, coarse_sweeps;
   Dims n[kTailMaxLevels];
   int f[kTailMaxLevels][3];                 // coarsening factor of level l towards l + 1
@@ -177,13 +186,34 @@ struct TailDesc {
   int obx[kTailMaxLevels], oby[kTailMaxLevels], obz[kTailMaxLevels];  // LDS offsets (elements)
   int ob[kTailMaxLevels], oe[kTailMaxLevels], oid[kTailMaxLevels];
   int ors;                                  // LDS scratch: one value per cell of the first level
-  // staging: the first npack LDS elements are a flat copy of pack (the tail
-  // levels' bx, by, bz, 1/D), then the first level's b goes to ob[0]
+  // staging: the first npack LDS elements are a flat copy of pack (the image's
+  // levels' bx, by, bz, 1/D)
   const T* pack;
   int npack;
-  const T* b0;
-  T* ge;                                    // correction of the first tail level (output)
+  const T* b0;                              // the first level's right-hand side and correction
+  T* ge;
+  // the matrix of the last level's cycle (column-major, null: the tail goes
+  // down to the coarsest level) and kTailThreads scratch entries for its product
+  const T* M;
+  int omv;
+  // the first level held in registers (top; else it is the image's one level,
+  // a matrix): its extents, face coefficients, 1/D, its correction's two colour
+  // planes in LDS (reg_planes), and without a matrix the coarsest level's
+  int top;
+  Dims nt;
+  int ft[3];
+  T h2t;
+  const T *tbx, *tby, *tbz, *tid;
+  int oet, oeb;
 };
+
+// LDS entries of such a level's correction: two planes of one entry per pair,
+// with room for a plane of pairs before, between and after them (neighbours
+// through a wall read it, at a face coefficient of zero)
+inline size_t reg_planes(const Dims& n) {
+  const size_t sz = (size_t)((n.nx + 1) / 2) * n.ny;
+  return 2 * sz * n.nz + 3 * sz;
+}
 
 enum FinMode { FIN_RESID0 = 0, FIN_RHO = 1, FIN_ALPHA = 2, FIN_RR = 3, FIN_BETA = 4, FIN_TRR = 5 };
 
@@ -302,6 +332,10 @@ void launch_face_tables(const Dims& n, const T* bx, const T* by, const T* bz, T*
 bool face_tables_pay(const Dims& n);
 template <typename T>
 void launch_vcycle_tail(const TailDesc<T>& D, size_t lds_bytes, hipStream_t st);
+// M: the matrix of the cycle over D's levels (every one within one wavefront's
+// pairs), N^2 entries for N cells of the first; elems: of the LDS image
+template <typename T>
+void launch_tail_matrix(const TailDesc<T>& D, int elems, T* M, hipStream_t st);
 void launch_d2f(const double* a, float* b, size_t n, hipStream_t st);
 void launch_f2d(const float* a, double* b, size_t n, hipStream_t st);
 // the V-cycle's last kernel (its FP64 result z in natural order) fused with

@@ -1920,370 +1920,586 @@ __global__ void __launch_bounds__(256) k_coarsen_level(Dims nf, int fx, int fy, 
 // ------------------------------------------------------- coarse-level tail
 // Every level from the first tail level down to the coarsest runs in one
 // workgroup with coefficients, 1/D, right-hand sides and corrections held in
-// LDS, so a smoothing pass costs a barrier instead of a launch.  Levels whose
-// cell pairs fit one wavefront run in wavefront 0 alone, ordered by
-// wavefront-level fences instead of workgroup barriers.  Each thread decodes
-// its cell pairs once per level visit, with every LDS index a pass of either
-// colour needs, so that a pass is its loads and its arithmetic.
+// LDS, so a smoothing pass costs a barrier instead of a launch.  Each thread
+// decodes its cell pairs once per level visit, and a pass is its loads and its
+// arithmetic.
+//
+// A launch runs every instruction of this kernel a few times at most, on a
+// compute unit whose instruction cache holds none of them: with each level's
+// passes written out for both colours and directions it was 54 KB of code, and
+// fetching it took more of the 20 us of a 128 x 64 x 64 cycle's tail than the
+// passes.  So there is one body: a loop over the level visits, one loop over
+// a visit's passes, and the colour a number.
 //
 // Walls carry beta = 0 and every correction in LDS is finite (the tail zeroes
 // them all before its first level), so a wall term beta_f e_nb is an exact
 // zero and the passes add it unconditionally; only the open top face, whose
 // coefficient is not zero, is dropped by a select.
-struct TailCell {
-  int c;          // cell index (b, e, 1/D, bz of the lower face)
-  int fx, fy;     // west x-face and south y-face
-  int w, e, s, n, d, u;   // neighbour cells; the cell itself through a wall or the top
-  bool ok, top;   // the cell exists (i < nx); it lies in the top row
-};
-struct TailPairs {
-  int ti[2], j[2], k[2];
-  int np;
-  TailCell cell[2][2];   // [pair][colour]: the pair's red cell, then its black one
-};
+// t / n for 0 <= t < 8192 with inv = 1.0f / n, exact ((t + 1/2) / n is at least
+// 1/(2n) from a whole number, and the product's error below 2^-11 / n): an
+// integer division by a number that is not a constant takes some thirty
+// instructions
+__device__ __forceinline__ int tail_div(int t, float inv) { return (int)(((float)t + 0.5f) * inv); }
 
-// lanes 0..nthr-1 take pairs t and t + nthr
+struct TailCell {
+  int c;                  // cell index (b, e, 1/D, bz of the lower face)
+  int fx, fy;             // west x-face and south y-face
+  int w, e, s, n, d, u;   // neighbour cells; the cell itself through a wall or the top
+  bool ok, top;           // the cell exists (i < nx; else the pair's other cell); it lies in the top row
+};
+// a thread's pairs: t and t + nthr
+struct TailPairs {
+  int np;
+  int i[2], j[2], k[2];                          // first column, row, plane
+  int c[2], fx[2], fy[2];                        // cell, west x-face and south y-face of the first column
+  int ds[2], dn[2], dd[2], du[2];                // distances of the neighbours, zero through a wall or the top
+};
 __device__ __forceinline__ void tail_decode(const Dims& n, int tid, int nthr, TailPairs& tp) {
-  const int hx = (n.nx + 1) >> 1;
+  const int hx = (n.nx + 1) >> 1, sxy = n.nx * n.ny;
   const int NP = hx * n.ny * n.nz;
-  const int sxy = n.nx * n.ny;
-  tp.np = 0;
+  const float ihx = 1.0f / (float)hx, iny = 1.0f / (float)n.ny;
+  tp.np = tid < NP ? (tid + nthr < NP ? 2 : 1) : 0;
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
-    const int t = tid + q * nthr;
-    if (t < NP) {
-      tp.ti[q] = t % hx;
-      const int r = t / hx;
-      tp.j[q] = r % n.ny;
-      tp.k[q] = r / n.ny;
-      tp.np = q + 1;
-      const int j = tp.j[q], k = tp.k[q];
+    const int t = min(tid + q * nthr, NP - 1), r = tail_div(t, ihx);
+    const int k = tail_div(r, iny), j = r - k * n.ny, i = 2 * (t - r * hx);
+    tp.i[q] = i;
+    tp.j[q] = j;
+    tp.k[q] = k;
+    tp.c[q] = i + n.nx * j + sxy * k;
+    tp.fx[q] = i + (n.nx + 1) * (j + n.ny * k);
+    tp.fy[q] = i + n.nx * (j + (n.ny + 1) * k);
+    tp.ds[q] = j > 0 ? -n.nx : 0;
+    tp.dn[q] = j < n.ny - 1 ? n.nx : 0;
+    tp.dd[q] = k > 0 ? -sxy : 0;
+    tp.du[q] = k < n.nz - 1 ? sxy : 0;
+  }
+}
+// pair q's cell of a colour
+__device__ __forceinline__ TailCell tail_cell(const Dims& n, const TailPairs& tp, int q, int colour) {
+  const int o = (tp.j[q] + tp.k[q] + colour) & 1;
+  TailCell x;
+  x.ok = q < tp.np && tp.i[q] + o < n.nx;
+  const int oc = tp.i[q] + o < n.nx ? o : 0, i = tp.i[q] + oc;
+  x.top = tp.du[q] == 0;
+  x.c = tp.c[q] + oc;
+  x.fx = tp.fx[q] + oc;
+  x.fy = tp.fy[q] + oc;
+  x.w = x.c - (i > 0 ? 1 : 0);
+  x.e = x.c + (i < n.nx - 1 ? 1 : 0);
+  x.s = x.c + tp.ds[q];
+  x.n = x.c + tp.dn[q];
+  x.d = x.c + tp.dd[q];
+  x.u = x.c + tp.du[q];
+  return x;
+}
+
+// a level's arrays in LDS
+template <typename T>
+struct TailArrays {
+  const T *bx, *by, *bz, *id, *b;
+  T* e;
+};
+// what a cell's update reads: six faces, six neighbours, its own b and 1/D
+template <typename T>
+struct TailLoads {
+  T f[6], v[6], b, id;
+  __device__ __forceinline__ TailLoads(const TailArrays<T>& A, const TailCell& x, int nx, int sxy) {
+    f[0] = A.bx[x.fx];
+    f[1] = A.bx[x.fx + 1];
+    f[2] = A.by[x.fy];
+    f[3] = A.by[x.fy + nx];
+    f[4] = A.bz[x.c];
+    f[5] = A.bz[x.c + sxy];
+    v[0] = A.e[x.w];
+    v[1] = A.e[x.e];
+    v[2] = A.e[x.s];
+    v[3] = A.e[x.n];
+    v[4] = A.e[x.d];
+    v[5] = A.e[x.u];
+    b = A.b[x.c];
+    id = A.id[x.c];
+  }
+};
+
+// one colour pass.  Every load of the thread's cells is issued before the
+// arithmetic starts (the scheduling barrier keeps the compiler from
+// interleaving them with the sums, which would wait on each pair in turn).
+template <typename T>
+__device__ __forceinline__ void tail_pass(const Dims& n, const TailPairs& tp, const TailArrays<T>& A, T h2, int colour,
+                                          bool from_zero) {
+  const int sxy = n.nx * n.ny;
+  const TailCell x0 = tail_cell(n, tp, 0, colour);
+  auto value = [&](const TailCell& x, const TailLoads<T>& l) {
+    T num = h2 * l.b;
+    if (!from_zero) {
 #pragma unroll
-      for (int col = 0; col < 2; ++col) {
-        const int i = 2 * tp.ti[q] + ((j + k + col) & 1);
-        TailCell& x = tp.cell[q][col];
-        x.ok = i < n.nx;
-        x.top = k == n.nz - 1;
-        x.c = i + n.nx * j + sxy * k;
-        x.fx = i + (n.nx + 1) * (j + n.ny * k);
-        x.fy = i + n.nx * (j + (n.ny + 1) * k);
-        x.w = i > 0 ? x.c - 1 : x.c;
-        x.e = i < n.nx - 1 ? x.c + 1 : x.c;
-        x.s = j > 0 ? x.c - n.nx : x.c;
-        x.n = j < n.ny - 1 ? x.c + n.nx : x.c;
-        x.d = k > 0 ? x.c - sxy : x.c;
-        x.u = x.top ? x.c : x.c + sxy;
+      for (int q = 0; q < 5; ++q) num += l.f[q] * l.v[q];   // west, east, south, north, down, up
+      const T with_up = num + l.f[5] * l.v[5];
+      num = x.top ? num : with_up;
+    }
+    return num * l.id;
+  };
+  if (tp.np == 2) {
+    const TailCell x1 = tail_cell(n, tp, 1, colour);
+    const TailLoads<T> l0(A, x0, n.nx, sxy), l1(A, x1, n.nx, sxy);
+    __builtin_amdgcn_sched_barrier(0);
+    const T v0 = value(x0, l0), v1 = value(x1, l1);
+    if (x0.ok) A.e[x0.c] = v0;
+    if (x1.ok) A.e[x1.c] = v1;
+  } else if (x0.ok) {
+    const TailLoads<T> l0(A, x0, n.nx, sxy);
+    __builtin_amdgcn_sched_barrier(0);
+    A.e[x0.c] = value(x0, l0);
+  }
+  __syncthreads();
+}
+
+// A coarsest level of one or two cells in a row: the same sweeps, with the
+// same arithmetic, done by one thread in registers.  Cell 0 is red, cell 1
+// black; the face between them is bx[1]; there is no other neighbour.
+template <typename T>
+__device__ __forceinline__ void tail_coarsest_row(const TailArrays<T>& A, bool two, T h2, int S, int tid) {
+  if (tid == 0) {
+    const T r0 = h2 * A.b[0], i0 = A.id[0];
+    const T r1 = two ? h2 * A.b[1] : (T)0, i1 = two ? A.id[1] : (T)0, w = two ? A.bx[1] : (T)0;
+    T e0 = 0, e1 = 0;
+#pragma unroll 1
+    for (int s = 0; s < 2 * S; ++s) {   // forward: red, black; backward: black, red
+      if (s < S) {
+        T num = r0;
+        if (s > 0) num += w * e1;
+        e0 = num * i0;
+      }
+      T num = r1;
+      num += w * e0;
+      e1 = num * i1;
+      if (s >= S) {
+        T n0 = r0;
+        n0 += w * e1;
+        e0 = n0 * i0;
+      }
+    }
+    A.e[0] = e0;
+    if (two) A.e[1] = e1;
+  }
+  __syncthreads();
+}
+
+// The cycle from the last level of D down, e = M b.  A level of up to 128 pairs
+// keeps a wavefront or two busy, and its passes (40 of them on the coarsest
+// level) are a chain of LDS round trips, 0.3 us each; the cycle is a
+// linear map, so its matrix, formed once per solve, gives the same values in one
+// product: 256 x 1 x 64's levels of 64, 16 and 4 cells took 20 of the tail's
+// 40 us.  R: the level's cells, rounded up; thread (g, i) sums columns g, g + G,
+// .. of row i (32 loads in flight at a time), then the G sums are added in order.
+// Past 256 cells the matrix outgrows what one compute unit loads in the time
+// of the passes (512 cells: 2 MB at 64 B per clock, 14 us).
+template <typename T, int R>
+__device__ __forceinline__ void matrix_product(const TailDesc<T>& D, T* sm, int tid, int N) {
+  constexpr int G = kTailThreads / R, K = R / G, U = K < 32 ? K : 32;
+  const int l = D.nl - 1, i = tid % R, g = tid / R;
+  const T* b = sm + D.ob[l];
+  T* mv = sm + D.omv;
+  T m[U];
+  double s = 0;
+#pragma unroll 1
+  for (int c0 = g; c0 < N; c0 += G * U) {
+#pragma unroll
+    for (int q = 0; q < U; ++q) m[q] = D.M[min(c0 + G * q, N - 1) * N + min(i, N - 1)];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const double v = (double)m[q] * (double)b[min(c0 + G * q, N - 1)];
+      s += c0 + G * q < N ? v : 0.0;
+    }
+  }
+  mv[tid] = (T)s;
+  __syncthreads();
+  if (tid < N) {
+    double t = 0;
+#pragma unroll 4
+    for (int q = 0; q < G; ++q) t += (double)mv[tid + q * R];
+    sm[D.oe[l] + tid] = (T)t;
+  }
+  __syncthreads();
+}
+template <typename T>
+__device__ __forceinline__ void tail_matrix_product(const TailDesc<T>& D, T* sm, int tid) {
+  const Dims n = D.n[D.nl - 1];
+  const int N = n.nx * n.ny * n.nz;
+  if (N > 128)
+    matrix_product<T, 256>(D, sm, tid, N);
+  else if (N > 64)
+    matrix_product<T, 128>(D, sm, tid, N);
+  else if (N > 32)
+    matrix_product<T, 64>(D, sm, tid, N);
+  else
+    matrix_product<T, 32>(D, sm, tid, N);
+}
+
+// The tail's first level, and a coarsest level that is no matrix: its face
+// coefficients, 1/D and right-hand side live in registers, NP pairs per thread
+// (pair tid + q kTailThreads), and only its correction is in LDS, by colour and
+// pair index (reg_planes), so that a wavefront's reads are consecutive and a
+// neighbour is a fixed distance away.  Same passes, in the same order, as the
+// separate launches.  A pass is six LDS reads per cell, a dozen FP64 operations
+// and a barrier: 0.46 us for 25 x 9 x 13 cells against a launch of 3.4
+// (200 x 72 x 104, whose coarsest level that is: 40 passes, 1.42 times the
+// step's speed); with the coefficients in LDS, 14 reads per cell, 18 x 8 x 9's
+// 40 passes (72 x 32 x 36) made the step 5 to 10% slower.
+template <typename T>
+struct RegView {
+  Dims n, nc;      // the level and the next one
+  int fy, fz;      // coarsening factors (fx is 2)
+  T h2;
+  const T *bx, *by, *bz, *id, *b;
+  T *planes, *rs;  // LDS: the correction (reg_planes entries), the residual scratch in natural order
+};
+template <typename T, int NP>
+struct RegLevel {
+  RegView<T> V;
+  T* e;      // the red plane; the black one is P + sz further
+  int tid, hx, sz, P;
+  int cp[NP], co[NP];   // per pair: natural index of the first column, and the coarse cell above
+  // per pair: the face between its cells, each colour's five other faces (x
+  // outer, south, north, down, up), 1/D and b
+  T fm[NP], f[NP][2][5], id[NP][2], b[NP][2];
+  unsigned ok, odd, top;   // per (pair, colour): exists; odd column; per pair: top row
+
+  __device__ __forceinline__ int pair(int q) const {   // (the last pairs of the last thread groups repeat one)
+    return q < NP - 1 ? tid + q * kTailThreads : min(tid + q * kTailThreads, P - 1);
+  }
+  // every load from a clamped index, so that all are in flight together; what
+  // lies outside the level is then dropped
+  __device__ __forceinline__ RegLevel(const RegView<T>& V_, int t) : V(V_), tid(t) { load(); }
+  __device__ __forceinline__ void load() {
+    const Dims& g = V.n;
+    const int sxy = g.nx * g.ny;
+    hx = (g.nx + 1) >> 1;
+    sz = hx * g.ny;
+    P = sz * g.nz;
+    e = V.planes + sz;
+    ok = odd = top = 0;
+    const float ihx = 1.0f / (float)hx, iny = 1.0f / (float)g.ny;
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int p = pair(q);
+      const int r = tail_div(p, ihx), ti = p - r * hx, k = tail_div(r, iny), j = r - k * g.ny;
+      cp[q] = 2 * ti + g.nx * r;
+      co[q] = ti + V.nc.nx * ((j >> (V.fy - 1)) + V.nc.ny * (k >> (V.fz - 1)));
+      if (k == g.nz - 1) top |= 1u << q;
+      const int row = (g.nx + 1) * (j + g.ny * k);
+      fm[q] = V.bx[row + 2 * ti + 1];   // (past an odd row's end: the wall face, zero)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int o = (j + k + c) & 1, i = min(2 * ti + o, g.nx - 1);
+        if (tid + q * kTailThreads < P && 2 * ti + o < g.nx) ok |= 1u << (2 * q + c);
+        if (o) odd |= 1u << (2 * q + c);
+        const int fy = i + g.nx * (j + (g.ny + 1) * k), cc = i + g.nx * j + sxy * k;
+        f[q][c][0] = V.bx[row + (o ? i + 1 : i)];
+        f[q][c][1] = V.by[fy];
+        f[q][c][2] = V.by[fy + g.nx];
+        f[q][c][3] = V.bz[cc];
+        f[q][c][4] = V.bz[cc + sxy];
+        id[q][c] = V.id[cc];
+        b[q][c] = V.b[cc];
       }
     }
   }
-}
+  __device__ __forceinline__ void zero() {
+    for (int q = tid; q < 2 * P + 3 * sz; q += kTailThreads) e[q - sz] = (T)0;
+    __syncthreads();
+  }
+  template <int C>
+  __device__ __forceinline__ T* plane() const { return C ? e + P + sz : e; }
+  // the other colour's values around a pair's cell of colour C: in the pair,
+  // beyond it along x, south, north, down, up (the entries above the top row
+  // stay zero)
+  template <int C>
+  __device__ __forceinline__ void around(int q, T (&v)[6]) const {
+    const T* o = plane<1 - C>() + pair(q);
+    v[0] = o[0];
+    v[1] = o[odd >> (2 * q + C) & 1u ? 1 : -1];
+    v[2] = o[-hx];
+    v[3] = o[hx];
+    v[4] = o[-sz];
+    v[5] = o[sz];
+  }
 
-// ordering point between two phases: a workgroup barrier, or (WAVE) a
-// wavefront-level fence for phases run by wavefront 0 alone
-template <bool WAVE>
-__device__ __forceinline__ void tail_sync() {
-  if constexpr (WAVE) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  } else {
+  template <int C>
+  __device__ __forceinline__ void pass(bool from_zero) {
+    T v[NP][6];
+    if (!from_zero) {
+#pragma unroll
+      for (int q = 0; q < NP; ++q) around<C>(q, v[q]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      T num = V.h2 * b[q][C];
+      if (!from_zero) {
+        num += fm[q] * v[q][0];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) num += f[q][C][i] * v[q][i + 1];
+        const T with_up = num + f[q][C][4] * v[q][5];
+        num = top >> q & 1u ? num : with_up;
+      }
+      if (ok >> (2 * q + C) & 1u) plane<C>()[pair(q)] = num * id[q][C];
+    }
+    __syncthreads();
+  }
+
+  template <int C>
+  __device__ __forceinline__ void residual(T ih2) {
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      T v[6];
+      around<C>(q, v);
+      const T xc = plane<C>()[pair(q)];
+      T acc = fm[q] * (xc - v[0]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc += f[q][C][i] * (xc - v[i + 1]);
+      acc += top >> q & 1u ? (T)2 * f[q][C][4] * xc : f[q][C][4] * (xc - v[5]);
+      if (ok >> (2 * q + C) & 1u) V.rs[2 * pair(q) + (odd >> (2 * q + C) & 1u)] = b[q][C] - ih2 * acc;
+    }
+  }
+
+  // the red, black, .. passes of a visit: down from zero (up 0), up (1), or the
+  // coarsest level's sweeps forward then backward
+  __device__ __forceinline__ void smooth(int passes, bool up, bool bottom) {
+#pragma unroll 1
+    for (int s = 0; s < passes; ++s) {
+      const bool zero = !up && s == 0;
+      if ((s + (up || (bottom && 2 * s >= passes))) & 1)
+        pass<1>(zero);
+      else
+        pass<0>(zero);
+    }
+  }
+  // the residual and its restriction
+  __device__ __forceinline__ void restrict_to(T* bc) {
+    const T ih2 = (T)1 / V.h2;
+    residual<0>(ih2);
+    residual<1>(ih2);
+    __syncthreads();
+    // each coarse cell's mean of its children (a level that is restricted has
+    // an even nx, so entry 2 p + odd of the scratch is the cell's natural
+    // index)
+    const Dims &g = V.n, nc = V.nc;
+    const int sy = V.fy - 1, sk = V.fz - 1, sxy = g.nx * g.ny;
+    const T inv = (T)1 / (T)(2 << (sy + sk));
+    const float inx = 1.0f / (float)nc.nx, iny = 1.0f / (float)nc.ny;
+#pragma unroll 1
+    for (int c = tid; c < nc.nx * nc.ny * nc.nz; c += kTailThreads) {
+      const int r = tail_div(c, inx), K = tail_div(r, iny), f0 = 2 * (c - r * nc.nx) + g.nx * ((r - K * nc.ny) << sy) + (sxy << sk) * K;
+      T sum = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int dj = q & 1, dk = q >> 1;
+        if (dj <= sy && dk <= sk) {
+          sum += V.rs[f0 + g.nx * dj + sxy * dk];
+          sum += V.rs[f0 + g.nx * dj + sxy * dk + 1];
+        }
+      }
+      bc[c] = sum * inv;
+    }
+    __syncthreads();
+  }
+  __device__ __forceinline__ void prolong(const T* ec) {
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int p = pair(q);
+      const T add = ec[co[q]];
+      if (ok >> (2 * q) & 1u) plane<0>()[p] += add;
+      if (ok >> (2 * q) & 2u) plane<1>()[p] += add;
+    }
+    __syncthreads();
+  }
+
+  __device__ __forceinline__ void store(T* ge) const {
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int p = pair(q);
+      if (ok >> (2 * q) & 1u) ge[cp[q] + (odd >> (2 * q) & 1u)] = plane<0>()[p];
+      if (ok >> (2 * q) & 2u) ge[cp[q] + (odd >> (2 * q + 1) & 1u)] = plane<1>()[p];
+    }
+  }
+};
+
+// The V-cycle over the levels in LDS by nthr threads: the visits go down the
+// levels and up again
+template <typename T, bool REG>
+__device__ __forceinline__ void tail_levels(const TailDesc<T>& D, T* sm, int tid, int nthr) {
+  const int nl = D.nl;
+#pragma unroll 1
+  for (int it = 0; it < 2 * nl - 1; ++it) {
+    const bool up = it >= nl;
+    const int l = up ? 2 * nl - 2 - it : it;
+    const bool bottom = l == nl - 1;
+    if (bottom && D.M) {
+      tail_matrix_product<T>(D, sm, tid);
+      continue;
+    }
+    const Dims n = D.n[l];
+    const int sxy = n.nx * n.ny;
+    const T h2 = D.h2[l];
+    const TailArrays<T> A{sm + D.obx[l], sm + D.oby[l], sm + D.obz[l], sm + D.oid[l], sm + D.ob[l], sm + D.oe[l]};
+    if constexpr (REG) {
+      if (bottom) {
+        RegLevel<T, 1> t({n, n, 1, 1, h2, A.bx, A.by, A.bz, A.id, A.b, sm + D.oeb, nullptr}, tid);
+        t.zero();
+        t.smooth(4 * D.coarse_sweeps, false, true);
+        t.store(A.e);
+        __syncthreads();
+        continue;
+      }
+    }
+    if (bottom && n.nx <= 2 && n.ny == 1 && n.nz == 1) {
+      tail_coarsest_row<T>(A, n.nx == 2, h2, D.coarse_sweeps, tid);
+      continue;
+    }
+    TailPairs tp;
+    tail_decode(n, tid, nthr, tp);
+    const Dims nc = bottom ? n : D.n[l + 1];
+    const int sy = D.f[l][1] - 1, sz = D.f[l][2] - 1;   // the halved directions' shifts
+    if (up) {
+      // prolongation: both cells of a pair share one coarse cell (fx = 2)
+      const T* ec = sm + D.oe[l + 1];
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        if (q < tp.np) {
+          const T add = ec[(tp.i[q] >> 1) + nc.nx * ((tp.j[q] >> sy) + nc.ny * (tp.k[q] >> sz))];
+          A.e[tp.c[q]] += add;
+          if (tp.i[q] + 1 < n.nx) A.e[tp.c[q] + 1] += add;
+        }
+      __syncthreads();
+    }
+    // red, black, .. down from zero; black, red, .. up; on the coarsest level
+    // the sweeps forward, then backward
+    const int passes = bottom ? 4 * D.coarse_sweeps : 2 * (up ? D.nu_post : D.nu_pre);
+#pragma unroll 1
+    for (int s = 0; s < passes; ++s)
+      tail_pass<T>(n, tp, A, h2, (s + (up || (bottom && 2 * s >= passes))) & 1, !up && s == 0);
+    if (up || bottom) continue;
+    // every fine cell's residual b - A e, each thread for both cells of its
+    // pairs (a wall term is an exact zero) ...
+    T* rs = sm + D.ors;
+    const T ih2 = (T)1 / h2;
+#pragma unroll 1
+    for (int col = 0; col < 2; ++col)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const TailCell x = tail_cell(n, tp, q, col);
+        if (!x.ok) continue;
+        const TailLoads<T> a(A, x, n.nx, sxy);
+        const T xc = A.e[x.c];
+        __builtin_amdgcn_sched_barrier(0);
+        T acc = 0;
+#pragma unroll
+        for (int d = 0; d < 5; ++d) acc += a.f[d] * (xc - a.v[d]);
+        acc += x.top ? (T)2 * a.f[5] * xc : a.f[5] * (xc - a.v[5]);
+        rs[x.c] = a.b - ih2 * acc;
+      }
+    __syncthreads();
+    // ... then each coarse cell's mean of its children, summed in the order
+    // (dk, dj, di) (a level that is restricted has an even nx: fx = 2; fy, fz
+    // are 1 along a dimension of one cell, else 2)
+    T* bc = sm + D.ob[l + 1];
+    const T inv = (T)1 / (T)(2 << (sy + sz));
+    const float inx = 1.0f / (float)nc.nx, iny = 1.0f / (float)nc.ny;
+#pragma unroll 1
+    for (int c = tid; c < nc.nx * nc.ny * nc.nz; c += nthr) {
+      const int r = tail_div(c, inx), K = tail_div(r, iny), f = 2 * (c - r * nc.nx) + n.nx * ((r - K * nc.ny) << sy) + (sxy << sz) * K;
+      T sum = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int dj = q & 1, dk = q >> 1;
+        if (dj <= sy && dk <= sz) {
+          sum += rs[f + n.nx * dj + sxy * dk];
+          sum += rs[f + n.nx * dj + sxy * dk + 1];
+        }
+      }
+      bc[c] = sum * inv;
+    }
     __syncthreads();
   }
 }
 
-template <typename T, bool WAVE, int COLOUR>
-__device__ __forceinline__ void tail_pass(const Dims& n, const TailPairs& tp, T h2, const T* bx, const T* by,
-                                          const T* bz, const T* invd, const T* b, T* e, bool from_zero) {
-  const int sxy = n.nx * n.ny;
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {   // compile-time indices: the cells stay in registers
-    if (q >= tp.np) break;
-    const TailCell& x = tp.cell[q][COLOUR];
-    if (x.ok) {
-      const T id = invd[x.c], bc = b[x.c];
-      if (from_zero) {
-        e[x.c] = (h2 * bc) * id;
-      } else {
-        // every load is issued before the arithmetic starts (the scheduling
-        // barrier keeps the compiler from interleaving them with the sums,
-        // which would wait on each pair in turn); the up term is formed and
-        // then selected, so that its loads do not sit behind a branch
-        const T cw = bx[x.fx], ce = bx[x.fx + 1], cs = by[x.fy], cn = by[x.fy + n.nx];
-        const T cd = bz[x.c], cu = bz[x.c + sxy];
-        const T ew = e[x.w], ee = e[x.e], es = e[x.s], en = e[x.n], ed = e[x.d], eu = e[x.u];
-        __builtin_amdgcn_sched_barrier(0);
-        T num = h2 * bc;
-        num += cw * ew;   // west, east, south, north, down, up
-        num += ce * ee;
-        num += cs * es;
-        num += cn * en;
-        num += cd * ed;
-        const T with_up = num + cu * eu;
-        num = x.top ? num : with_up;
-        e[x.c] = num * id;
-      }
-    }
-  }
-  tail_sync<WAVE>();
+// Column blockIdx.x of that matrix: the cycle over D's levels, one wavefront,
+// from a unit right-hand side.  Also an FP32 cycle's is computed in FP64 from
+// its FP32 coefficients, and its products are summed in FP64: the result is
+// then nearer the exact cycle than the FP32 passes' own.
+template <typename T>
+__global__ void __launch_bounds__(64) k_tail_matrix(TailDesc<double> D, const T* __restrict__ pack, T* __restrict__ M) {
+  extern __shared__ double tail_smem[];
+  double* sm = tail_smem;
+  const int tid = threadIdx.x, N = D.n[0].nx * D.n[0].ny * D.n[0].nz;
+  for (int q = tid; q < D.npack; q += 64) sm[q] = (double)pack[q];
+  for (int q = D.npack + tid; q < D.omv; q += 64) sm[q] = 0.0;
+  __syncthreads();
+  if (tid == 0) sm[D.ob[0] + blockIdx.x] = 1.0;
+  __syncthreads();
+  tail_levels<double, false>(D, sm, tid, 64);
+  for (int q = tid; q < N; q += 64) M[(size_t)blockIdx.x * N + q] = (T)sm[D.oe[0] + q];
 }
 
-// One level's share of the tail, run either by the whole workgroup or (WAVE)
-// by wavefront 0 alone.
-template <typename T, bool WAVE>
-struct TailLevel {
-  const TailDesc<T>& D;
-  T* sm;
-  int tid, nthr;
-
-  template <int C0>
-  __device__ void smooth_from(int l, const TailPairs& tp, int pairs, bool from_zero) const {
-    const Dims n = D.n[l];
-    const T *bx = sm + D.obx[l], *by = sm + D.oby[l], *bz = sm + D.obz[l], *b = sm + D.ob[l];
-    const T* invd = sm + D.oid[l];
-    T* e = sm + D.oe[l];
-    const T h2 = D.h2[l];
-    for (int s = 0; s < pairs; ++s) {
-      tail_pass<T, WAVE, C0>(n, tp, h2, bx, by, bz, invd, b, e, from_zero && s == 0);
-      tail_pass<T, WAVE, 1 - C0>(n, tp, h2, bx, by, bz, invd, b, e, false);
-    }
-  }
-
-  // `pairs` (red, black) or (black, red) sweeps
-  __device__ void smooth(int l, const TailPairs& tp, int first_colour, int pairs, bool from_zero) const {
-    if (first_colour == 0)
-      smooth_from<0>(l, tp, pairs, from_zero);
-    else
-      smooth_from<1>(l, tp, pairs, from_zero);
-  }
-
-  __device__ void zero(int l) const {
-    const int N = D.n[l].nx * D.n[l].ny * D.n[l].nz;
-    T* e = sm + D.oe[l];
-    for (int c = tid; c < N; c += nthr) e[c] = (T)0;
-    tail_sync<WAVE>();
-  }
-
-  // pre-smoothing, then the restricted residual into the next level's b
-  __device__ void down(int l) const {
-    TailPairs tp;
-    tail_decode(D.n[l], tid, nthr, tp);
-    if (D.nu_pre > 0) {
-      // the red pass from zero writes the red cells without reading e; the
-      // black pass after it reads them (and its own zeroed entries at walls)
-      smooth(l, tp, 0, D.nu_pre, true);
-    } else {
-      zero(l);
-    }
-    const Dims nf = D.n[l], nc = D.n[l + 1];
-    const int fx = D.f[l][0], fy = D.f[l][1], fz = D.f[l][2];
-    const T *bx = sm + D.obx[l], *by = sm + D.oby[l], *bz = sm + D.obz[l], *b = sm + D.ob[l];
-    const T* e = sm + D.oe[l];
-    T* bc = sm + D.ob[l + 1];
-    T* rs = sm + D.ors;   // scratch: the fine residual
-    const T ih2 = (T)1 / D.h2[l];
-    const T inv = (T)1 / (T)(fx * fy * fz);
-    const int sxy = nf.nx * nf.ny;
-    // every fine cell's residual b - A e, each thread for both cells of its
-    // pairs (a wall term is an exact zero) ...
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      if (q >= tp.np) break;
-      // both cells' loads first (a cell past the row's end reads the
-      // pair's other cell, and is not stored), then their sums
-      T v[2][14];
-#pragma unroll
-      for (int col = 0; col < 2; ++col) {
-        const TailCell& x = tp.cell[q][col];
-        const int c = x.ok ? x.c : tp.cell[q][1 - col].c;
-        const int w = x.ok ? x.w : c, ea = x.ok ? x.e : c, so = x.ok ? x.s : c, no = x.ok ? x.n : c;
-        const int d = x.ok ? x.d : c, u = x.ok ? x.u : c;
-        const int ix = x.ok ? x.fx : tp.cell[q][1 - col].fx, iy = x.ok ? x.fy : tp.cell[q][1 - col].fy;
-        v[col][0] = e[c];
-        v[col][1] = bx[ix];
-        v[col][2] = bx[ix + 1];
-        v[col][3] = by[iy];
-        v[col][4] = by[iy + nf.nx];
-        v[col][5] = bz[c];
-        v[col][6] = bz[c + sxy];
-        v[col][7] = e[w];
-        v[col][8] = e[ea];
-        v[col][9] = e[so];
-        v[col][10] = e[no];
-        v[col][11] = e[d];
-        v[col][12] = e[u];
-        v[col][13] = b[c];
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int col = 0; col < 2; ++col) {
-        const TailCell& x = tp.cell[q][col];
-        const T* a = v[col];
-        const T xc = a[0];
-        T acc = 0;
-        acc += a[1] * (xc - a[7]);    // west, east, south, north, down, up
-        acc += a[2] * (xc - a[8]);
-        acc += a[3] * (xc - a[9]);
-        acc += a[4] * (xc - a[10]);
-        acc += a[5] * (xc - a[11]);
-        acc += x.top ? (T)2 * a[6] * xc : a[6] * (xc - a[12]);
-        if (x.ok) rs[x.c] = a[13] - ih2 * acc;
-      }
-    }
-    tail_sync<WAVE>();
-    // ... then each coarse cell's mean of its children, summed in the order
-    // (dk, dj, di) by the thread whose pair is the cell's (dj, dk) = (0, 0)
-    // corner: a level that is restricted has an even nx, so a pair (ti, j, k)
-    // is exactly the two x-children of coarse column ti (fx = 2; fy, fz are
-    // 1 along a dimension of one cell, else 2)
-    const int sy = fy - 1, sz = fz - 1;
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      if (q >= tp.np) break;
-      const int ti = tp.ti[q], j = tp.j[q], k = tp.k[q];
-      if ((j & sy) == 0 && (k & sz) == 0) {
-        T sum = 0;
-        for (int dk = 0; dk < fz; ++dk)
-          for (int dj = 0; dj < fy; ++dj) {
-            const int f = 2 * ti + nf.nx * (j + dj) + sxy * (k + dk);
-            sum += rs[f];
-            sum += rs[f + 1];
-          }
-        bc[ti + nc.nx * ((j >> sy) + nc.ny * (k >> sz))] = sum * inv;
-      }
-    }
-    tail_sync<WAVE>();
-  }
-
-  // coarsest level: sweeps forward (red, black) then backward (black, red) from zero
-  __device__ void coarsest(int l) const {
-    const Dims n = D.n[l];
-    if (n.nx <= 2 && n.ny == 1 && n.nz == 1) {
-      coarsest_row(l);
-      return;
-    }
-    if (D.coarse_sweeps > 0) {
-      TailPairs tp;
-      tail_decode(D.n[l], tid, nthr, tp);
-      smooth(l, tp, 0, D.coarse_sweeps, true);
-      smooth(l, tp, 1, D.coarse_sweeps, false);
-    } else {
-      zero(l);
-    }
-  }
-
-  // A coarsest level of one or two cells in a row: the same sweeps, with the
-  // same arithmetic, done by one thread in registers.  Cell 0 is red, cell 1
-  // black; the face between them is bx[1]; there is no other neighbour.
-  __device__ void coarsest_row(int l) const {
-    if (tid == 0) {
-      const bool two = D.n[l].nx == 2;
-      const T h2 = D.h2[l];
-      const T *b = sm + D.ob[l], *invd = sm + D.oid[l], *bx = sm + D.obx[l];
-      T* e = sm + D.oe[l];
-      const T r0 = h2 * b[0], i0 = invd[0];
-      const T r1 = two ? h2 * b[1] : (T)0, i1 = two ? invd[1] : (T)0, w = two ? bx[1] : (T)0;
-      T e0 = 0, e1 = 0;
-      const int S = D.coarse_sweeps;
-      for (int s = 0; s < S; ++s) {   // forward: red (from zero first), black
-        T num = r0;
-        if (two && s > 0) num += w * e1;
-        e0 = num * i0;
-        num = r1;
-        num += w * e0;
-        e1 = num * i1;
-      }
-      for (int s = 0; s < S; ++s) {   // backward: black, red
-        T num = r1;
-        num += w * e0;
-        e1 = num * i1;
-        num = r0;
-        if (two) num += w * e1;
-        e0 = num * i0;
-      }
-      e[0] = e0;
-      if (two) e[1] = e1;
-    }
-    tail_sync<WAVE>();
-  }
-
-  // prolongation of the next level's correction (both cells of a pair share
-  // one coarse cell: fx = 2), then post-smoothing
-  __device__ void up(int l) const {
-    const Dims nf = D.n[l], nc = D.n[l + 1];
-    const int sy = D.f[l][1] - 1, sz = D.f[l][2] - 1;
-    T* e = sm + D.oe[l];
-    const T* ec = sm + D.oe[l + 1];
-    TailPairs tp;
-    tail_decode(nf, tid, nthr, tp);
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      if (q >= tp.np) break;
-      const int ti = tp.ti[q], j = tp.j[q], k = tp.k[q];
-      const T add = ec[ti + nc.nx * ((j >> sy) + nc.ny * (k >> sz))];
-      const int c = 2 * ti + nf.nx * (j + nf.ny * k);
-      e[c] += add;
-      if (2 * ti + 1 < nf.nx) e[c + 1] += add;
-    }
-    tail_sync<WAVE>();
-    smooth(l, tp, 1, D.nu_post, false);
-  }
-};
-
-template <typename T>
+// The tail whose first level is held in registers, NP pairs per thread
+template <typename T, int NP>
 __global__ void __launch_bounds__(kTailThreads) k_vcycle_tail(TailDesc<T> D) {
   extern __shared__ double tail_smem[];
   T* sm = reinterpret_cast<T*>(tail_smem);
   const int nl = D.nl;
   const int tid = threadIdx.x;
-  // stage the pack (every coefficient array and 1/D) and the first
-  // right-hand side: one flat loop, sixteen independent loads in flight per
-  // thread
-  {
-    // each load from one address chosen by a select (past the end: the last
-    // entry of b0, not stored), so no load waits behind a branch
-    const int np = D.npack, n0 = D.n[0].nx * D.n[0].ny * D.n[0].nz, total = np + n0;
-    for (int base = tid; base < total; base += 16 * kTailThreads) {
-      T v[16];
+  RegLevel<T, NP> t({D.nt, D.n[0], D.ft[1], D.ft[2], D.h2t, D.tbx, D.tby, D.tbz, D.tid, D.b0, sm + D.oet, sm + D.ors}, tid);
+  // stage the pack (every coefficient array and 1/D of the levels below) while
+  // those loads are in flight: one flat loop, sixteen independent loads per
+  // thread at a time
+#pragma unroll 1
+  for (int base = tid; base < D.npack; base += 16 * kTailThreads) {
+    T v[16];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int q = base + u * kTailThreads;
-        const T* src = q < np ? D.pack + q : D.b0 + min(max(q - np, 0), n0 - 1);
-        v[u] = *src;
-      }
+    for (int u = 0; u < 16; ++u) v[u] = D.pack[min(base + u * kTailThreads, D.npack - 1)];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int q = base + u * kTailThreads;
-        if (q < total) sm[q < np ? q : D.ob[0] + (q - np)] = v[u];
-      }
-    }
-    // every level's correction starts at zero: the passes read a cell's own
-    // entry through a wall before it is first written
-    for (int l = 0; l < nl; ++l) {
-      const int N = D.n[l].nx * D.n[l].ny * D.n[l].nz;
-      for (int c = tid; c < N; c += kTailThreads) sm[D.oe[l] + c] = (T)0;
-    }
+    for (int u = 0; u < 16; ++u)
+      if (base + u * kTailThreads < D.npack) sm[base + u * kTailThreads] = v[u];
   }
+  // every level's correction starts at zero: the passes read a cell's own
+  // entry through a wall before it is first written
+#pragma unroll 1
+  for (int l = 0; l < nl; ++l) {
+    const int N = D.n[l].nx * D.n[l].ny * D.n[l].nz;
+#pragma unroll 1
+    for (int c = tid; c < N; c += kTailThreads) sm[D.oe[l] + c] = (T)0;
+  }
+  t.zero();
+#pragma unroll 1
+  for (bool up = false;; up = true) {
+    t.smooth(nl == 0 ? 4 * D.coarse_sweeps : 2 * (up ? D.nu_post : D.nu_pre), up, nl == 0);
+    if (nl == 0 || up) break;
+    t.restrict_to(sm + D.ob[0]);
+    tail_levels<T, true>(D, sm, tid, kTailThreads);
+    if constexpr (NP * sizeof(T) >= 24) {
+      // read again rather than kept: the levels between want the registers
+      // (also the ones its indices would take: hiding that the thread's number
+      // is the same keeps them from being formed once)
+      asm volatile("" : "+v"(t.tid));
+      t.load();
+    }
+    t.prolong(sm + D.oe[0]);
+  }
+  t.store(D.ge);
+}
+
+// The tail whose first level's cycle is a matrix
+template <typename T>
+__global__ void __launch_bounds__(kTailThreads) k_vcycle_matrix(TailDesc<T> D) {
+  extern __shared__ double tail_smem[];
+  T* sm = reinterpret_cast<T*>(tail_smem);
+  const int tid = threadIdx.x, N = D.n[0].nx * D.n[0].ny * D.n[0].nz;
+  if (tid < N) sm[D.ob[0] + tid] = D.b0[tid];
   __syncthreads();
-  // first level (ls) from which every level fits one wavefront
-  int ls = nl;
-  while (ls > 0 && ((D.n[ls - 1].nx + 1) / 2) * D.n[ls - 1].ny * D.n[ls - 1].nz <= 64) --ls;
-  const TailLevel<T, false> big{D, sm, tid, kTailThreads};
-  for (int l = 0; l < ls && l < nl - 1; ++l) big.down(l);
-  if (ls >= nl) big.coarsest(nl - 1);
-  if (ls < nl) {
-    if (tid < 64) {
-      const TailLevel<T, true> small{D, sm, tid, 64};
-      for (int l = ls; l < nl - 1; ++l) small.down(l);
-      small.coarsest(nl - 1);
-      for (int l = nl - 2; l >= ls; --l) small.up(l);
-    }
-    __syncthreads();
-  }
-  for (int l = (ls < nl ? ls : nl - 1) - 1; l >= 0; --l) big.up(l);
-  {
-    const int N0 = D.n[0].nx * D.n[0].ny * D.n[0].nz;
-    for (int q = tid; q < N0; q += kTailThreads) D.ge[q] = sm[D.oe[0] + q];
-  }
+  tail_matrix_product<T>(D, sm, tid);
+  if (tid < N) D.ge[tid] = sm[D.oe[0] + tid];
 }
 
 template <typename T>
@@ -2976,13 +3192,44 @@ void launch_coarsen_level(const Level& F, const T* fbx, const T* fby, const T* f
 template <typename T>
 void launch_vcycle_tail(const TailDesc<T>& D, size_t lds_bytes, hipStream_t st) {
   // dynamic LDS above 64 KB needs the kernel's limit raised (once per process)
-  static bool raised = false;
-  if (lds_bytes > 64 * 1024 && !raised) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_vcycle_tail<T>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTailLdsBytes);
-    raised = true;
+  using Kern = void (*)(TailDesc<T>);
+  constexpr int M = tail_top_pairs<T>();
+  static const Kern kerns[] = {k_vcycle_matrix<T>, k_vcycle_tail<T, 1>, k_vcycle_tail<T, 2>, k_vcycle_tail<T, 3>,
+                               k_vcycle_tail<T, 4>, k_vcycle_tail<T, M < 5 ? M : 5>, k_vcycle_tail<T, M < 6 ? M : 6>};
+  static bool raised[7] = {};
+  // pairs per thread of the level in registers
+  const int v = D.top ? ((D.nt.nx + 1) / 2 * D.nt.ny * D.nt.nz + kTailThreads - 1) / kTailThreads : 0;
+  if (lds_bytes > 64 * 1024 && !raised[v]) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kerns[v]), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)kTailLdsBytes);
+    raised[v] = true;
   }
-  hipLaunchKernelGGL(k_vcycle_tail<T>, dim3(1), dim3(kTailThreads), lds_bytes, st, D);
+  hipLaunchKernelGGL(kerns[v], dim3(1), dim3(kTailThreads), lds_bytes, st, D);
+}
+
+template <typename T>
+void launch_tail_matrix(const TailDesc<T>& D, int elems, T* M, hipStream_t st) {
+  TailDesc<double> C{};
+  C.nl = D.nl;
+  C.nu_pre = D.nu_pre;
+  C.nu_post = D.nu_post;
+  C.coarse_sweeps = D.coarse_sweeps;
+  for (int l = 0; l < D.nl; ++l) {
+    C.n[l] = D.n[l];
+    for (int d = 0; d < 3; ++d) C.f[l][d] = D.f[l][d];
+    C.h2[l] = (double)D.h2[l];
+    C.obx[l] = D.obx[l];
+    C.oby[l] = D.oby[l];
+    C.obz[l] = D.obz[l];
+    C.oid[l] = D.oid[l];
+    C.ob[l] = D.ob[l];
+    C.oe[l] = D.oe[l];
+  }
+  C.ors = D.ors;
+  C.npack = D.npack;
+  C.omv = D.omv;
+  const int N = D.n[0].nx * D.n[0].ny * D.n[0].nz;
+  hipLaunchKernelGGL(k_tail_matrix<T>, dim3(N), dim3(64), (size_t)elems * sizeof(double), st, C, D.pack, M);
 }
 
 template <typename T>
@@ -3178,7 +3425,8 @@ void launch_apply_A(const Dims& n, double h, const double* bx, const double* by,
                                         T*, T*, T*, bool, hipStream_t);                               \
   template void launch_fill<T>(T*, size_t, hipStream_t);                                              \
   template void launch_face_tables<T>(const Dims&, const T*, const T*, const T*, T*, T*, T*, hipStream_t); \
-  template void launch_vcycle_tail<T>(const TailDesc<T>&, size_t, hipStream_t);
+  template void launch_vcycle_tail<T>(const TailDesc<T>&, size_t, hipStream_t);                       \
+  template void launch_tail_matrix<T>(const TailDesc<T>&, int, T*, hipStream_t);
 NSK_INST(double)
 NSK_INST(float)
 #undef NSK_INST
