@@ -231,10 +231,13 @@ size_t tail_top_elems(const Level* lev, int L, int l) {
   return tot;
 }
 
+// Whether a visit's smoothing is the 2-D launches' (k_pre2d, k_post2d)
+bool tank2d_smooths(const ns_params& P) { return P.nu_pre == 2 && P.nu_post == 2; }
+
 // First level of the tail (L: none): the finest whose cycle is a matrix, or
 // whose pairs the workgroup holds in registers (*top) with the levels below in
 // LDS.
-int plan_tail(const Level* lev, int L, size_t w, size_t* bytes, bool* top) {
+int plan_tail(const Level* lev, int L, bool tank2d, size_t w, size_t* bytes, bool* top) {
   for (int l = 0; l < L; ++l) {
     const Dims n = lev[l].n;
     const size_t pairs = (size_t)((n.nx + 1) / 2) * n.ny * n.nz;
@@ -245,6 +248,11 @@ int plan_tail(const Level* lev, int L, size_t w, size_t* bytes, bool* top) {
     *top = tail_matrix_level(lev, L, l) != l;
     *bytes = (*top ? tail_top_elems(lev, L, l) : 2 * pad4((size_t)n.nx * n.ny * n.nz) + kTailThreads) * w;
     const size_t per = w == sizeof(double) ? tail_top_pairs<double>() : tail_top_pairs<float>();
+    // A level that k_pre2d and k_post2d take joins the tail at one pair per
+    // thread: 320 x 1 x 64 (its 160 x 32 first coarse level as launches) 1.41
+    // ms against 1.50 with two pairs in the tail, 240 x 1 x 48 1.25 against 1.31;
+    // leaving the next smaller level out too: 1.44 and 1.38
+    if (tank2d && l < L - 1 && tank2d_fits(lev[l]) && pairs > (size_t)kTailThreads) continue;
     if (pairs <= per * kTailThreads && *bytes <= kTailLdsBytes) return l;
   }
   *bytes = 0;
@@ -307,8 +315,8 @@ size_t carve(const ns_params* P, ns_ctx* X, char* base) {
   // kernel stages them with one flat copy.
   size_t lds64 = 0, lds32 = 0;
   bool top64 = false, top32 = false;
-  const int t64 = plan_tail(lev, L, sizeof(double), &lds64, &top64);
-  const int t32 = plan_tail(lev, L, sizeof(float), &lds32, &top32);
+  const int t64 = plan_tail(lev, L, tank2d_smooths(*P), sizeof(double), &lds64, &top64);
+  const int t32 = plan_tail(lev, L, tank2d_smooths(*P), sizeof(float), &lds32, &top32);
   const size_t np64 = tail_pack_elems(lev, L, t64), np32 = tail_pack_elems(lev, L, t32);
   double* pk64 = cv.take<double>(np64);
   float* pk32 = cv.take<float>(np32);
@@ -378,7 +386,8 @@ size_t carve(const ns_params* P, ns_ctx* X, char* base) {
     const size_t cs = 2 * (size_t)((V.n.nx + 1) / 2) * V.n.ny * V.n.nz;
     // a third plane for the black plane's copy that a fused red-black pass
     // reads: on the coarse levels, and on the finest where its fused sweep applies
-    const size_t ces = (l >= 1 || gs_rb_fine_fits(V.n)) ? cs + cs / 2 : cs;
+    // (a 2-D coarse level's second half is its visit's result)
+    const size_t ces = l >= 1 && V.n.ny == 1 ? 2 * cs : (l >= 1 || gs_rb_fine_fits(V.n)) ? cs + cs / 2 : cs;
     V.bf = cv.take<float>(l < t32 ? cs : c);
     V.ef = cv.take<float>(l < t32 ? ces : c);
     V.bfn = V.efn = nullptr;
@@ -629,6 +638,19 @@ struct CgReq {
 // b0d: an FP32 cycle's finest-level right-hand side in FP64 (natural), read
 // by its first kernel in place of b0 (the levels below the finest, the
 // tail, and a cycle without pre-smoothing read b0)
+// Whether level l's visits are the 2-D launches (their vectors are natural)
+template <typename T>
+bool use_2d(const ns_ctx* X, int l) {
+  return l < X->L - 1 && l < tail_start<T>(X) && tank2d_fits(X->lev[l]) && tank2d_smooths(X->P) &&
+         X->timed_kernel != NS_TIME_SMOOTH0;
+}
+// where a coarse level's visit leaves its correction
+template <typename T>
+T* corr(const ns_ctx* X, int l) {
+  const Dims n = X->lev[l].n;
+  return LV<T>::e(X->lev[l]) + (use_2d<T>(X, l) ? (size_t)n.nx * n.nz : 0);
+}
+
 template <typename T>
 void vcycle(ns_ctx* X, int l, const T* b0, T* e0, CgReq* dq = nullptr, const double* b0d = nullptr) {
   const ns_params& P = X->P;
@@ -636,6 +658,35 @@ void vcycle(ns_ctx* X, int l, const T* b0, T* e0, CgReq* dq = nullptr, const dou
   hipStream_t st = X->st;
   if (l == tail_start<T>(X)) {
     launch_tail<T>(X, l, l == 0 ? b0 : LV<T>::b(L), l == 0 ? e0 : LV<T>::e(L), tail_bytes<T>(X));
+    return;
+  }
+  if (use_2d<T>(X, l)) {
+    const Level& C = X->lev[l + 1];
+    const bool csplit = (l + 1) < tail_start<T>(X) && !use_2d<T>(X, l + 1);
+    const T *fx = LV<T>::bx(L), *fz = LV<T>::bz(L), *id = LV<T>::invd(L);
+    // (the visit up may not write what the tiles beside it read: below the
+    // finest level it leaves its result in corr's place)
+    T* w = LV<T>::e(L);
+    if (l > 0) {
+      const T* b = LV<T>::b(L);
+      launch_pre2d<T, T>(L, fx, fz, id, b, w, csplit, LV<T>::b(C), st);
+      vcycle<T>(X, l + 1, nullptr, nullptr);
+      launch_post2d<T, T, T>(L, fx, fz, id, b, w, csplit, corr<T>(X, l + 1), corr<T>(X, l), nullptr, nullptr, st);
+      return;
+    }
+    auto both = [&](auto* b) {
+      using TB = std::remove_cv_t<std::remove_pointer_t<decltype(b)>>;
+      launch_pre2d<T, TB>(L, fx, fz, id, b, w, csplit, LV<T>::b(C), st);
+      vcycle<T>(X, 1, nullptr, nullptr);
+      if (dq && dq->dots)
+        dq->nparts = launch_post2d<T, TB, double>(L, fx, fz, id, b, w, csplit, corr<T>(X, 1), dq->z, dq->r, X->partials, st);
+      else
+        launch_post2d<T, TB, T>(L, fx, fz, id, b, w, csplit, corr<T>(X, 1), e0, nullptr, nullptr, st);
+    };
+    if constexpr (sizeof(T) == 4)
+      both(b0d);   // (a cycle that pre-smooths above the tail reads the FP64 residual)
+    else
+      both(b0);
     return;
   }
   T* b = LV<T>::b(L);   // split
@@ -738,7 +789,7 @@ void vcycle(ns_ctx* X, int l, const T* b0, T* e0, CgReq* dq = nullptr, const dou
     launch_fill<T>(e, nsplit, st);
   }
   const Level& C = X->lev[l + 1];
-  const bool csplit = (l + 1) < tail_start<T>(X);
+  const bool csplit = (l + 1) < tail_start<T>(X);   // (a 2-D level's next one is 2-D: use_2d)
   launch_resid_restrict<T>(L, bx, by, bz, b, e, C, LV<T>::b(C), csplit, st);
   vcycle<T>(X, l + 1, nullptr, nullptr);
   // post-smoothing: (prolongation + black) fused, then red, then black, red

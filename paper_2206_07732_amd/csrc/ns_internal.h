@@ -330,6 +330,18 @@ template <typename T>
 void launch_face_tables(const Dims& n, const T* bx, const T* by, const T* bz, T* tx, T* ty, T* tz, hipStream_t st);
 // whether the library turns the line tables on for a finest level of extents n
 bool face_tables_pay(const Dims& n);
+// a visit of a 2-D level down and up, one launch each: two pre-smoothing sweeps
+// from zero with the restricted residual, and the prolongation with two
+// post-smoothing sweeps (b, e and out natural; csplit: the layout of the next
+// level's vectors).  With r, launch_post2d leaves the partials of r out and
+// returns their count.
+bool tank2d_fits(const Level& L);
+template <typename T, typename TB>
+void launch_pre2d(const Level& L, const T* bx, const T* bz, const T* invd, const TB* b, T* e, bool csplit, T* bc,
+                  hipStream_t st);
+template <typename T, typename TB, typename TO>
+int launch_post2d(const Level& L, const T* bx, const T* bz, const T* invd, const TB* b, const T* e, bool csplit,
+                  const T* ec, TO* out, const double* r, double* partials, hipStream_t st);
 template <typename T>
 void launch_vcycle_tail(const TailDesc<T>& D, size_t lds_bytes, hipStream_t st);
 // M: the matrix of the cycle over D's levels (every one within one wavefront's

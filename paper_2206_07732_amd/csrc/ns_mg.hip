@@ -2478,7 +2478,7 @@ __global__ void __launch_bounds__(kTailThreads) k_vcycle_tail(TailDesc<T> D) {
     if (nl == 0 || up) break;
     t.restrict_to(sm + D.ob[0]);
     tail_levels<T, true>(D, sm, tid, kTailThreads);
-    if constexpr (NP * sizeof(T) >= 24) {
+    if constexpr (NP * sizeof(T) >= 16) {
       // read again rather than kept: the levels between want the registers
       // (also the ones its indices would take: hiding that the thread's number
       // is the same keeps them from being formed once)
@@ -2500,6 +2500,227 @@ __global__ void __launch_bounds__(kTailThreads) k_vcycle_matrix(TailDesc<T> D) {
   __syncthreads();
   tail_matrix_product<T>(D, sm, tid);
   if (tid < N) D.ge[tid] = sm[D.oe[0] + tid];
+}
+
+// ------------------------------------------------------------ 2-D levels
+// A level of a 2-D tank is small: each of its passes is a launch of 3 to 5 us
+// for a fraction of that of work.  So a visit is one launch each way: a block
+// takes a tile of 64 x 8 cells and a ring of four around it, holds the ring's
+// and the tile's coefficients in registers (three cell pairs per thread) and
+// the correction in LDS by colour and pair, and runs all four passes on both;
+// each pass's values are right one cell further in from the ring's edge than
+// the last one's, so the tile's are right at the end.  Every value comes from
+// the same arithmetic as in the separate passes.  The ring costs 2.25 times the
+// tile's loads and arithmetic, a fourth of which four separate passes would
+// have loaded; 256 x 64: 16.5 us of launches for 5.9 down, 18.2 for 7.1 up.
+constexpr int kT2X = 64, kT2Z = 8, kT2H = 4;                         // tile, ring
+constexpr int kT2Row = (kT2X + 2 * kT2H) / 2, kT2Rows = kT2Z + 2 * kT2H;   // pairs per row, rows
+constexpr int kT2P = kT2Row * kT2Rows, kT2Threads = 192, kT2N = kT2P / kT2Threads;
+static_assert(kT2P % kT2Threads == 0, "whole threads");
+
+template <typename T>
+struct Tile2d {
+  T* e;     // LDS: the red plane, kT2P + 2 kT2Row entries before the black one's
+  int x0, z0, nx, nz;
+  T fm[kT2N], f[kT2N][2][3], id[kT2N][2], b[kT2N][2];   // as TailTop: x outer, down, up
+  unsigned in = 0, odd = 0, top = 0;
+
+  static constexpr int kLds = 2 * kT2P + 3 * kT2Row;   // planes, and a row before, between and after
+  __device__ __forceinline__ int pair(int q) const { return (int)threadIdx.x + q * kT2Threads; }
+  // the global cell of pair q's colour c
+  __device__ __forceinline__ int col(int q, int c) const {
+    return x0 - kT2H + 2 * (pair(q) % kT2Row) + (int)(odd >> (2 * q + c) & 1u);
+  }
+  __device__ __forceinline__ int row(int q) const { return z0 - kT2H + pair(q) / kT2Row; }
+  __device__ __forceinline__ bool has(int q, int c) const { return in >> (2 * q + c) & 1u; }
+  // whether the cell lies in the tile (and the grid)
+  __device__ __forceinline__ bool tile(int q, int c) const {
+    const int i = col(q, c) - x0, k = row(q) - z0;
+    return has(q, c) && i >= 0 && i < kT2X && k >= 0 && k < kT2Z;
+  }
+
+  // b natural, 1/D colour-split; every load from a clamped index, what lies
+  // outside the grid zero
+  template <typename TB>
+  __device__ __forceinline__ void load(T* lds, int nx_, int nz_, const T* __restrict__ bx, const T* __restrict__ bz,
+                                       const T* __restrict__ invd, const TB* __restrict__ bg) {
+    e = lds + kT2Row;
+    nx = nx_;
+    nz = nz_;
+    x0 = blockIdx.x * kT2X;
+    z0 = blockIdx.y * kT2Z;
+    const int hx = nx >> 1, P = hx * nz;   // (a level that is halved has an even nx)
+    TB bb[kT2N][2];
+#pragma unroll
+    for (int q = 0; q < kT2N; ++q) {
+      const int k = row(q), kc = min(max(k, 0), nz - 1), i0 = x0 - kT2H + 2 * (pair(q) % kT2Row);
+      const int ic = min(max(i0, 0), nx - 2);
+      const bool ok = k >= 0 && k < nz && i0 >= 0 && i0 < nx;
+      if (k == nz - 1) top |= 1u << q;
+      fm[q] = bx[ic + 1 + (nx + 1) * kc];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int o = (k + c) & 1, g = ic + o + nx * kc;
+        if (o) odd |= 1u << (2 * q + c);
+        if (ok) in |= 1u << (2 * q + c);
+        f[q][c][0] = bx[ic + 2 * o + (nx + 1) * kc];
+        f[q][c][1] = bz[g];
+        f[q][c][2] = bz[g + nx];
+        id[q][c] = invd[c * P + (ic >> 1) + hx * kc];
+        bb[q][c] = bg[g];
+      }
+    }
+    for (int q = threadIdx.x; q < kLds; q += kT2Threads) lds[q] = (T)0;
+#pragma unroll
+    for (int q = 0; q < kT2N; ++q) {
+      const bool ok = in >> (2 * q) & 1u;
+      fm[q] = ok ? fm[q] : (T)0;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) f[q][c][d] = ok ? f[q][c][d] : (T)0;
+        id[q][c] = ok ? id[q][c] : (T)0;
+        b[q][c] = ok ? (T)bb[q][c] : (T)0;
+      }
+    }
+    __syncthreads();
+  }
+  template <int C>
+  __device__ __forceinline__ T* plane() const { return C ? e + kT2P + kT2Row : e; }
+  template <int C>
+  __device__ __forceinline__ void around(int q, T (&v)[4]) const {
+    const T* o = plane<1 - C>() + pair(q);
+    v[0] = o[0];
+    v[1] = o[odd >> (2 * q + C) & 1u ? 1 : -1];
+    v[2] = o[-kT2Row];
+    v[3] = o[kT2Row];
+  }
+  template <int C>
+  __device__ __forceinline__ void pass(bool from_zero) {
+    T v[kT2N][4];
+    if (!from_zero) {
+#pragma unroll
+      for (int q = 0; q < kT2N; ++q) around<C>(q, v[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < kT2N; ++q) {
+      T num = h2 * b[q][C];
+      if (!from_zero) {
+        num += fm[q] * v[q][0];
+        num += f[q][C][0] * v[q][1];
+        num += f[q][C][1] * v[q][2];
+        const T with_up = num + f[q][C][2] * v[q][3];
+        num = top >> q & 1u ? num : with_up;
+      }
+      plane<C>()[pair(q)] = num * id[q][C];
+    }
+    __syncthreads();
+  }
+  template <int C>
+  __device__ __forceinline__ void residual(T ih2, T* rs) const {
+#pragma unroll
+    for (int q = 0; q < kT2N; ++q) {
+      T v[4];
+      around<C>(q, v);
+      const T xc = plane<C>()[pair(q)];
+      T acc = fm[q] * (xc - v[0]);
+      acc += f[q][C][0] * (xc - v[1]);
+      acc += f[q][C][1] * (xc - v[2]);
+      acc += top >> q & 1u ? (T)2 * f[q][C][2] * xc : f[q][C][2] * (xc - v[3]);
+      if (tile(q, C)) rs[col(q, C) - x0 + kT2X * (row(q) - z0)] = b[q][C] - ih2 * acc;
+    }
+  }
+  T h2;
+};
+
+// Down: V(2,.)'s two pre-smoothing sweeps from zero, the correction (natural),
+// and the restricted residual into the next level's b (colour-split when
+// csplit, else natural)
+template <typename T, typename TB>
+__global__ void __launch_bounds__(kT2Threads) k_pre2d(int nx, int nz, T h2, const T* __restrict__ bx,
+                                                      const T* __restrict__ bz, const T* __restrict__ invd,
+                                                      const TB* __restrict__ b, T* __restrict__ e, int csplit,
+                                                      T* __restrict__ bc) {
+  __shared__ T lds[Tile2d<T>::kLds];
+  __shared__ T rs[kT2X * kT2Z];
+  Tile2d<T> t;
+  t.h2 = h2;
+  t.load(lds, nx, nz, bx, bz, invd, b);
+  t.template pass<0>(true);
+  t.template pass<1>(false);
+  t.template pass<0>(false);
+  t.template pass<1>(false);
+  const T ih2 = (T)1 / h2;
+  t.template residual<0>(ih2, rs);
+  t.template residual<1>(ih2, rs);
+#pragma unroll
+  for (int q = 0; q < kT2N; ++q) {
+    const int p = t.pair(q);
+    if (t.tile(q, 0)) e[t.col(q, 0) + nx * t.row(q)] = t.template plane<0>()[p];
+    if (t.tile(q, 1)) e[t.col(q, 1) + nx * t.row(q)] = t.template plane<1>()[p];
+  }
+  __syncthreads();
+  const int ncx = nx >> 1, chx = (ncx + 1) >> 1, cP = chx * (nz >> 1);
+  for (int q = threadIdx.x; q < kT2X * kT2Z / 4; q += kT2Threads) {
+    const int li = q % (kT2X / 2), lk = q / (kT2X / 2), I = t.x0 / 2 + li, K = t.z0 / 2 + lk;
+    if (I >= ncx || K >= nz >> 1) continue;
+    const T* r = rs + 2 * li + 2 * kT2X * lk;
+    T sum = 0;
+    sum += r[0];
+    sum += r[1];
+    sum += r[kT2X];
+    sum += r[kT2X + 1];
+    bc[csplit ? ((I + K) & 1) * cP + (I >> 1) + chx * K : I + ncx * K] = sum * (T)0.25;
+  }
+}
+
+// Up: prolongation of the next level's correction ec, two post-smoothing
+// sweeps, and the result to out (natural; FP64 z of the CG loop, or the level's
+// own e, which no other block's ring reads by then: out is not e).  With r
+// (the CG residual) also the per-block sums of r out.
+template <typename T, typename TB, typename TO>
+__global__ void __launch_bounds__(kT2Threads) k_post2d(int nx, int nz, T h2, const T* __restrict__ bx,
+                                                       const T* __restrict__ bz, const T* __restrict__ invd,
+                                                       const TB* __restrict__ b, const T* __restrict__ e, int csplit,
+                                                       const T* __restrict__ ec, TO* __restrict__ out,
+                                                       const double* __restrict__ r, double* __restrict__ partials) {
+  __shared__ T lds[Tile2d<T>::kLds];
+  Tile2d<T> t;
+  t.h2 = h2;
+  // the red cells' starting values (the first pass overwrites the black ones)
+  T st[kT2N], sc[kT2N];
+  {
+    const int ncx = nx >> 1, chx = (ncx + 1) >> 1, cP = chx * (nz >> 1);
+    const int x0 = blockIdx.x * kT2X, z0 = blockIdx.y * kT2Z;
+#pragma unroll
+    for (int q = 0; q < kT2N; ++q) {
+      const int p = (int)threadIdx.x + q * kT2Threads;
+      const int k = min(max(z0 - kT2H + p / kT2Row, 0), nz - 1), i = min(max(x0 - kT2H + 2 * (p % kT2Row), 0), nx - 2);
+      const int I = i >> 1, K = k >> 1;
+      st[q] = e[i + (k & 1) + nx * k];
+      sc[q] = ec[csplit ? ((I + K) & 1) * cP + (I >> 1) + chx * K : I + ncx * K];
+    }
+  }
+  t.load(lds, nx, nz, bx, bz, invd, b);
+#pragma unroll
+  for (int q = 0; q < kT2N; ++q) t.template plane<0>()[t.pair(q)] = t.has(q, 0) ? st[q] + sc[q] : (T)0;
+  __syncthreads();
+  t.template pass<1>(false);
+  t.template pass<0>(false);
+  t.template pass<1>(false);
+  t.template pass<0>(false);
+  double v[1] = {0.0};
+#pragma unroll
+  for (int q = 0; q < kT2N; ++q)
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+      if (t.tile(q, c)) {
+        const int g = t.col(q, c) + nx * t.row(q);
+        const TO z = (TO)(c ? t.template plane<1>()[t.pair(q)] : t.template plane<0>()[t.pair(q)]);
+        out[g] = z;
+        if (r) v[0] += r[g] * (double)z;
+      }
+  if (r) block_partials<1>(v, partials, (int)(blockIdx.x + gridDim.x * blockIdx.y));
 }
 
 template <typename T>
@@ -3231,6 +3452,39 @@ void launch_tail_matrix(const TailDesc<T>& D, int elems, T* M, hipStream_t st) {
   const int N = D.n[0].nx * D.n[0].ny * D.n[0].nz;
   hipLaunchKernelGGL(k_tail_matrix<T>, dim3(N), dim3(64), (size_t)elems * sizeof(double), st, C, D.pack, M);
 }
+
+// 2-D levels that are halved both ways (k_pre2d, k_post2d)
+bool tank2d_fits(const Level& L) { return L.n.ny == 1 && L.f[0] == 2 && L.f[2] == 2; }
+static dim3 grid2d(const Dims& n) { return dim3((n.nx + kT2X - 1) / kT2X, (n.nz + kT2Z - 1) / kT2Z); }
+
+template <typename T, typename TB>
+void launch_pre2d(const Level& L, const T* bx, const T* bz, const T* invd, const TB* b, T* e, bool csplit, T* bc,
+                  hipStream_t st) {
+  hipLaunchKernelGGL((k_pre2d<T, TB>), grid2d(L.n), dim3(kT2Threads), 0, st, L.n.nx, L.n.nz, (T)(L.h * L.h), bx, bz, invd,
+                     b, e, csplit ? 1 : 0, bc);
+}
+template <typename T, typename TB, typename TO>
+int launch_post2d(const Level& L, const T* bx, const T* bz, const T* invd, const TB* b, const T* e, bool csplit,
+                  const T* ec, TO* out, const double* r, double* partials, hipStream_t st) {
+  const dim3 g = grid2d(L.n);
+  hipLaunchKernelGGL((k_post2d<T, TB, TO>), g, dim3(kT2Threads), 0, st, L.n.nx, L.n.nz, (T)(L.h * L.h), bx, bz, invd, b,
+                     e, csplit ? 1 : 0, ec, out, r, partials);
+  return (int)(g.x * g.y);
+}
+#define NSK_INST2(T, TB)                                                                                        \
+  template void launch_pre2d<T, TB>(const Level&, const T*, const T*, const T*, const TB*, T*, bool, T*, hipStream_t);
+#define NSK_INST3(T, TB, TO)                                                                                    \
+  template int launch_post2d<T, TB, TO>(const Level&, const T*, const T*, const T*, const TB*, const T*, bool, \
+                                        const T*, TO*, const double*, double*, hipStream_t);
+NSK_INST2(double, double)
+NSK_INST2(float, float)
+NSK_INST2(float, double)
+NSK_INST3(double, double, double)
+NSK_INST3(float, float, float)
+NSK_INST3(float, double, double)
+NSK_INST3(float, double, float)
+#undef NSK_INST2
+#undef NSK_INST3
 
 template <typename T>
 void launch_fill(T* a, size_t n, hipStream_t st) {
