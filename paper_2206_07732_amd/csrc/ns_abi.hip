@@ -1514,11 +1514,12 @@ ns_status levelset_advect_reinit(ns_ctx* X, double dt) {
     launch_copy(X->sig_a, X->F.sigma, X->nc, st);
   } else {
     // sig_a keeps sigma0 (for the sign); ping-pong between the field and
-    // sig_b so that the last pseudo-step lands in the field
+    // sig_b so that the last launch (one or two pseudo-steps) lands in the field
     const double* cur = X->sig_a;
-    for (int it = 0; it < nr; ++it) {
-      double* dst = ((nr - 1 - it) % 2 == 0) ? X->F.sigma : X->sig_b;
-      launch_reinit(ph, X->sig_a, cur, dst, dtau, st);
+    const int per = reinit_steps(ph.n), nl = (nr + per - 1) / per;   // launches
+    for (int it = 0; it < nl; ++it) {
+      double* dst = ((nl - 1 - it) % 2 == 0) ? X->F.sigma : X->sig_b;
+      launch_reinit(ph, X->sig_a, cur, dst, dtau, std::min(per, nr - it * per), st);
       cur = dst;
     }
   }

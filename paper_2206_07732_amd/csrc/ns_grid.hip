@@ -202,6 +202,122 @@ __global__ void __launch_bounds__(256) k_advect(Phys P, const double* __restrict
   out[c] = sc - (dt / P.h) * acc;
 }
 
+// The same for larger grids: a lane holds kRR rows of a column and marches up
+// kz planes.  The plane's two neighbours above and below and most along y are
+// then in registers, and the face value above a cell is the one below the next,
+// that between two of its rows serves both: 4.5 of the six limiters and 11.5
+// of the 19 loads, whose issue (16 clocks for a wavefront's 8-byte load) and
+// the index arithmetic around them bound the one-cell form.  Four wavefronts
+// per SIMD hide the loads as well as loading a plane ahead with half as many.
+// 301 x 125 x 131 (39 us at the copy rate): 66 -> 46 us.
+constexpr int kRR = 2, kRW = 8;   // rows of a lane, wavefronts of a block
+__global__ void __launch_bounds__(64 * kRW, 4) k_advect_march(Phys P, const double* __restrict__ s,
+                                                           const double* __restrict__ u, const double* __restrict__ v,
+                                                           const double* __restrict__ w, double dt,
+                                                           double* __restrict__ out, int kz) {
+  constexpr int R = kRR;
+  const Dims n = P.n;
+  const Tile tl = xcd_tile();
+  const int i = tl.x * 64 + threadIdx.x;
+  const int j0 = (tl.y * kRW + __builtin_amdgcn_readfirstlane(threadIdx.y)) * R;
+  const int kb = tl.z * kz, ke = min(kb + kz, n.nz);
+  if (j0 >= n.ny) return;
+  const double c0 = dt / P.h;
+  const int ic = min(i, n.nx - 1);
+  // byte offsets in a plane (32 bits: a load's base is then a scalar)
+  auto at = [](const double* plane, unsigned off) {
+    return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(plane) + off);
+  };
+  unsigned row[R + 4], vrow[R + 1], urow[R];
+#pragma unroll
+  for (int r = 0; r < R + 4; ++r) row[r] = 8u * (unsigned)(n.nx * clampi(j0 + r - 2, 0, n.ny - 1) + ic);
+#pragma unroll
+  for (int r = 0; r < R + 1; ++r) vrow[r] = 8u * (unsigned)(n.nx * min(j0 + r, n.ny) + ic);
+#pragma unroll
+  for (int r = 0; r < R; ++r) urow[r] = 8u * (unsigned)((n.nx + 1) * min(j0 + r, n.ny - 1) + ic);
+  int ox[4];   // the neighbours along x
+#pragma unroll
+  for (int o = 0; o < 4; ++o) ox[o] = 8 * (clampi(ic + (o < 2 ? o - 2 : o - 1), 0, n.nx - 1) - ic);
+  const size_t sxy = (size_t)n.nx * n.ny;
+  struct Plane {
+    double x[R][4], y[4], u[R][2], v[R + 1], w[R];
+  };
+  auto load = [&](int k, Plane& p) {
+    const int kc = min(k, n.nz - 1);
+    const double* q = s + sxy * kc;
+    const double* qu = u + (size_t)(n.nx + 1) * n.ny * kc;
+    const double* qv = v + (size_t)n.nx * (n.ny + 1) * kc;
+    const double* qw = w + sxy * (kc + 1);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+      for (int o = 0; o < 4; ++o) p.x[r][o] = at(q, row[r + 2] + ox[o]);
+      p.u[r][0] = at(qu, urow[r]);
+      p.u[r][1] = at(qu, urow[r] + 8);
+      p.w[r] = at(qw, row[r + 2]);   // the face above
+    }
+    p.y[0] = at(q, row[0]);
+    p.y[1] = at(q, row[1]);
+    p.y[2] = at(q, row[R + 2]);
+    p.y[3] = at(q, row[R + 3]);
+#pragma unroll
+    for (int r = 0; r < R + 1; ++r) p.v[r] = at(qv, vrow[r]);
+  };
+  auto centre = [&](int k, double (&o)[R]) {
+    const double* q = s + sxy * clampi(k, 0, n.nz - 1);
+#pragma unroll
+    for (int r = 0; r < R; ++r) o[r] = at(q, row[r + 2]);
+  };
+  double z[5][R], wm[R], zm[R];   // planes k - 2 .. k + 2; the face below: velocity and value
+  Plane p;
+#pragma unroll
+  for (int o = 0; o < 5; ++o) centre(kb + o - 2, z[o]);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    wm[r] = at(w + sxy * kb, row[r + 2]);
+    zm[r] = koren_face(wm[r], z[0][r], z[1][r], z[2][r], z[3][r]);
+  }
+#pragma unroll 1
+  for (int k = kb; k < ke; ++k) {
+    double zn[R];
+    load(k, p);
+    centre(k + 3, zn);
+    double acc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const double sc = z[2][r];
+      const double sp = koren_face(p.u[r][1], p.x[r][1], sc, p.x[r][2], p.x[r][3]);
+      const double sm = koren_face(p.u[r][0], p.x[r][0], p.x[r][1], sc, p.x[r][2]);
+      acc[r] = p.u[r][1] * (sp - sc) - p.u[r][0] * (sm - sc);
+    }
+    // rows j0 - 2 .. j0 + R + 1
+    double y[R + 4];
+    y[0] = p.y[0];
+    y[1] = p.y[1];
+#pragma unroll
+    for (int r = 0; r < R; ++r) y[r + 2] = z[2][r];
+    y[R + 2] = p.y[2];
+    y[R + 3] = p.y[3];
+    double fy = koren_face(p.v[0], y[0], y[1], y[2], y[3]);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const double fp = koren_face(p.v[r + 1], y[r + 1], y[r + 2], y[r + 3], y[r + 4]);
+      const double sc = z[2][r];
+      acc[r] += p.v[r + 1] * (fp - sc) - p.v[r] * (fy - sc);
+      fy = fp;
+      const double zp = koren_face(p.w[r], z[1][r], sc, z[3][r], z[4][r]);
+      acc[r] += p.w[r] * (zp - sc) - wm[r] * (zm[r] - sc);
+      wm[r] = p.w[r];
+      zm[r] = zp;
+      if (i < n.nx && j0 + r < n.ny)
+        *reinterpret_cast<double*>(reinterpret_cast<char*>(out + sxy * k) + row[r + 2]) = sc - c0 * acc[r];
+#pragma unroll
+      for (int o = 0; o < 4; ++o) z[o][r] = z[o + 1][r];
+      z[4][r] = zn[r];
+    }
+  }
+}
+
 // --------------------------------------------------------------------------
 // reinitialisation pseudo-step: Godunov upwind |grad sigma|, smoothed sign of
 // the pre-reinitialisation field sigma0.
@@ -249,6 +365,174 @@ __global__ void __launch_bounds__(256) k_reinit(Phys P, const double* __restrict
   }
   const double upd = sc - dtau * sg * (sqrt(g2) - 1.0);
   nxt[c] = sg == 0.0 ? sc : upd;
+}
+
+// sqrt(x) for x >= 0 and a / sqrt(x) for x > 0, by Newton steps on the
+// hardware's reciprocal square root (to about one unit in the last place); out
+// of the range that needs no scaling, the library's
+__device__ __forceinline__ double root(double x) {
+  if (!(x > 1e-280 && x < 1e280)) return sqrt(x);
+  const double y = __builtin_amdgcn_rsq(x);
+  const double s0 = x * y, h0 = 0.5 * y, r = fma(-h0, s0, 0.5);
+  const double s1 = fma(s0, r, s0), h1 = fma(h0, r, h0);
+  return fma(fma(-s1, s1, x), h1, s1);
+}
+__device__ __forceinline__ double over_root(double a, double x) {
+  if (!(x > 1e-280 && x < 1e280)) return a / sqrt(x);
+  const double y0 = __builtin_amdgcn_rsq(x);
+  const double e0 = fma(-x * y0, y0, 1.0), y1 = fma(y0 * e0, fma(0.375, e0, 0.5), y0);
+  const double q = a * y1, r = x * y1;   // sqrt(x), then one correction of the quotient
+  return fma(fma(-q, r, a), y1, q);
+}
+
+// A pseudo-step's update of one cell from its six neighbours, f = the sign of
+// sg (1 where positive, else -1): along each direction the larger of the two
+// upwind differences is max(f s - min(f s_-, f s_+), 0).
+__device__ __forceinline__ double reinit_cell(double sc, double sg, double xm, double xp, double ym, double yp,
+                                              double zm, double zp, double dtau, double ih) {
+  const double f = sg > 0.0 ? 1.0 : -1.0;
+  const double fs = f * sc;
+  const double dx = fmax(fs - fmin(f * xm, f * xp), 0.0);
+  const double dy = fmax(fs - fmin(f * ym, f * yp), 0.0);
+  const double dz = fmax(fs - fmin(f * zm, f * zp), 0.0);
+  const double g2 = dx * dx + dy * dy + dz * dz;
+  const double upd = sc - dtau * sg * (root(g2) * ih - 1.0);
+  return sg == 0.0 ? sc : upd;
+}
+
+// STEPS pseudo-steps of the reinitialisation in one launch.  A lane holds
+// kRR rows of a column and marches up kz planes, so a plane's neighbours
+// along z and most along y are in registers, and the next plane's values are
+// loaded a plane ahead.  With two steps the first one's result of the last
+// two planes is in LDS for the second (the block's outer ring of cells only
+// feeds it); the sign of sigma0 is taken once for both.  The one-cell form is
+// bound by its 270 instructions per cell (a root and a division for the sign,
+// a root for the gradient) and at 512 x 256 x 256 by its 24 bytes; 301 x 125 x
+// 131 (23 us a step at the copy rate): five steps 194 -> 121 us, 512 x 256 x
+// 256: 1130 -> 790 us.
+template <int STEPS, bool FIRST>
+__global__ void __launch_bounds__(64 * kRW) k_reinit_march(Phys P, const double* __restrict__ s0,
+                                                         const double* __restrict__ cur, double* __restrict__ nxt,
+                                                         double dtau, int kz) {
+  constexpr int H = STEPS - 1, R = kRR, kRows = kRW * R;
+  __shared__ double lds[STEPS == 2 ? 2 * kRows * 64 : 1];
+  const Dims n = P.n;
+  const Tile tl = xcd_tile();
+  const int lane = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(threadIdx.y);
+  const int i = tl.x * (64 - 2 * H) - H + lane;
+  const int j0 = tl.y * (kRows - 2 * H) - H + wv * R;
+  const int kb = tl.z * kz, ke = min(kb + kz, n.nz);
+  const int sxy = n.nx * n.ny;
+  const double h = P.h, h2 = h * h, ih = 1.0 / h;
+  const int ic = clampi(i, 0, n.nx - 1), im = max(ic - 1, 0), ip = min(ic + 1, n.nx - 1);
+  // byte offsets in a plane (32 bits: a load's base is then a scalar): of the
+  // lane's cell in its rows and the rows beside them; of its neighbours along x
+  unsigned row[R + 2];
+#pragma unroll
+  for (int r = 0; r < R + 2; ++r) row[r] = 8u * (unsigned)(n.nx * clampi(j0 + r - 1, 0, n.ny - 1) + ic);
+  const int om = 8 * (im - ic), op = 8 * (ip - ic);
+  auto at = [](const double* plane, unsigned off) {
+    return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(plane) + off);
+  };
+  double cm[R], cc[R], cp[R], a0[R], xm[R], xp[R], ym, yp;
+  double sm[R], s1[R], g1[R];   // the first step's result two and one planes down, and its sign
+  auto centre = [&](int k, double (&o)[R]) {
+    const double* q = cur + (size_t)sxy * clampi(k, 0, n.nz - 1);
+#pragma unroll
+    for (int r = 0; r < R; ++r) o[r] = at(q, row[r + 1]);
+  };
+  auto beside = [&](int k, double (&m)[R], double (&pl)[R], double& lo, double& hi, double (&a)[R]) {
+    const double* q = cur + (size_t)sxy * clampi(k, 0, n.nz - 1);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      m[r] = at(q, row[r + 1] + om);
+      pl[r] = at(q, row[r + 1] + op);
+    }
+    lo = at(q, row[0]);
+    hi = at(q, row[R + 1]);
+    if (!FIRST) {
+      const double* z = s0 + (size_t)sxy * clampi(k, 0, n.nz - 1);
+#pragma unroll
+      for (int r = 0; r < R; ++r) a[r] = at(z, row[r + 1]);
+    }
+  };
+  const int p0 = max(kb - H, 0), p1 = ke - 1 + H;   // the first step's planes (the last may lie above the top)
+  centre(p0 - 1, cm);
+  centre(p0, cc);
+  centre(p0 + 1, cp);
+  beside(p0, xm, xp, ym, yp, a0);
+  auto put = [&](int k, int r, double v) {
+    *reinterpret_cast<double*>(reinterpret_cast<char*>(nxt + (size_t)sxy * k) + row[r + 1]) = v;
+  };
+  const bool outx = i < n.nx && (H == 0 || (lane > 0 && lane < 63));
+  const int lm = lane - (i > 0 ? 1 : 0), lp = lane + (i < n.nx - 1 ? 1 : 0);
+  const int lrow = wv * R;
+#pragma unroll 2
+  for (int p = p0; p <= p1; ++p) {
+    double cn[R], an[R], xmn[R], xpn[R], ymn, ypn;
+    double u[R], sg[R];
+    if (STEPS == 1 || p < n.nz) {
+      centre(p + 2, cn);
+      beside(p + 1, xmn, xpn, ymn, ypn, an);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const double a = FIRST ? cc[r] : a0[r];
+        sg[r] = over_root(a, a * a + h2);
+        u[r] = reinit_cell(cc[r], sg[r], xm[r], xp[r], r > 0 ? cc[r - 1] : ym, r < R - 1 ? cc[r + 1] : yp, cm[r], cp[r],
+                           dtau, ih);
+      }
+    }
+    if constexpr (STEPS == 1) {
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (outx && j0 + r < n.ny) put(p, r, u[r]);
+    } else {
+      if (p == n.nz) {   // above the top: the top plane's values
+#pragma unroll
+        for (int r = 0; r < R; ++r) u[r] = s1[r];
+      } else if (p == 0) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) s1[r] = u[r];   // (below the bed: the bottom plane's)
+      }
+      double* w = lds + (p & 1) * kRows * 64;
+      const double* b = lds + ((p - 1) & 1) * kRows * 64;
+      if (p < ke) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) w[(lrow + r) * 64 + lane] = u[r];
+      }
+      if (p > kb) {   // the second step, on plane p - 1
+        const int jm = j0 > 0 ? max(lrow - 1, 0) : lrow;
+        const double lo = b[jm * 64 + lane], hi = b[min(lrow + R, kRows - 1) * 64 + lane];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int y = j0 + r, lr = lrow + r;
+          const double vm = b[lr * 64 + max(lm, 0)], vp = b[lr * 64 + min(lp, 63)];
+          const double wm = y > 0 ? (r > 0 ? s1[r - 1] : lo) : s1[r];
+          const double wp = y < n.ny - 1 ? (r < R - 1 ? s1[r + 1] : hi) : s1[r];
+          const double o = reinit_cell(s1[r], g1[r], vm, vp, wm, wp, sm[r], u[r], dtau, ih);
+          if (outx && y >= 0 && y < n.ny && lr > 0 && lr < kRows - 1) put(p - 1, r, o);
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        sm[r] = s1[r];
+        s1[r] = u[r];
+        g1[r] = sg[r];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      cm[r] = cc[r];
+      cc[r] = cp[r];
+      cp[r] = cn[r];
+      a0[r] = an[r];
+      xm[r] = xmn[r];
+      xp[r] = xpn[r];
+    }
+    ym = ymn;
+    yp = ypn;
+  }
 }
 
 __global__ void k_copy(const double* __restrict__ a, double* __restrict__ b, size_t n) {
@@ -856,16 +1140,58 @@ __global__ void __launch_bounds__(1024) k_diag_finalize(const double* __restrict
 }  // namespace
 
 // ------------------------------------------------------------------ launchers
+// Where a lane marches up a column: from 2^20 cells on; below it a cell per lane,
+// whose many short wavefronts fill the chip better (128 x 64 x 64: advection
+// and five pseudo-steps 36 us against 43; 200 x 72 x 104: 98 against 80)
+static bool marches(const Dims& n) { return n.ny >= 4 && (long)n.nx * n.ny * n.nz >= (1L << 20); }
+int reinit_steps(const Dims& n) { return marches(n) ? 2 : 1; }
+
+// Planes of a march: the fewest rounds of blocks over the chip's 512 places
+// (two blocks per compute unit) times a block's planes, four more being spent
+// on its start and the planes that only feed it
+static int march_planes(int cols, int nz) {
+  int best = nz;
+  long cost = -1;
+  for (int c = 1; c <= std::max(1, nz / 4); ++c) {
+    const int kz = (nz + c - 1) / c;
+    const long t = (((long)cols * ((nz + kz - 1) / kz) + 511) / 512) * (kz + 4);
+    if (cost < 0 || t < cost) cost = t, best = kz;
+  }
+  return best;
+}
+
 void launch_advect(const Phys& P, const double* s, const double* u, const double* v, const double* w,
                    double dt, double* out, hipStream_t st) {
-  Geo g = geo3(P.n.nx, P.n.ny, P.n.nz);
+  const Dims n = P.n;
+  if (marches(n)) {
+    const int gx = (n.nx + 63) / 64, gy = (n.ny + kRW * kRR - 1) / (kRW * kRR), kz = march_planes(gx * gy, n.nz);
+    hipLaunchKernelGGL(k_advect_march, dim3(gx, gy, (n.nz + kz - 1) / kz), dim3(64, kRW), 0, st, P, s, u, v, w, dt, out, kz);
+    return;
+  }
+  Geo g = geo3(n.nx, n.ny, n.nz);
   hipLaunchKernelGGL(k_advect, g.grid, g.block, 0, st, P, s, u, v, w, dt, out);
 }
 
-void launch_reinit(const Phys& P, const double* s0, const double* cur, double* nxt, double dtau,
+template <int STEPS, bool FIRST>
+static void reinit_march(const Phys& P, const double* s0, const double* cur, double* nxt, double dtau, hipStream_t st) {
+  constexpr int H = STEPS - 1, rows = kRW * kRR - 2 * H, lanes = 64 - 2 * H;
+  const Dims n = P.n;
+  const int gx = (n.nx + lanes - 1) / lanes, gy = (n.ny + rows - 1) / rows, kz = march_planes(gx * gy, n.nz);
+  hipLaunchKernelGGL((k_reinit_march<STEPS, FIRST>), dim3(gx, gy, (n.nz + kz - 1) / kz), dim3(64, kRW), 0, st, P, s0, cur,
+                     nxt, dtau, kz);
+}
+
+void launch_reinit(const Phys& P, const double* s0, const double* cur, double* nxt, double dtau, int steps,
                    hipStream_t st) {
-  Geo g = geo3(P.n.nx, P.n.ny, P.n.nz);
-  hipLaunchKernelGGL(k_reinit, g.grid, g.block, 0, st, P, s0, cur, nxt, dtau);
+  const bool first = s0 == cur;   // (sigma0 is then read once)
+  if (reinit_steps(P.n) == 1) {
+    Geo g = geo3(P.n.nx, P.n.ny, P.n.nz);
+    hipLaunchKernelGGL(k_reinit, g.grid, g.block, 0, st, P, s0, cur, nxt, dtau);
+  } else if (steps == 2) {
+    first ? reinit_march<2, true>(P, s0, cur, nxt, dtau, st) : reinit_march<2, false>(P, s0, cur, nxt, dtau, st);
+  } else {
+    first ? reinit_march<1, true>(P, s0, cur, nxt, dtau, st) : reinit_march<1, false>(P, s0, cur, nxt, dtau, st);
+  }
 }
 
 void launch_copy(const double* src, double* dst, size_t n, hipStream_t st) {

@@ -236,8 +236,9 @@ constexpr int kHostPartsMax = 8192;
 // grid step kernels (ns_grid.hip)
 void launch_advect(const Phys& P, const double* s, const double* u, const double* v, const double* w,
                    double dt, double* out, hipStream_t st);
-void launch_reinit(const Phys& P, const double* s0, const double* cur, double* nxt, double dtau,
+void launch_reinit(const Phys& P, const double* s0, const double* cur, double* nxt, double dtau, int steps,
                    hipStream_t st);
+int reinit_steps(const Dims& n);
 void launch_copy(const double* src, double* dst, size_t n, hipStream_t st);
 void launch_props(const Phys& P, const double* sigma, double t, double* rho, double* rfl, double* mu,
                   double* chi, hipStream_t st);

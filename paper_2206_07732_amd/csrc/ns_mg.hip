@@ -2510,9 +2510,9 @@ __global__ void __launch_bounds__(kTailThreads) k_vcycle_matrix(TailDesc<T> D) {
 // the correction in LDS by colour and pair, and runs all four passes on both;
 // each pass's values are right one cell further in from the ring's edge than
 // the last one's, so the tile's are right at the end.  Every value comes from
-// the same arithmetic as in the separate passes.  The ring costs 2.25 times the
-// tile's loads and arithmetic, a fourth of which four separate passes would
-// have loaded; 256 x 64: 16.5 us of launches for 5.9 down, 18.2 for 7.1 up.
+// the same arithmetic as in the separate passes.  With its ring a tile is 2.25
+// times its cells, loaded once where the separate passes load them four to
+// five times; 256 x 64: 16.5 us of launches for 5.9 down, 18.2 for 7.1 up.
 constexpr int kT2X = 64, kT2Z = 8, kT2H = 4;                         // tile, ring
 constexpr int kT2Row = (kT2X + 2 * kT2H) / 2, kT2Rows = kT2Z + 2 * kT2H;   // pairs per row, rows
 constexpr int kT2P = kT2Row * kT2Rows, kT2Threads = 192, kT2N = kT2P / kT2Threads;
