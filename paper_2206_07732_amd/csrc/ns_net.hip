@@ -66,34 +66,82 @@ __device__ __forceinline__ long vox_count(const VDims& d) { return (long)d.nx * 
 // at half resolution read through nearest upsampling (channel stride sb), so
 // the decoder never materialises its upsampled inputs.
 // EPI 0: + bias, ReLU; 1: plain (gradient w.r.t. the input); 2: + bias,
-// ReLU, then the 1x1x1 head 16 -> 1 into delta (FP32), storing the
-// activation only when Y is given.
+// ReLU, then the 1x1x1 head 16 -> 1 into delta (FP32) and, if given, delta2;
+// the activation is not stored.
+// A tile has M rows in y (few_blocks, many_blocks), a block NB of the output channels' groups of 16: the accumulators' order of
+// summation is the same in every form.
 constexpr int kTX = 16, kTY = 4, kTZ = 4;
-constexpr int kHX = kTX + 2, kHY = kTY + 2, kHZ = kTZ + 2, kHV = kHX * kHY * kHZ;
-// The two 8-channel halves of a staged chunk live in separate planes
-// (16-byte entries).  Adjacent 16-lane groups of an A-fragment read take the
-// two halves of the same voxels; the LDS serves half of one group with half
-// of the next, which is free of bank conflicts only when their entries are a
-// multiple of 16 apart, so the plane stride is a multiple of 16 entries.
-constexpr int kPlane = (kHV + 15) / 16 * 16;
+template <int M>
+struct ConvTile {
+  static constexpr int HX = kTX + 2, HY = M + 2, HZ = kTZ + 2, HV = HX * HY * HZ;
+  // The two 8-channel halves of a staged chunk live in separate planes
+  // (16-byte entries).  Adjacent 16-lane groups of an A-fragment read take the
+  // two halves of the same voxels; the LDS serves half of one group with half
+  // of the next, which is free of bank conflicts only when their entries are a
+  // multiple of 16 apart, so the plane stride is a multiple of 16 entries.
+  static constexpr int plane = (HV + 15) / 16 * 16;
+  // offset of tap (dz, dy, dx) = (tap / 9, tap / 3 % 3, tap % 3) in the halo tile (0 for the pad tap)
+  __host__ __device__ static constexpr int tap_off(int tap) {
+    return tap >= 27 ? 0 : ((tap / 9) * HY + (tap / 3) % 3) * HX + tap % 3;
+  }
+};
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 u) { return __builtin_bit_cast(bf16x8, u); }
 
-// offset of tap (dz, dy, dx) = (tap / 9, tap / 3 % 3, tap % 3) in the halo tile (0 for the pad tap)
-__host__ __device__ constexpr int tap_off(int tap) {
-  return tap >= 27 ? 0 : ((tap / 9) * kHY + (tap / 3) % 3) * kHX + tap % 3;
+// 2x2x2 averages of a block's staged tile (per wavefront, i.e. z-plane, 16 M
+// voxels of C channels) into the half-resolution tensor P, whose channels are
+// all the block's; in k_pool's order
+template <int C, int M>
+__device__ __forceinline__ void pool_tile(const uint16_t* stg, const VDims& d, int x0, int y0, int z0, int ps, int po,
+                                          uint16_t* __restrict__ P) {
+  constexpr int G = C / 8, NV = 8 * (M / 2) * (kTZ / 2);
+  const int e = threadIdx.x, v = e / G, g = e % G;
+  const int X = v % 8, Y = v / 8 % (M / 2), Z = v / (4 * M);
+  const int gx = x0 / 2 + X, gy = y0 / 2 + Y, gz = z0 / 2 + Z;
+  if (v >= NV || gx >= d.nx / 2 || gy >= d.ny / 2 || gz >= d.nz / 2) return;
+  float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int i = q & 1, j = q >> 1 & 1, k = q >> 2;
+    const u32x4 w = *reinterpret_cast<const u32x4*>(stg + ((2 * Z + k) * 16 * M + (2 * Y + j) * 16 + 2 * X + i) * C + 8 * g);
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      s[2 * h] += __uint_as_float(w[h] << 16);
+      s[2 * h + 1] += __uint_as_float(w[h] & 0xFFFF0000u);
+    }
+  }
+  u32x4 o;
+#pragma unroll
+  for (int h = 0; h < 4; ++h) o[h] = (uint32_t)f2bf(s[2 * h] * 0.125f) | ((uint32_t)f2bf(s[2 * h + 1] * 0.125f) << 16);
+  *reinterpret_cast<u32x4*>(P + ((long)gx + (long)(d.nx / 2) * (gy + (long)(d.ny / 2) * gz)) * ps + po + 8 * g) = o;
 }
 
-template <int CIN, int COUT, int EPI>
+// the sum of the 16 lanes of a row (in the order of an exclusive-or butterfly)
+template <int N>
+__device__ __forceinline__ float ror16(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float sum16(float v) {
+  v += ror16<8>(v);
+  v += ror16<4>(v);
+  v += ror16<2>(v);
+  v += ror16<1>(v);
+  return v;
+}
+
+template <int CIN, int COUT, int EPI, int M, int NB, bool POOL>
 __global__ void __launch_bounds__(256) k_conv(VDims d, const uint16_t* __restrict__ XA, int sa, int ca,
                                               const uint16_t* __restrict__ XB, int sb,
                                               const uint16_t* __restrict__ W, const float* __restrict__ bias,
                                               uint16_t* __restrict__ Y, int ys, int yo,
                                               const float* __restrict__ hw, const float* __restrict__ hb,
-                                              float* __restrict__ delta) {
+                                              float* __restrict__ delta, float* __restrict__ delta2,
+                                              uint16_t* __restrict__ P) {
   static_assert(CIN % 16 == 0 && COUT % 16 == 0, "channels in multiples of 16");
   static_assert(EPI != 2 || COUT == 16, "the fused head takes 16 channels");
-  constexpr int NT = COUT / 16, NC = CIN / 16;
+  using L = ConvTile<M>;
+  constexpr int NG = COUT / 16 / NB, NC = CIN / 16, CB = 16 * NB;   // CB: output channels of the block
+  constexpr int kHX = L::HX, kHY = L::HY, kHV = L::HV, kPlane = L::plane;
   constexpr int NE = (2 * kHV + 255) / 256;   // 16-byte tile pieces per thread
   // Weight fragments are loaded per tap pair (they stay in the caches):
   // holding a chunk's fourteen ahead in registers cost two of the wide
@@ -101,7 +149,8 @@ __global__ void __launch_bounds__(256) k_conv(VDims d, const uint16_t* __restric
   __shared__ u32x4 tile[2][2 * kPlane];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 15, kg = lane >> 4;
-  const int x0 = blockIdx.x * kTX, y0 = blockIdx.y * kTY, z0 = blockIdx.z * kTZ;
+  const int x0 = blockIdx.x / NG * kTX, y0 = blockIdx.y * M, z0 = blockIdx.z * kTZ;
+  const int g0 = blockIdx.x % NG * CB;   // the block's first output channel
   const int cnx = d.nx >> 1, cny = d.ny >> 1;
   const u32x4 zero = {0u, 0u, 0u, 0u};
   // this thread's tile pieces: fine and coarse voxel of each, in-grid mask
@@ -141,18 +190,18 @@ __global__ void __launch_bounds__(256) k_conv(VDims d, const uint16_t* __restric
     }
   };
   // weight fragment of tap pair p, output tile t, chunk c
-  const uint16_t* wl = W + (long)r * 27 * CIN + (long)(kg >> 1) * CIN + 8 * (kg & 1);
+  const uint16_t* wl = W + (long)(g0 + r) * 27 * CIN + (long)(kg >> 1) * CIN + 8 * (kg & 1);
   auto wfrag = [&](int p, int t, int c) -> bf16x8 {
     const int tap = 2 * p + (kg >> 1);
     return as_bf16x8(tap < 27 ? *reinterpret_cast<const u32x4*>(wl + (long)t * 16 * 27 * CIN + 2 * p * CIN + 16 * c)
                               : zero);
   };
   const int lbase = (kg & 1) * kPlane + wave * kHY * kHX + r;   // this lane's A piece for tap 0, row 0
-  f32x4 acc[4][NT];
+  f32x4 acc[M][NB];
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
+  for (int m = 0; m < M; ++m)
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < NB; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   fetch(0);
   put(0);
   __syncthreads();
@@ -164,56 +213,57 @@ __global__ void __launch_bounds__(256) k_conv(VDims d, const uint16_t* __restric
   // peak).  The first pairs' weights are requested before the next chunk's
   // tile pieces, which the in-order load counter would otherwise make them
   // wait behind.
-  constexpr int WD = NT == 1 ? 3 : 1;   // weight prefetch distance in tap pairs
-  bf16x8 aq[2][4], bq[WD + 1][NT];
+  constexpr int WD = M == 2 ? 13 : M == 4 && NB == 1 ? 3 : 1;   // weight prefetch distance in tap pairs
+  bf16x8 aq[2][M], bq[WD + 1][NB];
 #pragma unroll 1
   for (int c = 0; c < NC; ++c) {
     const u32x4* T = tile[c & 1] + lbase;
-    auto lda = [&](int p, bf16x8 (&a)[4]) {
+    auto lda = [&](int p, bf16x8 (&a)[M]) {
       const bool tv = 2 * p + (kg >> 1) < 27;
-      const int o = (kg >> 1) ? tap_off(2 * p + 1) : tap_off(2 * p);
+      const int o = (kg >> 1) ? L::tap_off(2 * p + 1) : L::tap_off(2 * p);
 #pragma unroll
-      for (int m = 0; m < 4; ++m) a[m] = as_bf16x8(tv ? T[o + m * kHX] : zero);
+      for (int m = 0; m < M; ++m) a[m] = as_bf16x8(tv ? T[o + m * kHX] : zero);
     };
 #pragma unroll
     for (int q = 0; q < WD; ++q)
 #pragma unroll
-      for (int t = 0; t < NT; ++t) bq[q][t] = wfrag(q, t, c);
+      for (int t = 0; t < NB; ++t) bq[q][t] = wfrag(q, t, c);
     if (c + 1 < NC) fetch(c + 1);
     lda(0, aq[0]);
 #pragma unroll
     for (int p = 0; p < 14; ++p) {
       if (p + WD < 14) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t) bq[(p + WD) % (WD + 1)][t] = wfrag(p + WD, t, c);
+        for (int t = 0; t < NB; ++t) bq[(p + WD) % (WD + 1)][t] = wfrag(p + WD, t, c);
       }
       if (p + 1 < 14) lda(p + 1, aq[(p + 1) & 1]);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int m = 0; m < 4; ++m)
+      for (int m = 0; m < M; ++m)
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+        for (int t = 0; t < NB; ++t)
           acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq[p & 1][m], bq[p % (WD + 1)][t], acc[m][t], 0, 0, 0);
     }
     if (c + 1 < NC) put((c + 1) & 1);
     __syncthreads();
   }
-  // Epilogue.  Up to 64 output channels the wave's 64 voxels x COUT results
+  // Epilogue.  Up to 64 output channels the wave's 16 M voxels x CB results
   // are transposed through its own slice of the (now idle) tile memory and
   // stored as 16-byte pieces of 8 channels; wider layers store directly.
-  constexpr bool STAGE = COUT <= 64;
-  static_assert(!STAGE || 4 * 64 * COUT * 2 <= (int)sizeof(tile), "staging fits in the tile");
-  const bool store = (EPI != 2) || (Y != nullptr);
-  uint16_t* stg = reinterpret_cast<uint16_t*>(&tile[0][0]) + wave * 64 * COUT;
+  constexpr bool STAGE = CB <= 64;
+  static_assert(!STAGE || 4 * 16 * M * CB * 2 <= (int)sizeof(tile), "staging fits in the tile");
+  static_assert(!POOL || (STAGE && M % 2 == 0), "pooled from the staged tile");
+  constexpr bool store = EPI != 2;   // (the head's layer keeps no activation)
+  uint16_t* stg = reinterpret_cast<uint16_t*>(&tile[0][0]) + wave * 16 * M * CB;
   const int z = z0 + wave;
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
+  for (int m = 0; m < M; ++m) {
     const int y = y0 + m;
     const long row = (long)d.nx * (y + (long)d.ny * z);
     float hs[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int co = t * 16 + r;
+    for (int t = 0; t < NB; ++t) {
+      const int cl = t * 16 + r, co = g0 + cl;
       const float bb = (EPI == 1) ? 0.f : bias[co];
       const float wh = (EPI == 2) ? hw[co] : 0.f;
 #pragma unroll
@@ -222,8 +272,8 @@ __global__ void __launch_bounds__(256) k_conv(VDims d, const uint16_t* __restric
         float val = acc[m][t][i] + bb;
         if (EPI != 1) val = fmaxf(val, 0.f);
         const uint16_t q = f2bf(val);
-        if (STAGE)
-          stg[(m * 16 + 4 * kg + i) * COUT + co] = q;
+        if (STAGE && store)
+          stg[(m * 16 + 4 * kg + i) * CB + cl] = q;
         else if (store && x < d.nx && y < d.ny && z < d.nz)
           Y[(row + x) * ys + yo + co] = q;
         if (EPI == 2) hs[i] = wh * bf2f(q);
@@ -232,30 +282,32 @@ __global__ void __launch_bounds__(256) k_conv(VDims d, const uint16_t* __restric
     if (EPI == 2) {
       // sum the 16 channels: the 16 lanes of one row group
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int o = 8; o >= 1; o >>= 1) hs[i] += __shfl_xor(hs[i], o, 16);
+      for (int i = 0; i < 4; ++i) hs[i] = sum16(hs[i]);
       if (r == 0 && y < d.ny && z < d.nz) {
         const float b0 = hb[0];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int x = x0 + 4 * kg + i;
-          if (x < d.nx) delta[row + x] = hs[i] + b0;
+          if (x < d.nx) {
+            delta[row + x] = hs[i] + b0;
+            if (delta2) delta2[row + x] = hs[i] + b0;
+          }
         }
       }
     }
   }
   if (STAGE && store) {
     __syncthreads();
-    constexpr int G = COUT / 8;   // 16-byte pieces per voxel
+    constexpr int G = CB / 8;   // 16-byte pieces per voxel
 #pragma unroll
-    for (int j = 0; j < G; ++j) {
+    for (int j = 0; j < (M * G + 3) / 4; ++j) {
       const int q = lane + 64 * j, vl = q / G, cg = q % G;
       const int x = x0 + (vl & 15), y = y0 + (vl >> 4);
-      if (x < d.nx && y < d.ny && z < d.nz)
-        *reinterpret_cast<u32x4*>(Y + ((long)x + (long)d.nx * (y + (long)d.ny * z)) * ys + yo + 8 * cg) =
-            *reinterpret_cast<const u32x4*>(stg + vl * COUT + 8 * cg);
+      if (vl < 16 * M && x < d.nx && y < d.ny && z < d.nz)
+        *reinterpret_cast<u32x4*>(Y + ((long)x + (long)d.nx * (y + (long)d.ny * z)) * ys + yo + g0 + 8 * cg) =
+            *reinterpret_cast<const u32x4*>(stg + vl * CB + 8 * cg);
     }
+    if (POOL) pool_tile<CB, M>(reinterpret_cast<uint16_t*>(&tile[0][0]), d, x0, y0, z0, COUT, g0, P);
   }
 }
 
@@ -278,34 +330,31 @@ __global__ void __launch_bounds__(256) k_conv(VDims d, const uint16_t* __restric
 // tile leaves two blocks per compute unit; a chunk's staging is hidden only
 // by the other block.
 constexpr int kCX = 16, kCY = 8, kCZ = 4;
-constexpr int kCHX = kCX + 2, kCHY = kCY + 2, kCHZ = kCZ + 2, kCHV = kCHX * kCHY * kCHZ;
-constexpr int kCPlane = (kCHV + 15) / 16 * 16;
 
-template <int CIN, int COUT, int EPI>
+template <int CIN, int COUT, int M, int NB>
 __global__ void __launch_bounds__(256) k_conv_cm(VDims d, const uint16_t* __restrict__ XA, int sa, int ca,
                                                  const uint16_t* __restrict__ XB, int sb,
                                                  const uint16_t* __restrict__ W, const float* __restrict__ bias,
-                                                 uint16_t* __restrict__ Y, int ys, int yo,
-                                                 const float* __restrict__ hw, const float* __restrict__ hb,
-                                                 float* __restrict__ delta) {
+                                                 uint16_t* __restrict__ Y, int ys, int yo) {
   static_assert(CIN % 16 == 0 && COUT % 16 == 0, "channels in multiples of 16");
-  static_assert(EPI != 1, "the gradient w.r.t. the input runs on k_conv");
-  static_assert(EPI != 2 || COUT == 16, "the fused head takes 16 channels");
   static_assert(CIN % 32 == 0, "whole chunks of 32 input channels");
-  constexpr int NT = COUT / 16, NC = CIN / 32;
+  constexpr int NG = COUT / 16 / NB, NC = CIN / 32, CB = 16 * NB;
+  constexpr int kCHX = kCX + 2, kCHY = M + 2, kCHZ = kCZ + 2, kCHV = kCHX * kCHY * kCHZ;
+  constexpr int kCPlane = (kCHV + 15) / 16 * 16;
   __shared__ u32x4 tile[4 * kCPlane];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 15, kg = lane >> 4;
-  const int x0 = blockIdx.x * kCX, y0 = blockIdx.y * kCY, z0 = blockIdx.z * kCZ;
+  const int x0 = blockIdx.x / NG * kCX, y0 = blockIdx.y * M, z0 = blockIdx.z * kCZ;
+  const int g0 = blockIdx.x % NG * CB;   // the block's first output channel
   const int cnx = d.nx >> 1, cny = d.ny >> 1;
   const u32x4 zero = {0u, 0u, 0u, 0u};
-  f32x4 acc[kCY][NT];
+  f32x4 acc[M][NB];
 #pragma unroll
-  for (int m = 0; m < kCY; ++m)
+  for (int m = 0; m < M; ++m)
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < NB; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   // weight fragment: output column r of tile t, channels 32 c + 8 kg .. + 7 of tap
-  const uint16_t* wl = W + (long)r * 27 * CIN + 8 * kg;
+  const uint16_t* wl = W + (long)(g0 + r) * 27 * CIN + 8 * kg;
   auto wfrag = [&](int tap, int t, int c) -> bf16x8 {
     return as_bf16x8(*reinterpret_cast<const u32x4*>(wl + (long)t * 16 * 27 * CIN + (long)tap * CIN + 32 * c));
   };
@@ -331,6 +380,15 @@ __global__ void __launch_bounds__(256) k_conv_cm(VDims d, const uint16_t* __rest
       const u32x4 w = *reinterpret_cast<const u32x4*>(src);
       v[s] = in ? w : zero;
     }
+    // (few blocks: nothing else hides the weights' latency, so all of the chunk's
+    // are requested with its activations)
+    bf16x8 ball[M == 2 ? 27 : 1][NB];
+    if constexpr (M == 2) {
+#pragma unroll
+      for (int tap = 0; tap < 27; ++tap)
+#pragma unroll
+        for (int t = 0; t < NB; ++t) ball[tap][t] = wfrag(tap, t, c);
+    }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
@@ -343,20 +401,23 @@ __global__ void __launch_bounds__(256) k_conv_cm(VDims d, const uint16_t* __rest
     for (int dz = 0; dz < 3; ++dz) {
 #pragma unroll
       for (int dx = 0; dx < 3; ++dx) {
-        bf16x8 b[3][NT];
+        bf16x8 b[3][NB];
 #pragma unroll
         for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
-          for (int t = 0; t < NT; ++t) b[dy][t] = wfrag(9 * dz + 3 * dy + dx, t, c);
+          for (int t = 0; t < NB; ++t) {
+            const int tap = 9 * dz + 3 * dy + dx;
+            b[dy][t] = M == 2 ? ball[M == 2 ? tap : 0][t] : wfrag(tap, t, c);
+          }
         bf16x8 a[kCHY];
 #pragma unroll
         for (int hy = 0; hy < kCHY; ++hy) a[hy] = as_bf16x8(T[((wave + dz) * kCHY + hy) * kCHX + dx]);
 #pragma unroll
         for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
-          for (int m = 0; m < kCY; ++m)
+          for (int m = 0; m < M; ++m)
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
+            for (int t = 0; t < NB; ++t)
               acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m + dy], b[dy][t], acc[m][t], 0, 0, 0);
       }
     }
@@ -364,87 +425,66 @@ __global__ void __launch_bounds__(256) k_conv_cm(VDims d, const uint16_t* __rest
   // Epilogue: + bias, ReLU, BF16; the wave's 128 voxels x COUT results are
   // transposed through its own slice of the tile memory and stored as
   // 16-byte pieces of 8 channels.
-  static_assert(kCY * 16 * COUT * 2 * 4 <= (int)sizeof(tile), "staging fits in the tile");
-  const bool store = (EPI != 2) || (Y != nullptr);
+  static_assert(M * 16 * CB * 2 * 4 <= (int)sizeof(tile), "staging fits in the tile");
   __syncthreads();
-  uint16_t* stg = reinterpret_cast<uint16_t*>(&tile[0]) + wave * kCY * 16 * COUT;
+  uint16_t* stg = reinterpret_cast<uint16_t*>(&tile[0]) + wave * M * 16 * CB;
   const int z = z0 + wave;
 #pragma unroll
-  for (int m = 0; m < kCY; ++m) {
-    const int y = y0 + m;
-    const long row = (long)d.nx * (y + (long)d.ny * z);
-    float hs[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int m = 0; m < M; ++m) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int co = t * 16 + r;
+    for (int t = 0; t < NB; ++t) {
+      const int cl = t * 16 + r, co = g0 + cl;
       const float bb = bias[co];
-      const float wh = (EPI == 2) ? hw[co] : 0.f;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float val = fmaxf(acc[m][t][i] + bb, 0.f);
         const uint16_t q = f2bf(val);
-        stg[(m * 16 + 4 * kg + i) * COUT + co] = q;
-        if (EPI == 2) hs[i] = wh * bf2f(q);
-      }
-    }
-    if (EPI == 2) {
-      // sum the 16 channels: the 16 lanes of one row group
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int o = 8; o >= 1; o >>= 1) hs[i] += __shfl_xor(hs[i], o, 16);
-      if (r == 0 && y < d.ny && z < d.nz) {
-        const float b0 = hb[0];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int x = x0 + 4 * kg + i;
-          if (x < d.nx) delta[row + x] = hs[i] + b0;
-        }
+        stg[(m * 16 + 4 * kg + i) * CB + cl] = q;
       }
     }
   }
-  if (store) {
+  {
     __syncthreads();
-    constexpr int G = COUT / 8;   // 16-byte pieces per voxel
+    constexpr int G = CB / 8;   // 16-byte pieces per voxel
 #pragma unroll
-    for (int j = 0; j < 2 * G; ++j) {
+    for (int j = 0; j < M * G / 4; ++j) {
       const int q = lane + 64 * j, vl = q / G, cg = q % G;
       const int x = x0 + (vl & 15), y = y0 + (vl >> 4);
       if (x < d.nx && y < d.ny && z < d.nz)
-        *reinterpret_cast<u32x4*>(Y + ((long)x + (long)d.nx * (y + (long)d.ny * z)) * ys + yo + 8 * cg) =
-            *reinterpret_cast<const u32x4*>(stg + vl * COUT + 8 * cg);
+        *reinterpret_cast<u32x4*>(Y + ((long)x + (long)d.nx * (y + (long)d.ny * z)) * ys + yo + g0 + 8 * cg) =
+            *reinterpret_cast<const u32x4*>(stg + vl * CB + 8 * cg);
     }
   }
 }
 
-// First layer at inference: the four FP32 feature channels (channel-first,
-// feat[c nv + v]) are converted to bfloat16 while staged in LDS (8 bytes per
-// halo voxel), and K runs over (tap, channel) compactly, k = 4 tap + ci with
+// First layer at inference, from the four feature channels in bfloat16 (8 bytes
+// per voxel: k_pack_input), and K runs over (tap, channel) compactly, k = 4 tap + ci with
 // 108 real entries padded to 128: four K = 32 steps instead of fourteen.
-// Wc is [16 outputs][128 k].  Output: + bias, ReLU, bfloat16, channel stride ys.
-__global__ void __launch_bounds__(256) k_conv_in(VDims d, const float* __restrict__ feat,
+// Wc is [16 outputs][128 k].  Output: + bias, ReLU, bfloat16, channel stride ys,
+// and its 2x2x2 averages P.
+template <int M>
+__global__ void __launch_bounds__(256) k_conv_in(VDims d, const u32x2* __restrict__ xin,
                                                  const uint16_t* __restrict__ Wc, const float* __restrict__ bias,
-                                                 uint16_t* __restrict__ Y, int ys) {
+                                                 uint16_t* __restrict__ Y, int ys, uint16_t* __restrict__ P) {
+  using L = ConvTile<M>;
+  constexpr int kHX = L::HX, kHY = L::HY, kHV = L::HV;
   __shared__ u32x2 tile[kHV + 8];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, kg = lane >> 4;
-  const int x0 = blockIdx.x * kTX, y0 = blockIdx.y * kTY, z0 = blockIdx.z * kTZ;
-  const long nv = vox_count(d);
+  const int x0 = blockIdx.x * kTX, y0 = blockIdx.y * M, z0 = blockIdx.z * kTZ;
   for (int e = threadIdx.x; e < kHV; e += 256) {
     const int hx = e % kHX, hy = (e / kHX) % kHY, hz = e / (kHX * kHY);
     const int gx = x0 - 1 + hx, gy = y0 - 1 + hy, gz = z0 - 1 + hz;
     u32x2 val = {0u, 0u};
     if (gx >= 0 && gx < d.nx && gy >= 0 && gy < d.ny && gz >= 0 && gz < d.nz) {
-      const long v = (long)gx + (long)d.nx * (gy + (long)d.ny * gz);
-      val[0] = (uint32_t)f2bf(feat[v]) | ((uint32_t)f2bf(feat[nv + v]) << 16);
-      val[1] = (uint32_t)f2bf(feat[2 * nv + v]) | ((uint32_t)f2bf(feat[3 * nv + v]) << 16);
+      val = xin[(long)gx + (long)d.nx * (gy + (long)d.ny * gz)];
     }
     tile[e] = val;
   }
   __syncthreads();
-  f32x4 acc[4];
+  f32x4 acc[M];
 #pragma unroll
-  for (int m = 0; m < 4; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int m = 0; m < M; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int st = 0; st < 4; ++st) {
     const int t0 = 8 * st + 2 * kg, t1 = t0 + 1;   // this lane's two taps
@@ -452,7 +492,7 @@ __global__ void __launch_bounds__(256) k_conv_in(VDims d, const float* __restric
     const int o0 = ((t0 / 9) * kHY + (t0 / 3) % 3) * kHX + t0 % 3;
     const int o1 = ((t1 / 9) * kHY + (t1 / 3) % 3) * kHX + t1 % 3;
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
+    for (int m = 0; m < M; ++m) {
       const int base = (wave * kHY + m) * kHX + r;
       const u32x2 p0 = t0 < 27 ? tile[base + o0] : u32x2{0u, 0u};
       const u32x2 p1 = t1 < 27 ? tile[base + o1] : u32x2{0u, 0u};
@@ -461,23 +501,24 @@ __global__ void __launch_bounds__(256) k_conv_in(VDims d, const float* __restric
     }
   }
   // transpose through LDS and store 16-byte pieces (as in k_conv)
-  __shared__ uint16_t stg_all[4 * 64 * 16];
-  uint16_t* stg = stg_all + wave * 64 * 16;
+  __shared__ uint16_t stg_all[4 * 16 * M * 16];
+  uint16_t* stg = stg_all + wave * 16 * M * 16;
   const float bb = bias[r];
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
+  for (int m = 0; m < M; ++m)
 #pragma unroll
     for (int i = 0; i < 4; ++i) stg[(m * 16 + 4 * kg + i) * 16 + r] = f2bf(fmaxf(acc[m][i] + bb, 0.f));
   __syncthreads();
   const int z = z0 + wave;
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
+  for (int j = 0; j < M / 2; ++j) {
     const int q = lane + 64 * j, vl = q >> 1, cg = q & 1;
     const int x = x0 + (vl & 15), y = y0 + (vl >> 4);
     if (x < d.nx && y < d.ny && z < d.nz)
       *reinterpret_cast<u32x4*>(Y + ((long)x + (long)d.nx * (y + (long)d.ny * z)) * ys + 8 * cg) =
           *reinterpret_cast<const u32x4*>(stg + vl * 16 + 8 * cg);
   }
+  pool_tile<16, M>(stg_all, d, x0, y0, z0, 16, 0, P);
 }
 
 // Weight and bias gradient of a convolution,
@@ -845,6 +886,11 @@ __global__ void k_adam(float* __restrict__ th, const float* __restrict__ g, floa
 // ------------------------------------------------ features, loss, guess
 // four input channels (channel-first FP32): rhs h^2 rho_w / P0, the
 // log-density fraction, p_prev / P0 and the residual (b - A p_prev) h^2 rho_w / P0
+// (PACK: as k_pack_input leaves them)
+__device__ __forceinline__ u32x2 pack4(float a, float b, float c, float d) {
+  return u32x2{(uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16), (uint32_t)f2bf(c) | ((uint32_t)f2bf(d) << 16)};
+}
+template <bool PACK>
 __global__ void k_features(long nv, double s, double lr_w, double inv_lr, double inv_P0,
                            const double* __restrict__ b, const double* __restrict__ rho,
                            const double* __restrict__ pprev, const double* __restrict__ Ap,
@@ -852,10 +898,24 @@ __global__ void k_features(long nv, double s, double lr_w, double inv_lr, double
   const long v = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= nv) return;
   const double bb = b[v];
-  feat[v] = (float)(bb * s);
-  feat[nv + v] = (float)((log(rho[v]) - lr_w) * inv_lr);
-  feat[2 * nv + v] = (float)(pprev[v] * inv_P0);
-  feat[3 * nv + v] = (float)((bb - Ap[v]) * s);
+  const float f0 = (float)(bb * s), f1 = (float)((log(rho[v]) - lr_w) * inv_lr);
+  const float f2 = (float)(pprev[v] * inv_P0), f3 = (float)((bb - Ap[v]) * s);
+  if (PACK) {
+    reinterpret_cast<u32x2*>(feat)[v] = pack4(f0, f1, f2, f3);
+    return;
+  }
+  feat[v] = f0;
+  feat[nv + v] = f1;
+  feat[2 * nv + v] = f2;
+  feat[3 * nv + v] = f3;
+}
+
+// channel-first FP32 features -> bfloat16, the four channels of a voxel together
+// (the inference input: the first layer reads a voxel once per tile and halo,
+// 2.5 times, which at 256 x 128 x 128 cost it 82 us from the FP32 planes)
+__global__ void k_pack_input(long nv, const float* __restrict__ feat, u32x2* __restrict__ xin) {
+  const long v = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (v < nv) xin[v] = pack4(feat[v], feat[nv + v], feat[2 * nv + v], feat[3 * nv + v]);
 }
 
 // channel-first FP32 features -> channels-last bfloat16 input, padded to 16
@@ -1173,22 +1233,55 @@ ns_status nfail(ns_net* N, ns_status s, const char* msg) {
   return s;
 }
 
-template <int CIN, int COUT, int EPI>
-void conv(const ns_net* N, VDims d, const uint16_t* XA, int sa, int ca, const uint16_t* XB, int sb,
-          const uint16_t* W, const float* bias, uint16_t* Y, int ys, int yo, const float* hw = nullptr,
-          const float* hb = nullptr, float* delta = nullptr) {
-  const dim3 grid((d.nx + kTX - 1) / kTX, (d.ny + kTY - 1) / kTY, (d.nz + kTZ - 1) / kTZ);
-  hipLaunchKernelGGL((k_conv<CIN, COUT, EPI>), grid, dim3(256), 0, N->st, d, XA, sa, ca, XB, sb, W, bias, Y, ys,
-                     yo, hw, hb, delta);
+// Where a level has fewer than 128 tiles of every output channel, tiles of two rows
+// and 16 channels: 64 x 32 x 32 inference, 32 -> 64 channels on 4 blocks 13.0
+// us, on 32 6.2; 96 -> 32 on 16 blocks 27.7 us, on 128 14.4.  With 256 tiles
+// the smaller ones lose (the same grid's 48 -> 16 layer 10.0 us, 12.0 so).
+inline bool few_blocks(const dim3& g) { return (long)g.x * g.y * g.z < 128; }
+// Where tiles of eight rows leave four blocks per compute unit, the layers of 16
+// output channels take them: a row's fragment feeds one MFMA there, and eight of
+// them per tap pair cover the LDS latency that four do not (256 x 128 x 128: 48 ->
+// 16 channels 295 -> 245 us; 96 x 64 x 48, on 576 blocks, 80 us in all against 82)
+inline bool many_blocks(const VDims& d) {
+  return (long)((d.nx + kTX - 1) / kTX) * ((d.ny + 7) / 8) * ((d.nz + kTZ - 1) / kTZ) >= 1024;
 }
 
-template <int CIN, int COUT, int EPI>
+template <int CIN, int COUT, int EPI, bool POOL = false>
+void conv(const ns_net* N, VDims d, const uint16_t* XA, int sa, int ca, const uint16_t* XB, int sb,
+          const uint16_t* W, const float* bias, uint16_t* Y, int ys, int yo, const float* hw = nullptr,
+          const float* hb = nullptr, float* delta = nullptr, float* delta2 = nullptr, uint16_t* P = nullptr) {
+  constexpr int NT = COUT / 16;
+  dim3 grid((d.nx + kTX - 1) / kTX, (d.ny + kTY - 1) / kTY, (d.nz + kTZ - 1) / kTZ);
+  if (EPI == 2 && many_blocks(d)) {
+    grid.y = (d.ny + 7) / 8;
+    hipLaunchKernelGGL((k_conv<CIN, COUT, EPI, EPI == 2 ? 8 : kTY, NT, POOL>), grid, dim3(256), 0, N->st, d, XA, sa, ca,
+                       XB, sb, W, bias, Y, ys, yo, hw, hb, delta, delta2, P);
+    return;
+  }
+  if (!few_blocks(grid)) {
+    hipLaunchKernelGGL((k_conv<CIN, COUT, EPI, kTY, NT, POOL>), grid, dim3(256), 0, N->st, d, XA, sa, ca, XB, sb, W, bias,
+                       Y, ys, yo, hw, hb, delta, delta2, P);
+    return;
+  }
+  grid.x *= NT;
+  grid.y = (d.ny + 1) / 2;
+  hipLaunchKernelGGL((k_conv<CIN, COUT, EPI, 2, 1, POOL>), grid, dim3(256), 0, N->st, d, XA, sa, ca, XB, sb, W, bias, Y,
+                     ys, yo, hw, hb, delta, delta2, P);
+}
+
+template <int CIN, int COUT>
 void conv_cm(const ns_net* N, VDims d, const uint16_t* XA, int sa, int ca, const uint16_t* XB, int sb,
-             const uint16_t* W, const float* bias, uint16_t* Y, int ys, int yo, const float* hw = nullptr,
-             const float* hb = nullptr, float* delta = nullptr) {
-  const dim3 grid((d.nx + kCX - 1) / kCX, (d.ny + kCY - 1) / kCY, (d.nz + kCZ - 1) / kCZ);
-  hipLaunchKernelGGL((k_conv_cm<CIN, COUT, EPI>), grid, dim3(256), 0, N->st, d, XA, sa, ca, XB, sb, W, bias, Y,
-                     ys, yo, hw, hb, delta);
+             const uint16_t* W, const float* bias, uint16_t* Y, int ys, int yo) {
+  constexpr int NT = COUT / 16;
+  dim3 grid((d.nx + kCX - 1) / kCX, (d.ny + kCY - 1) / kCY, (d.nz + kCZ - 1) / kCZ);
+  if (!few_blocks(grid)) {
+    hipLaunchKernelGGL((k_conv_cm<CIN, COUT, kCY, NT>), grid, dim3(256), 0, N->st, d, XA, sa, ca, XB, sb, W, bias, Y, ys,
+                       yo);
+    return;
+  }
+  grid.x *= NT;
+  grid.y = (d.ny + 1) / 2;
+  hipLaunchKernelGGL((k_conv_cm<CIN, COUT, 2, 1>), grid, dim3(256), 0, N->st, d, XA, sa, ca, XB, sb, W, bias, Y, ys, yo);
 }
 
 // bf16 copies (forward and flipped-transposed) of the FP32 master weights
@@ -1227,30 +1320,32 @@ void forward_train(ns_net* N) {
 // Inference forward: the decoder convolutions read the skip tensor and the
 // coarse tensor directly (no upsampled copies), and the head is fused into
 // the last convolution, so a5 is never stored.
-// The input is the FP32 feature tensor in N->feat.
-void forward_infer(ns_net* N) {
+// The input is the packed features in N->feat; delta2, if given, receives a copy
+// of the result.
+void forward_infer(ns_net* N, float* delta2) {
   const float* th = N->theta;
   uint16_t* a1 = N->C1;   // dense [v0][16] in the concatenation buffer's memory
   uint16_t* a2 = N->C2;   // dense [v1][32]
   {
     const VDims d = N->res0;
-    const dim3 grid((d.nx + kTX - 1) / kTX, (d.ny + kTY - 1) / kTY, (d.nz + kTZ - 1) / kTZ);
-    hipLaunchKernelGGL(k_conv_in, grid, dim3(256), 0, N->st, d, N->feat, N->wc0, th + N->ob[0], a1, 16);
+    const bool many = many_blocks(d);
+    const int rows = many ? 8 : kTY;
+    const dim3 grid((d.nx + kTX - 1) / kTX, (d.ny + rows - 1) / rows, (d.nz + kTZ - 1) / kTZ);
+    hipLaunchKernelGGL(many ? k_conv_in<8> : k_conv_in<kTY>, grid, dim3(256), 0, N->st, d,
+                       reinterpret_cast<const u32x2*>(N->feat), N->wc0, th + N->ob[0], a1, 16, N->p1);
   }
-  hipLaunchKernelGGL(k_pool, g1(N->v1 * 2), dim3(256), 0, N->st, N->res0, a1, 16, 0, 16, N->p1);
-  conv<16, 32, 0>(N, N->res1, N->p1, 16, 16, nullptr, 0, N->wf[1], th + N->ob[1], a2, 32, 0);
-  hipLaunchKernelGGL(k_pool, g1(N->v2 * 4), dim3(256), 0, N->st, N->res1, a2, 32, 0, 32, N->p2);
+  conv<16, 32, 0, true>(N, N->res1, N->p1, 16, 16, nullptr, 0, N->wf[1], th + N->ob[1], a2, 32, 0, nullptr, nullptr,
+                        nullptr, nullptr, N->p2);
   conv<32, 64, 0>(N, N->res2, N->p2, 32, 32, nullptr, 0, N->wf[2], th + N->ob[2], N->a3, 64, 0);
-  conv_cm<96, 32, 0>(N, N->res1, a2, 32, 32, N->a3, 64, N->wf[3], th + N->ob[3], N->a4, 32, 0);
+  conv_cm<96, 32>(N, N->res1, a2, 32, 32, N->a3, 64, N->wf[3], th + N->ob[3], N->a4, 32, 0);
   conv<48, 16, 2>(N, N->res0, a1, 16, 16, N->a4, 32, N->wf[4], th + N->ob[4], nullptr, 16, 0, th + N->ohw,
-                  th + N->ohb, N->delta);
+                  th + N->ohb, N->delta, delta2);
 }
 
-void forward(ns_net* N) {
-  if (N->training)
-    forward_train(N);
-  else
-    forward_infer(N);
+void forward(ns_net* N, float* delta2 = nullptr) {
+  if (!N->training) return forward_infer(N, delta2);
+  forward_train(N);
+  if (delta2) (void)hipMemcpyAsync(delta2, N->delta, N->v0 * sizeof(float), hipMemcpyDeviceToDevice, N->st);
 }
 
 template <int CIN, int COUT>
@@ -1413,17 +1508,14 @@ ns_status ns_net_set_input(ns_net* N, const float* feat4) {
   if (!N || !feat4) return NS_EINVAL;
   if (N->training)
     hipLaunchKernelGGL(k_set_input, g1(N->v0), dim3(256), 0, N->st, N->v0, feat4, N->x0);
-  else if (hipMemcpyAsync(N->feat, feat4, 4 * N->v0 * sizeof(float), hipMemcpyDeviceToDevice, N->st) != hipSuccess)
-    return nfail(N, NS_EHIP, "copy failed");
+  else
+    hipLaunchKernelGGL(k_pack_input, g1(N->v0), dim3(256), 0, N->st, N->v0, feat4, reinterpret_cast<u32x2*>(N->feat));
   return hipGetLastError() == hipSuccess ? NS_OK : nfail(N, NS_EHIP, "launch failed");
 }
 
 ns_status ns_net_forward(ns_net* N, float* delta_out) {
   if (!N) return NS_EINVAL;
-  forward(N);
-  if (delta_out)
-    if (hipMemcpyAsync(delta_out, N->delta, N->v0 * sizeof(float), hipMemcpyDeviceToDevice, N->st) != hipSuccess)
-      return nfail(N, NS_EHIP, "copy failed");
+  forward(N, delta_out);
   return hipGetLastError() == hipSuccess ? NS_OK : nfail(N, NS_EHIP, "launch failed");
 }
 
@@ -1465,8 +1557,8 @@ namespace nsk {
 void net_features(ns_net* N, const Dims& n, double h, double rho_w, double rho_a, double P0, const double* b,
                   const double* rho, const double* pprev, const double* Ap, float* feat, hipStream_t st) {
   const long nv = (long)n.nx * n.ny * n.nz;
-  (void)N;
-  hipLaunchKernelGGL(k_features, g1(nv), dim3(256), 0, st, nv, h * h * rho_w / P0, log(rho_w),
+  const bool pack = N && !N->training && feat == N->feat;
+  hipLaunchKernelGGL(pack ? k_features<true> : k_features<false>, g1(nv), dim3(256), 0, st, nv, h * h * rho_w / P0, log(rho_w),
                      1.0 / (log(rho_a) - log(rho_w)), 1.0 / P0, b, rho, pprev, Ap, feat);
 }
 
