@@ -189,13 +189,9 @@ __global__ void __launch_bounds__(256) k_conv(VDims d, const uint16_t* __restric
       if (e < 2 * kHV) tile[buf][(e & 1) * kPlane + (e >> 1)] = pre[i];
     }
   };
-  // weight fragment of tap pair p, output tile t, chunk c
-  const uint16_t* wl = W + (long)(g0 + r) * 27 * CIN + (long)(kg >> 1) * CIN + 8 * (kg & 1);
-  auto wfrag = [&](int p, int t, int c) -> bf16x8 {
-    const int tap = 2 * p + (kg >> 1);
-    return as_bf16x8(tap < 27 ? *reinterpret_cast<const u32x4*>(wl + (long)t * 16 * 27 * CIN + 2 * p * CIN + 16 * c)
-                              : zero);
-  };
+  // weight fragment of tap pair p, output tile t, chunk c (W in fragment order)
+  const u32x4* wl = reinterpret_cast<const u32x4*>(W) + (long)(g0 / 16) * NC * 14 * 64 + lane;
+  auto wfrag = [&](int p, int t, int c) -> bf16x8 { return as_bf16x8(wl[((t * NC + c) * 14 + p) * 64]); };
   const int lbase = (kg & 1) * kPlane + wave * kHY * kHX + r;   // this lane's A piece for tap 0, row 0
   f32x4 acc[M][NB];
 #pragma unroll
@@ -328,11 +324,11 @@ __global__ void __launch_bounds__(256) k_conv(VDims d, const uint16_t* __restric
 // 328 us against k_conv's 321, and for 32 -> 64 (an eighth of the voxels)
 // 23.5 against 21 us, so those stay on k_conv.  Its single-buffered 68 KB
 // tile leaves two blocks per compute unit; a chunk's staging is hidden only
-// by the other block.
+// by the other block, so the launch bound keeps the registers of two.
 constexpr int kCX = 16, kCY = 8, kCZ = 4;
 
 template <int CIN, int COUT, int M, int NB>
-__global__ void __launch_bounds__(256) k_conv_cm(VDims d, const uint16_t* __restrict__ XA, int sa, int ca,
+__global__ void __launch_bounds__(256, 2) k_conv_cm(VDims d, const uint16_t* __restrict__ XA, int sa, int ca,
                                                  const uint16_t* __restrict__ XB, int sb,
                                                  const uint16_t* __restrict__ W, const float* __restrict__ bias,
                                                  uint16_t* __restrict__ Y, int ys, int yo) {
@@ -353,11 +349,9 @@ __global__ void __launch_bounds__(256) k_conv_cm(VDims d, const uint16_t* __rest
   for (int m = 0; m < M; ++m)
 #pragma unroll
     for (int t = 0; t < NB; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // weight fragment: output column r of tile t, channels 32 c + 8 kg .. + 7 of tap
-  const uint16_t* wl = W + (long)(g0 + r) * 27 * CIN + 8 * kg;
-  auto wfrag = [&](int tap, int t, int c) -> bf16x8 {
-    return as_bf16x8(*reinterpret_cast<const u32x4*>(wl + (long)t * 16 * 27 * CIN + (long)tap * CIN + 32 * c));
-  };
+  // weight fragment: tile t's output columns, chunk c's 32 channels of tap
+  const u32x4* wl = reinterpret_cast<const u32x4*>(W) + (long)(g0 / 16) * NC * 27 * 64 + lane;
+  auto wfrag = [&](int tap, int t, int c) -> bf16x8 { return as_bf16x8(wl[((t * NC + c) * 27 + tap) * 64]); };
 #pragma unroll 1
   for (int c = 0; c < NC; ++c) {
     if (c > 0) __syncthreads();   // every wave is done with the previous chunk
@@ -460,7 +454,7 @@ __global__ void __launch_bounds__(256) k_conv_cm(VDims d, const uint16_t* __rest
 // First layer at inference, from the four feature channels in bfloat16 (8 bytes
 // per voxel: k_pack_input), and K runs over (tap, channel) compactly, k = 4 tap + ci with
 // 108 real entries padded to 128: four K = 32 steps instead of fourteen.
-// Wc is [16 outputs][128 k].  Output: + bias, ReLU, bfloat16, channel stride ys,
+// Wc holds the four steps' fragments.  Output: + bias, ReLU, bfloat16, channel stride ys,
 // and its 2x2x2 averages P.
 template <int M>
 __global__ void __launch_bounds__(256) k_conv_in(VDims d, const u32x2* __restrict__ xin,
@@ -488,7 +482,7 @@ __global__ void __launch_bounds__(256) k_conv_in(VDims d, const u32x2* __restric
 #pragma unroll
   for (int st = 0; st < 4; ++st) {
     const int t0 = 8 * st + 2 * kg, t1 = t0 + 1;   // this lane's two taps
-    const bf16x8 b = as_bf16x8(*reinterpret_cast<const u32x4*>(Wc + r * 128 + 32 * st + 8 * kg));
+    const bf16x8 b = as_bf16x8(reinterpret_cast<const u32x4*>(Wc)[64 * st + lane]);
     const int o0 = ((t0 / 9) * kHY + (t0 / 3) % 3) * kHX + t0 % 3;
     const int o1 = ((t1 / 9) * kHY + (t1 / 3) % 3) * kHX + t1 % 3;
 #pragma unroll
@@ -845,29 +839,53 @@ __global__ void k_skip_mask(VDims fine, const uint16_t* __restrict__ dC, int os,
   *reinterpret_cast<u32x4*>(d + v * C + 8 * g) = pack8(o);
 }
 
-// The bfloat16 copies of the master weights in one launch, layer
-// blockIdx.y: W as it is, and for the input gradient W' [ci][26 - tap][co] =
-// W[co][tap][ci]; beyond the five layers, the first layer's compact form
-// wc0[co][4 tap + ci].
+// The bfloat16 copies of the master weights in one launch, in the order the
+// convolutions' lanes read them: a fragment's 64 pieces of 8 channels (1 KB) are
+// consecutive.  From rows of 27 CIN channels a fragment touched 16 lines: 64 x
+// 32 x 32 inference 41.9 -> 35.9 us, 256 x 128 x 128 446 -> 420, a 128 x 64 x 64
+// training step 500 -> 475.  blockIdx.y: the layer l of W, then l of
+// W'[ci][26 - tap][co] = W[co][tap][ci] for the input gradient, and last the first
+// layer's compact form, k = 4 tap + ci.  A thread fills one piece.
+//   k_conv:    piece ((t NC + c) 14 + p) 64 + lane: output 16 t + lane % 16, tap
+//              2 p + lane / 32 (the 28th zero), inputs 16 c + 8 (lane / 16 % 2) ..
+//   k_conv_cm: piece ((t NC + c) 27 + tap) 64 + lane: inputs 32 c + 8 (lane / 16) ..
 struct WeightCopies {
   const float* w[5];
   uint16_t *wf[5], *wt[5], *wc0;
   int cin[5], cout[5];
+  int cm;   // the layer that k_conv_cm takes (-1: none)
 };
 __global__ void __launch_bounds__(256) k_weight_copies(WeightCopies W) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x, l = blockIdx.y;
-  if (l == 5) {
-    if (q >= 16 * 128) return;
-    const int co = q / 128, k = q % 128, tap = k / 4, ci = k % 4;
-    W.wc0[q] = tap < 27 ? f2bf(W.w[0][(co * 27 + tap) * 16 + ci]) : (uint16_t)0;
-    return;
+  const int q = blockIdx.x * blockDim.x + threadIdx.x, l = blockIdx.y % 5;
+  const int lane = q & 63, r = lane & 15, kg = lane >> 4;
+  u32x4 o = {0u, 0u, 0u, 0u};
+  uint16_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  uint16_t* out;
+  if (blockIdx.y == 10) {
+    if (q >= 4 * 64) return;
+    out = W.wc0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int k = 32 * (q >> 6) + 8 * kg + e;
+      if (k < 108) v[e] = f2bf(W.w[0][(r * 27 + k / 4) * 16 + k % 4]);
+    }
+  } else {
+    const bool back = blockIdx.y >= 5, cm = !back && l == W.cm;
+    const int cin = back ? W.cout[l] : W.cin[l], cout = back ? W.cin[l] : W.cout[l];
+    const int nc = cin / (cm ? 32 : 16), np = cm ? 27 : 14;
+    if (q >= cout / 16 * nc * np * 64) return;
+    out = back ? W.wt[l] : W.wf[l];
+    const int p = (q >> 6) % np, tc = (q >> 6) / np, c = tc % nc, co = 16 * (tc / nc) + r;
+    const int tap = cm ? p : 2 * p + (kg >> 1), ci = cm ? 32 * c + 8 * kg : 16 * c + 8 * (kg & 1);
+    if (tap < 27) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        v[e] = f2bf(back ? W.w[l][((ci + e) * 27 + 26 - tap) * cout + co] : W.w[l][(co * 27 + tap) * cin + ci + e]);
+    }
   }
-  const int cin = W.cin[l], cout = W.cout[l];
-  if (q >= cout * 27 * cin) return;
-  const uint16_t v = f2bf(W.w[l][q]);
-  W.wf[l][q] = v;
-  const int co = q / (27 * cin), r = q % (27 * cin), tap = r / cin, ci = r % cin;
-  W.wt[l][((size_t)ci * 27 + (26 - tap)) * cout + co] = v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = (uint32_t)v[2 * e] | ((uint32_t)v[2 * e + 1] << 16);
+  reinterpret_cast<u32x4*>(out)[q] = o;
 }
 
 // Adam with bias correction; padded (always-zero-gradient) entries stay put
@@ -1129,8 +1147,8 @@ size_t net_layout(ns_net* N, int nx, int ny, int nz, int training, char* base) {
   }
   uint16_t *wf[5], *wt[5];
   for (int l = 0; l < 5; ++l) {
-    wf[l] = cv.take<uint16_t>((size_t)kCout[l] * 27 * kCin[l]);
-    wt[l] = cv.take<uint16_t>((size_t)kCout[l] * 27 * kCin[l]);
+    wf[l] = cv.take<uint16_t>((size_t)kCout[l] * 28 * kCin[l]);
+    wt[l] = cv.take<uint16_t>((size_t)kCout[l] * 28 * kCin[l]);
   }
   uint16_t* wc0 = cv.take<uint16_t>(16 * 128);
   uint16_t* x0 = cv.take<uint16_t>(v0 * 16);
@@ -1287,17 +1305,18 @@ void conv_cm(const ns_net* N, VDims d, const uint16_t* XA, int sa, int ca, const
 // bf16 copies (forward and flipped-transposed) of the FP32 master weights
 void refresh_weights(ns_net* N) {
   WeightCopies W;
-  int most = 16 * 128;
+  int most = 4 * 64;
   for (int l = 0; l < 5; ++l) {
     W.w[l] = N->theta + N->ow[l];
     W.wf[l] = N->wf[l];
     W.wt[l] = N->wt[l];
     W.cin[l] = kCin[l];
     W.cout[l] = kCout[l];
-    most = std::max(most, kCout[l] * 27 * kCin[l]);
+    most = std::max(most, kCout[l] * 28 * kCin[l] / 8);
   }
   W.wc0 = N->wc0;
-  hipLaunchKernelGGL(k_weight_copies, dim3((most + 255) / 256, 6), dim3(256), 0, N->st, W);
+  W.cm = N->training ? -1 : 3;   // (training runs every layer on k_conv)
+  hipLaunchKernelGGL(k_weight_copies, dim3((most + 255) / 256, 11), dim3(256), 0, N->st, W);
 }
 
 // Training forward: every activation the backward pass reads is stored (a1 and
