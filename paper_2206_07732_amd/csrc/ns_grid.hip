@@ -9,6 +9,7 @@
 // velocity, zero for wall-normal velocity (whose faces hold 0).
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "ns_internal.h"
 
@@ -53,6 +54,58 @@ __device__ __forceinline__ double fv(const double* __restrict__ a, const Dims& n
   return a[i + mx * (j + my * k)];
 }
 
+// The values of two columns, i and i + 1, and their arithmetic: a lane that
+// takes both loads them with one 16-byte access, at any 8-byte alignment.  A
+// wavefront's access costs the address unit the same 16 clocks at 8 and at 16
+// bytes per lane, and that unit is what bounds a stencil of FP64 values.
+struct V2 {
+  double x, y;
+};
+struct __attribute__((packed, aligned(8))) V2Mem {
+  double x, y;
+};
+struct __attribute__((packed, aligned(4))) F2Mem {
+  float x, y;
+};
+__device__ __forceinline__ V2 operator+(V2 a, V2 b) { return {a.x + b.x, a.y + b.y}; }
+__device__ __forceinline__ V2 operator-(V2 a, V2 b) { return {a.x - b.x, a.y - b.y}; }
+__device__ __forceinline__ V2 operator*(V2 a, V2 b) { return {a.x * b.x, a.y * b.y}; }
+__device__ __forceinline__ V2 operator*(double a, V2 b) { return {a * b.x, a * b.y}; }
+__device__ __forceinline__ V2 operator*(V2 a, double b) { return {a.x * b, a.y * b}; }
+__device__ __forceinline__ void operator+=(V2& a, V2 b) { a.x += b.x, a.y += b.y; }
+// Columns i + O and i + O + 1, each clamped to [0, mx), of a row that starts at
+// `row` (0 <= i < mx, mx >= 2).  Where the row is the same for the wavefront the
+// load's base is a scalar and its offset is shared by every row.
+template <int O>
+__device__ __forceinline__ V2 pair_at(const double* __restrict__ a, int mx, int i, int row) {
+  const unsigned off = 8u * (unsigned)(O < 0 ? max(i + O, 0) : min(i + O, mx - 2));
+  const V2Mem m = *reinterpret_cast<const V2Mem*>(reinterpret_cast<const char*>(a + row) + off);
+  if (O < 0) return {m.x, i + O < 0 ? m.x : m.y};
+  return {i + O > mx - 2 ? m.y : m.x, m.y};
+}
+// What a sum holds so far is formed here: the compiler would sink a
+// direction's arithmetic to the end of the kernel, past the branches of the
+// limiters, and keep every direction's loads in registers for it.
+__device__ __forceinline__ void settle(double&) {}
+__device__ __forceinline__ void settle(V2& a) { asm volatile("" : "+v"(a.x), "+v"(a.y)); }
+// cv and fv at column i + O, of one column or of two
+template <typename T, int O>
+__device__ __forceinline__ T cvt(const double* __restrict__ a, const Dims& n, int i, int j, int k) {
+  if constexpr (std::is_same_v<T, V2>)
+    return pair_at<O>(a, n.nx, i, n.nx * (clampi(j, 0, n.ny - 1) + n.ny * clampi(k, 0, n.nz - 1)));
+  else
+    return cv(a, n, i + O, j, k);
+}
+template <int C, typename T, int O>
+__device__ __forceinline__ T fvt(const double* __restrict__ a, const Dims& n, int i, int j, int k) {
+  if constexpr (std::is_same_v<T, V2>) {
+    const int mx = n.nx + (C == 0), my = n.ny + (C == 1), mz = n.nz + (C == 2);
+    return pair_at<O>(a, mx, i, mx * (clampi(j, 0, my - 1) + my * clampi(k, 0, mz - 1)));
+  } else {
+    return fv<C>(a, n, i + O, j, k);
+  }
+}
+
 // Koren-limited upwind face value; up2 is the cell behind the upwind cell up,
 // dn the downwind cell.  Third order (kappa = 1/3) where smooth, first order
 // at extrema, total-variation diminishing.
@@ -72,6 +125,10 @@ __device__ __forceinline__ double koren(double up2, double up, double dn) {
 __device__ __forceinline__ double koren_face(double a, double mm, double m, double p, double pp) {
   const bool pos = a >= 0.0;
   return koren(pos ? mm : pp, pos ? m : p, pos ? p : m);
+}
+
+__device__ __forceinline__ V2 koren_face(V2 a, V2 mm, V2 m, V2 p, V2 pp) {
+  return {koren_face(a.x, mm.x, m.x, p.x, pp.x), koren_face(a.y, mm.y, m.y, p.y, pp.y)};
 }
 
 __device__ __forceinline__ double heaviside(double phi, double eps) {
@@ -575,25 +632,25 @@ __global__ void __launch_bounds__(256) k_props(Phys P, const double* __restrict_
 // mean of their four cell viscosities.  m1, p1: the face's neighbours along D;
 // dvp, dvm: du_D/dx_C on the two edges.  *a (if not null) receives the
 // magnitude of the coefficient of the face's own value.
-template <int C, int D>
-__device__ __forceinline__ double visc_stress(const double* __restrict__ mu, const Dims& n, int i, int j, int k,
-                                              double uf, double m1, double p1, double dvp, double dvm, double ih,
-                                              double* a) {
+template <int C, int D, typename T = double>
+__device__ __forceinline__ T visc_stress(const double* __restrict__ mu, const Dims& n, int i, int j, int k,
+                                              T uf, T m1, T p1, T dvp, T dvm, double ih,
+                                              T* a) {
   constexpr int ci = (C == 0), cj = (C == 1), ck = (C == 2);
   constexpr int di = (D == 0), dj = (D == 1), dk = (D == 2);
-  double tp, tm;
+  T tp, tm;
   if constexpr (C == D) {
-    const double mup = cv(mu, n, i, j, k), mum = cv(mu, n, i - ci, j - cj, k - ck);
+    const T mup = cvt<T, 0>(mu, n, i, j, k), mum = cvt<T, -ci>(mu, n, i, j - cj, k - ck);
     tp = 2.0 * mup * (p1 - uf) * ih;
     tm = 2.0 * mum * (uf - m1) * ih;
     if (a) *a = 2.0 * (mup + mum) * ih * ih;
   } else {
-    const double mep = 0.25 * (cv(mu, n, i - ci, j - cj, k - ck) + cv(mu, n, i, j, k) +
-                               cv(mu, n, i - ci + di, j - cj + dj, k - ck + dk) +
-                               cv(mu, n, i + di, j + dj, k + dk));
-    const double mem = 0.25 * (cv(mu, n, i - ci - di, j - cj - dj, k - ck - dk) +
-                               cv(mu, n, i - di, j - dj, k - dk) + cv(mu, n, i - ci, j - cj, k - ck) +
-                               cv(mu, n, i, j, k));
+    const T mep = 0.25 * (cvt<T, -ci>(mu, n, i, j - cj, k - ck) + cvt<T, 0>(mu, n, i, j, k) +
+                               cvt<T, -ci + di>(mu, n, i, j - cj + dj, k - ck + dk) +
+                               cvt<T, di>(mu, n, i, j + dj, k + dk));
+    const T mem = 0.25 * (cvt<T, -ci - di>(mu, n, i, j - cj - dj, k - ck - dk) +
+                               cvt<T, -di>(mu, n, i, j - dj, k - dk) + cvt<T, -ci>(mu, n, i, j - cj, k - ck) +
+                               cvt<T, 0>(mu, n, i, j, k));
     tp = mep * ((p1 - uf) * ih + dvp);
     tm = mem * ((uf - m1) * ih + dvm);
     if (a) *a = (mep + mem) * ih * ih;
@@ -605,54 +662,122 @@ __device__ __forceinline__ double visc_stress(const double* __restrict__ mu, con
 // form), viscous stress, and with CONS the consistent transport's mass flux
 // (Koren-limited upwind face density at t^n times the advecting velocity)
 // and the momentum it carries (times the same upwind velocity).
-template <int C, int D, bool CONS>
+template <int C, int D, bool CONS, typename T>
 __device__ __forceinline__ void mom_dir(const double* __restrict__ uc, const double* __restrict__ ud,
                                         const double* __restrict__ mu, const double* __restrict__ rho_n,
-                                        const Dims& n, int i, int j, int k, double uf, double ih, double& adv,
-                                        double& visc, double& conv, double& mflux) {
+                                        const Dims& n, int i, int j, int k, T uf, double ih, T& adv,
+                                        T& visc, T& conv, T& mflux) {
   constexpr int ci = (C == 0), cj = (C == 1), ck = (C == 2);
   constexpr int di = (D == 0), dj = (D == 1), dk = (D == 2);
-  const double m2 = fv<C>(uc, n, i - 2 * di, j - 2 * dj, k - 2 * dk);
-  const double m1 = fv<C>(uc, n, i - di, j - dj, k - dk);
-  const double p1 = fv<C>(uc, n, i + di, j + dj, k + dk);
-  const double p2 = fv<C>(uc, n, i + 2 * di, j + 2 * dj, k + 2 * dk);
-  double ap, am, dvp = 0.0, dvm = 0.0;
+  const T m2 = fvt<C, T, -2 * di>(uc, n, i, j - 2 * dj, k - 2 * dk);
+  const T m1 = fvt<C, T, -di>(uc, n, i, j - dj, k - dk);
+  const T p1 = fvt<C, T, di>(uc, n, i, j + dj, k + dk);
+  const T p2 = fvt<C, T, 2 * di>(uc, n, i, j + 2 * dj, k + 2 * dk);
+  T ap, am, dvp{}, dvm{};
   if constexpr (C == D) {
     ap = 0.5 * (uf + p1);
     am = 0.5 * (m1 + uf);
   } else {
     // transverse velocity on the two faces meeting the edge above / below
-    const double vpp = fv<D>(ud, n, i + di, j + dj, k + dk);
-    const double vpm = fv<D>(ud, n, i + di - ci, j + dj - cj, k + dk - ck);
-    const double vmp = fv<D>(ud, n, i, j, k);
-    const double vmm = fv<D>(ud, n, i - ci, j - cj, k - ck);
+    const T vpp = fvt<D, T, di>(ud, n, i, j + dj, k + dk);
+    const T vpm = fvt<D, T, di - ci>(ud, n, i, j + dj - cj, k + dk - ck);
+    const T vmp = fvt<D, T, 0>(ud, n, i, j, k);
+    const T vmm = fvt<D, T, -ci>(ud, n, i, j - cj, k - ck);
     ap = 0.5 * (vpm + vpp);
     am = 0.5 * (vmm + vmp);
     dvp = (vpp - vpm) * ih;
     dvm = (vmp - vmm) * ih;
   }
-  const double vp = koren_face(ap, m1, uf, p1, p2);
-  const double vm = koren_face(am, m2, m1, uf, p1);
-  adv += ap * (vp - uf) - am * (vm - uf);
+  const T vp = koren_face(ap, m1, uf, p1, p2);
+  const T vm = koren_face(am, m2, m1, uf, p1);
+  if constexpr (!CONS) adv += ap * (vp - uf) - am * (vm - uf);
   if constexpr (CONS) {
     // face density at t^n of the face o steps along D: mean of its two cells
-    auto rf = [&](int o) {
-      return 0.5 * (cv(rho_n, n, i - ci + o * di, j - cj + o * dj, k - ck + o * dk) +
-                    cv(rho_n, n, i + o * di, j + o * dj, k + o * dk));
+    auto rf = [&](auto oc) {
+      constexpr int o = decltype(oc)::value;
+      return 0.5 * (cvt<T, -ci + o * di>(rho_n, n, i, j - cj + o * dj, k - ck + o * dk) +
+                    cvt<T, o * di>(rho_n, n, i, j + o * dj, k + o * dk));
     };
-    const double rm2 = rf(-2), rm1 = rf(-1), r0 = rf(0), rp1 = rf(1), rp2 = rf(2);
-    const double mp = ap * koren_face(ap, rm1, r0, rp1, rp2);
-    const double mm = am * koren_face(am, rm2, rm1, r0, rp1);
+    const T rm2 = rf(std::integral_constant<int, -2>{}), rm1 = rf(std::integral_constant<int, -1>{});
+    const T r0 = rf(std::integral_constant<int, 0>{}), rp1 = rf(std::integral_constant<int, 1>{});
+    const T rp2 = rf(std::integral_constant<int, 2>{});
+    const T mp = ap * koren_face(ap, rm1, r0, rp1, rp2);
+    const T mm = am * koren_face(am, rm2, rm1, r0, rp1);
     conv += mp * vp - mm * vm;
     mflux += mp - mm;
+    settle(conv);
+    settle(mflux);
+  } else {
+    settle(adv);
   }
-  visc += visc_stress<C, D>(mu, n, i, j, k, uf, m1, p1, dvp, dvm, ih, nullptr);
+  visc += visc_stress<C, D, T>(mu, n, i, j, k, uf, m1, p1, dvp, dvm, ih, (T*)nullptr);
+  settle(visc);
 }
 
 // The predictor of component C.  CONS: the conservative form with
 // consistent mass/momentum transport, from the cell density rho_n at t^n:
 // (rb u* - rho^n_f u^n)/dt + conv/h = forces, rb = rho^n_f - dt mflux/h, and
 // beta from rb; otherwise the advective form with rho_f at t^{n+1}.
+// A wall's face f of it:
+template <int C>
+__device__ __forceinline__ void mom_wall(const Phys& P, int i, int k, unsigned f, double t1, double* __restrict__ out,
+                                         double* __restrict__ beta, float* __restrict__ betaf,
+                                         double* __restrict__ cn_rhs, double* __restrict__ cn_diag) {
+  // the inlet of a wave tank carries the generated wave's velocity
+  out[f] = (C == 0 && i == 0 && P.gen_len > 0.0) ? tank_vel(P, 0, 0.0, (k + 0.5) * P.h, t1) : 0.0;
+  beta[f] = 0.0;
+  betaf[f] = 0.0f;
+  if (cn_rhs) {
+    cn_rhs[f] = 0.0;
+    cn_diag[f] = 0.0;   // marks a face the Crank-Nicolson sweeps keep
+  }
+}
+// and any other, from its sums over the directions: advection and mass flux
+// (times h), viscous stress, momentum flux (times h); r0, rff, xf: the face's
+// density (CONS: at t^n), flowing density (C = 2) and solid fraction; damp: the
+// row's damping coefficient
+struct MomFace {
+  double u, beta, num, den;
+};
+template <int C, bool CONS>
+__device__ __forceinline__ MomFace mom_face(const Phys& P, double uf, double r0, double rff,
+                                            double xf, double adv, double visc, double conv, double mflux, double damp,
+                                            double ub, double dt, bool cn, double* __restrict__ flag) {
+  const double ih = 1.0 / P.h;
+  const double grav = (C == 2) ? -P.g * rff : 0.0;
+  const double pen = xf * P.inv_kp;
+  // Crank-Nicolson keeps half the viscous term at t^n on the right-hand side
+  // and writes the first iterate of its sweeps (the explicit value)
+  const double wv = cn ? 0.5 : 1.0;
+  MomFace m;
+  if constexpr (CONS) {
+    const double rb = r0 - dt * mflux * ih;
+    // a carried density at or below zero makes the projection operator
+    // indefinite: the step is past the transport's Courant bound
+    if (!(rb > 0.0)) *flag = 1.0;
+    m.num = r0 * uf / dt - conv * ih + wv * visc + grav + pen * ub;
+    m.den = rb / dt + pen + damp;
+    m.beta = 1.0 / (rb + P.pen_w * dt * pen);
+  } else {
+    m.num = r0 * (uf / dt - adv * ih) + wv * visc + grav + pen * ub;
+    m.den = r0 / dt + pen + damp;
+    m.beta = 1.0 / (r0 + P.pen_w * dt * pen);
+  }
+  m.u = cn ? (m.num + 0.5 * visc) / m.den : m.num / m.den;
+  return m;
+}
+// (the nearest body's heave velocity, at a z-face)
+template <int C>
+__device__ __forceinline__ double mom_heave(const Phys& P, int i, int j, int k, double t1) {
+  double ub = 0.0;
+  if (C == 2 && P.nb > 0) body_psi(P, (i + 0.5) * P.h, (j + 0.5) * P.h, k * P.h, t1, &ub);
+  return ub;
+}
+template <int C>
+__device__ __forceinline__ double mom_damp(const Phys& P, int k, double dt) {
+  return vort_coeff(P, (C == 2) ? k * P.h : (k + 0.5) * P.h, dt);   // -g u, implicit
+}
+
 template <int C, bool CONS>
 __global__ void __launch_bounds__(256) k_momentum(Phys P, const double* __restrict__ u,
                                                   const double* __restrict__ v,
@@ -676,14 +801,7 @@ __global__ void __launch_bounds__(256) k_momentum(Phys P, const double* __restri
   const size_t f = i + (size_t)mx * (j + (size_t)my * k);
   const bool wall = (C == 0) ? (i == 0 || i == n.nx) : (C == 1) ? (j == 0 || j == n.ny) : (k == 0);
   if (wall) {
-    // the inlet of a wave tank carries the generated wave's velocity
-    out[f] = (C == 0 && i == 0 && P.gen_len > 0.0) ? tank_vel(P, 0, 0.0, (k + 0.5) * P.h, t1) : 0.0;
-    beta[f] = 0.0;
-    betaf[f] = 0.0f;
-    if (cn_rhs) {
-      cn_rhs[f] = 0.0;
-      cn_diag[f] = 0.0;   // marks a face the Crank-Nicolson sweeps keep
-    }
+    mom_wall<C>(P, i, k, (unsigned)f, t1, out, beta, betaf, cn_rhs, cn_diag);
     return;
   }
   const double* uc = (C == 0) ? u : (C == 1) ? v : w;
@@ -693,65 +811,116 @@ __global__ void __launch_bounds__(256) k_momentum(Phys P, const double* __restri
   mom_dir<C, 0, CONS>(uc, u, mu, rho_n, n, i, j, k, uf, ih, adv, visc, conv, mflux);
   mom_dir<C, 1, CONS>(uc, v, mu, rho_n, n, i, j, k, uf, ih, adv, visc, conv, mflux);
   mom_dir<C, 2, CONS>(uc, w, mu, rho_n, n, i, j, k, uf, ih, adv, visc, conv, mflux);
-  adv *= ih;
-  const double rf = 0.5 * (cv(rho, n, i - ci, j - cj, k - ck) + cv(rho, n, i, j, k));
-  const double rff = 0.5 * (cv(rfl, n, i - ci, j - cj, k - ck) + cv(rfl, n, i, j, k));
+  const double r0 = CONS ? 0.5 * (cv(rho_n, n, i - ci, j - cj, k - ck) + cv(rho_n, n, i, j, k))
+                         : 0.5 * (cv(rho, n, i - ci, j - cj, k - ck) + cv(rho, n, i, j, k));
+  const double rff = C == 2 ? 0.5 * (cv(rfl, n, i - ci, j - cj, k - ck) + cv(rfl, n, i, j, k)) : 0.0;
   const double xf = 0.5 * (cv(chi, n, i - ci, j - cj, k - ck) + cv(chi, n, i, j, k));
-  double ub = 0.0;
-  if (C == 2 && P.nb > 0) body_psi(P, (i + 0.5) * P.h, (j + 0.5) * P.h, k * P.h, t1, &ub);
-  const double grav = (C == 2) ? -P.g * rff : 0.0;
-  const double pen = xf * P.inv_kp;
-  const double damp = vort_coeff(P, (C == 2) ? k * P.h : (k + 0.5) * P.h, dt);   // -g u, implicit
-  // Crank-Nicolson keeps half the viscous term at t^n on the right-hand side
-  // and writes the first iterate of its sweeps (the explicit value)
-  const double wv = cn_rhs ? 0.5 : 1.0;
-  if constexpr (CONS) {
-    const double r0 = 0.5 * (cv(rho_n, n, i - ci, j - cj, k - ck) + cv(rho_n, n, i, j, k));
-    const double rb = r0 - dt * mflux * ih;
-    // a carried density at or below zero makes the projection operator
-    // indefinite: the step is past the transport's Courant bound
-    if (!(rb > 0.0)) *flag = 1.0;
-    const double num = r0 * uf / dt - conv * ih + wv * visc + grav + pen * ub;
-    const double den = rb / dt + pen + damp;
-    out[f] = cn_rhs ? (num + 0.5 * visc) / den : num / den;
-    if (cn_rhs) {
-      cn_rhs[f] = num;
-      cn_diag[f] = den;
-    }
-    const double bt = 1.0 / (rb + P.pen_w * dt * pen);
-    beta[f] = bt;
-    betaf[f] = (float)bt;
-    return;
-  }
-  const double num = rf * (uf / dt - adv) + wv * visc + grav + pen * ub;
-  const double den = rf / dt + pen + damp;
-  out[f] = cn_rhs ? (num + 0.5 * visc) / den : num / den;
+  const MomFace m = mom_face<C, CONS>(P, uf, r0, rff, xf, adv, visc, conv, mflux, mom_damp<C>(P, k, dt),
+                                      mom_heave<C>(P, i, j, k, t1), dt, cn_rhs != nullptr, flag);
+  out[f] = m.u;
+  beta[f] = m.beta;
+  betaf[f] = (float)m.beta;
   if (cn_rhs) {
-    cn_rhs[f] = num;
-    cn_diag[f] = den;
+    cn_rhs[f] = m.num;
+    cn_diag[f] = m.den;
   }
-  const double bt = 1.0 / (rf + P.pen_w * dt * pen);
-  beta[f] = bt;
-  betaf[f] = (float)bt;
+}
+
+// The same for larger grids, two faces along x per lane (V2): half the accesses,
+// which bound the one-face form (55 to 59 of them per face, the address unit busy
+// 85% of the time), and the rows' arithmetic on scalars.  256 x 128 x 128, the
+// three components with consistent transport (3 x 56 us for the bytes at the
+// copy rate): 481 -> 352 us, advective 345 -> 272; 512 x 256 x 256 3.72 -> 2.55 ms.
+// (The last x-face of a row, a wall, is written with the one before it, so that
+// every component's row is nx wide.)
+template <int C, bool CONS>
+__global__ void __launch_bounds__(256, 4) k_momentum_pair(
+    Phys P, const double* __restrict__ u, const double* __restrict__ v, const double* __restrict__ w,
+    const double* __restrict__ rho, const double* __restrict__ rfl, const double* __restrict__ mu,
+    const double* __restrict__ chi, const double* __restrict__ rho_n, double dt, double t1, double* __restrict__ out,
+    double* __restrict__ beta, float* __restrict__ betaf, double* __restrict__ cn_rhs, double* __restrict__ cn_diag,
+    double* __restrict__ flag) {
+  const Dims n = P.n;
+  constexpr int ci = (C == 0), cj = (C == 1), ck = (C == 2);
+  const int mx = n.nx + ci, my = n.ny + cj, mz = n.nz + ck;
+  const Tile tl = xcd_tile();
+  // (a wavefront lies in one row)
+  const int i = 2 * (tl.x * 64 + threadIdx.x);
+  const int j = tl.y * blockDim.y + __builtin_amdgcn_readfirstlane(threadIdx.y);
+  const int k = tl.z * blockDim.z + __builtin_amdgcn_readfirstlane(threadIdx.z);
+  if (i >= n.nx || j >= my || k >= mz) return;
+  const unsigned f = (unsigned)(i + mx * (j + my * k));
+  const bool wall = (C == 1) ? (j == 0 || j == n.ny) : (C == 2) ? k == 0 : false;   // (the row is)
+  // (before the stencil, whose registers their library functions would add to)
+  const double damp = mom_damp<C>(P, k, dt);
+  const double ub0 = mom_heave<C>(P, i, j, k, t1), ub1 = mom_heave<C>(P, i + 1, j, k, t1);
+  __builtin_amdgcn_sched_barrier(0);
+  MomFace m[2];
+  if (wall) {
+    m[0] = m[1] = MomFace{0.0, 0.0, 0.0, 0.0};
+  } else {
+    const double* uc = (C == 0) ? u : (C == 1) ? v : w;
+    const V2 uf = fvt<C, V2, 0>(uc, n, i, j, k);
+    const double ih = 1.0 / P.h;
+    V2 adv{}, visc{}, conv{}, mflux{};
+    mom_dir<C, 0, CONS>(uc, u, mu, rho_n, n, i, j, k, uf, ih, adv, visc, conv, mflux);
+    mom_dir<C, 1, CONS>(uc, v, mu, rho_n, n, i, j, k, uf, ih, adv, visc, conv, mflux);
+    mom_dir<C, 2, CONS>(uc, w, mu, rho_n, n, i, j, k, uf, ih, adv, visc, conv, mflux);
+    auto mean = [&](const double* a) {
+      return 0.5 * (cvt<V2, -ci>(a, n, i, j - cj, k - ck) + cvt<V2, 0>(a, n, i, j, k));
+    };
+    const V2 r0 = mean(CONS ? rho_n : rho), xf = mean(chi);
+    const V2 rff = C == 2 ? mean(rfl) : V2{};
+    const bool cn = cn_rhs != nullptr;
+    // (a face that is a wall or past the row raises no flag)
+    const bool ok0 = C != 0 || i > 0, ok1 = i + 1 < n.nx;
+    m[0] = mom_face<C, CONS>(P, uf.x, ok0 ? r0.x : 1.0, rff.x, xf.x, adv.x, visc.x, conv.x, ok0 ? mflux.x : 0.0,
+                             damp, ub0, dt, cn, flag);
+    m[1] = mom_face<C, CONS>(P, uf.y, ok1 ? r0.y : 1.0, rff.y, xf.y, adv.y, visc.y, conv.y,
+                             ok1 ? mflux.y : 0.0, damp, ub1, dt, cn, flag);
+    if (C == 0 && i == 0)   // the inlet of a wave tank carries the generated wave's velocity
+      m[0] = MomFace{P.gen_len > 0.0 ? tank_vel(P, 0, 0.0, (k + 0.5) * P.h, t1) : 0.0, 0.0, 0.0, 0.0};
+  }
+  const bool two = i + 1 < n.nx;
+  if (two) {
+    *reinterpret_cast<V2Mem*>(out + f) = V2Mem{m[0].u, m[1].u};
+    *reinterpret_cast<V2Mem*>(beta + f) = V2Mem{m[0].beta, m[1].beta};
+    *reinterpret_cast<F2Mem*>(betaf + f) = F2Mem{(float)m[0].beta, (float)m[1].beta};
+    if (cn_rhs) {
+      *reinterpret_cast<V2Mem*>(cn_rhs + f) = V2Mem{m[0].num, m[1].num};
+      *reinterpret_cast<V2Mem*>(cn_diag + f) = V2Mem{m[0].den, m[1].den};
+    }
+  } else {
+    out[f] = m[0].u;
+    beta[f] = m[0].beta;
+    betaf[f] = (float)m[0].beta;
+    if (cn_rhs) {
+      cn_rhs[f] = m[0].num;
+      cn_diag[f] = m[0].den;
+    }
+  }
+  if (C == 0 && i + 2 >= n.nx) mom_wall<0>(P, n.nx, k, f + (two ? 2u : 1u), t1, out, beta, betaf, cn_rhs, cn_diag);
 }
 
 // Viscous stress of component C along D from the iterate, with its diagonal.
-template <int C, int D>
+template <int C, int D, typename T>
 __device__ __forceinline__ void sweep_dir(const double* __restrict__ uc, const double* __restrict__ ud,
                                           const double* __restrict__ mu, const Dims& n, int i, int j, int k,
-                                          double uf, double ih, double& L, double& a) {
+                                          T uf, double ih, T& L, T& a) {
   constexpr int ci = (C == 0), cj = (C == 1), ck = (C == 2);
   constexpr int di = (D == 0), dj = (D == 1), dk = (D == 2);
-  const double m1 = fv<C>(uc, n, i - di, j - dj, k - dk);
-  const double p1 = fv<C>(uc, n, i + di, j + dj, k + dk);
-  double dvp = 0.0, dvm = 0.0;
+  const T m1 = fvt<C, T, -di>(uc, n, i, j - dj, k - dk);
+  const T p1 = fvt<C, T, di>(uc, n, i, j + dj, k + dk);
+  T dvp{}, dvm{};
   if constexpr (C != D) {
-    dvp = (fv<D>(ud, n, i + di, j + dj, k + dk) - fv<D>(ud, n, i + di - ci, j + dj - cj, k + dk - ck)) * ih;
-    dvm = (fv<D>(ud, n, i, j, k) - fv<D>(ud, n, i - ci, j - cj, k - ck)) * ih;
+    dvp = (fvt<D, T, di>(ud, n, i, j + dj, k + dk) - fvt<D, T, di - ci>(ud, n, i, j + dj - cj, k + dk - ck)) * ih;
+    dvm = (fvt<D, T, 0>(ud, n, i, j, k) - fvt<D, T, -ci>(ud, n, i, j - cj, k - ck)) * ih;
   }
-  double ad;
-  L += visc_stress<C, D>(mu, n, i, j, k, uf, m1, p1, dvp, dvm, ih, &ad);
+  T ad;
+  L += visc_stress<C, D, T>(mu, n, i, j, k, uf, m1, p1, dvp, dvm, ih, &ad);
   a += ad;
+  settle(L);
+  settle(a);
 }
 
 // Largest value over a 256-thread block (64 x 4 or 64 x 1 x 4), two
@@ -780,7 +949,9 @@ __device__ __forceinline__ void block_max2(double& a, double& b) {
 // a_f the magnitude of L's diagonal; a face with D_f = 0 (a wall or the
 // inlet) keeps its value.  With part, the block's largest |u_new - u| and
 // largest |u_new| over the faces it updates go to part[2 lin], part[2 lin + 1].
-template <int C>
+// Larger grids take two faces along x per lane (T = V2), a row then nx wide: the
+// last x-face of a row, a wall, goes with the one before it.
+template <int C, typename T>
 __global__ void __launch_bounds__(256) k_cn_sweep(Phys P, const double* __restrict__ u,
                                                   const double* __restrict__ v,
                                                   const double* __restrict__ w,
@@ -788,38 +959,59 @@ __global__ void __launch_bounds__(256) k_cn_sweep(Phys P, const double* __restri
                                                   const double* __restrict__ rhs,
                                                   const double* __restrict__ diag, double* __restrict__ out,
                                                   double* __restrict__ part) {
+  constexpr bool PAIR = std::is_same_v<T, V2>;
   const Dims n = P.n;
   constexpr int ci = (C == 0), cj = (C == 1), ck = (C == 2);
   const int mx = n.nx + ci, my = n.ny + cj, mz = n.nz + ck;
   const Tile tl = xcd_tile();
-  const int i = tl.x * blockDim.x + threadIdx.x;
-  const int j = tl.y * blockDim.y + threadIdx.y;
-  const int k = tl.z * blockDim.z + threadIdx.z;
+  const int i = (PAIR ? 2 : 1) * (tl.x * 64 + threadIdx.x);
+  const int j = tl.y * blockDim.y + __builtin_amdgcn_readfirstlane(threadIdx.y);
+  const int k = tl.z * blockDim.z + __builtin_amdgcn_readfirstlane(threadIdx.z);
   double du = 0.0, um = 0.0;
-  if (i < mx && j < my && k < mz) {
-    const size_t f = i + (size_t)mx * (j + (size_t)my * k);
+  if (i < (PAIR ? n.nx : mx) && j < my && k < mz) {
+    const unsigned f = (unsigned)(i + mx * (j + my * k));
     const double* uc = (C == 0) ? u : (C == 1) ? v : w;
-    const double uf = uc[f];
-    const double dg = diag[f];
-    double nv = uf;
-    if (dg != 0.0) {
+    const bool two = PAIR && i + 1 < n.nx;
+    const T uf = fvt<C, T, 0>(uc, n, i, j, k);
+    double dg[2] = {diag[f], two ? diag[f + 1] : 0.0};
+    auto update = [&](double u0, double d0, double r0, double L, double a) {
+      const double nv = (r0 + 0.5 * (L + a * u0)) / (d0 + 0.5 * a);
+      if (d0 == 0.0) return u0;
+      du = fmax(du, fabs(nv - u0));
+      um = fmax(um, fabs(nv));
+      return nv;
+    };
+    if (dg[0] != 0.0 || dg[1] != 0.0) {
       const double ih = 1.0 / P.h;
-      double L = 0.0, a = 0.0;
-      sweep_dir<C, 0>(uc, u, mu, n, i, j, k, uf, ih, L, a);
-      sweep_dir<C, 1>(uc, v, mu, n, i, j, k, uf, ih, L, a);
-      sweep_dir<C, 2>(uc, w, mu, n, i, j, k, uf, ih, L, a);
-      nv = (rhs[f] + 0.5 * (L + a * uf)) / (dg + 0.5 * a);
-      du = fabs(nv - uf);
-      um = fabs(nv);
+      T L{}, a{};
+      sweep_dir<C, 0, T>(uc, u, mu, n, i, j, k, uf, ih, L, a);
+      sweep_dir<C, 1, T>(uc, v, mu, n, i, j, k, uf, ih, L, a);
+      sweep_dir<C, 2, T>(uc, w, mu, n, i, j, k, uf, ih, L, a);
+      if constexpr (PAIR) {
+        const double nx = update(uf.x, dg[0], rhs[f], L.x, a.x);
+        if (two)
+          *reinterpret_cast<V2Mem*>(out + f) = V2Mem{nx, update(uf.y, dg[1], rhs[f + 1], L.y, a.y)};
+        else
+          out[f] = nx;
+      } else {
+        out[f] = update(uf, dg[0], rhs[f], L, a);
+      }
+    } else if constexpr (PAIR) {
+      out[f] = uf.x;
+      if (two) out[f + 1] = uf.y;
+    } else {
+      out[f] = uf;
     }
-    out[f] = nv;
+    if (PAIR && C == 0 && i + 2 >= n.nx) {
+      const unsigned fw = f + (two ? 2u : 1u);
+      out[fw] = uc[fw];
+    }
   }
-  if (part) {   // uniform over the grid
-    block_max2(du, um);
-    if (threadIdx.x + threadIdx.y + threadIdx.z == 0) {
-      part[2 * (size_t)tl.lin] = du;
-      part[2 * (size_t)tl.lin + 1] = um;
-    }
+  if (!part) return;
+  block_max2(du, um);
+  if (threadIdx.x == 0 && threadIdx.y == 0 && threadIdx.z == 0) {
+    part[2 * (size_t)tl.lin] = du;
+    part[2 * (size_t)tl.lin + 1] = um;
   }
 }
 
@@ -1140,6 +1332,11 @@ __global__ void __launch_bounds__(1024) k_diag_finalize(const double* __restrict
 }  // namespace
 
 // ------------------------------------------------------------------ launchers
+// Where the predictor and its Crank-Nicolson sweeps take two faces along x per
+// lane: 64 x 40 x 40 (102400 cells) 23.2 us against 26.6 with two, 1024 x 1 x 208
+// (212992) 26.2 against 25.2, 96 x 48 x 56 40.8 against 35.8
+static bool pairs_pay(const Dims& n) { return n.nx >= 2 && (long)n.nx * n.ny * n.nz >= 3L << 16; }
+
 // Where a lane marches up a column: from 2^20 cells on; below it a cell per lane,
 // whose many short wavefronts fill the chip better (128 x 64 x 64: advection
 // and five pseudo-steps 36 us against 43; 200 x 72 x 104: 98 against 80)
@@ -1230,46 +1427,55 @@ void launch_momentum(const Phys& P, const double* u, const double* v, const doub
                      double* const* cn_diag, double* flag, hipStream_t st) {
   const Dims n = P.n;
   const Phys Pt = heave_at(P, t1);
-  Geo gx = geo3(n.nx + 1, n.ny, n.nz);
-  Geo gy = geo3(n.nx, n.ny + 1, n.nz);
-  Geo gz = geo3(n.nx, n.ny, n.nz + 1);
   double* r[3] = {nullptr, nullptr, nullptr};
   double* dg[3] = {nullptr, nullptr, nullptr};
   if (cn_rhs)
     for (int c = 0; c < 3; ++c) r[c] = cn_rhs[c], dg[c] = cn_diag[c];
-  if (rho_n) {
-    hipLaunchKernelGGL((k_momentum<0, true>), gx.grid, gx.block, 0, st, Pt, u, v, w, rho, rfl, mu, chi, rho_n, dt,
-                       t1, us, bx, bxf, r[0], dg[0], flag);
-    hipLaunchKernelGGL((k_momentum<1, true>), gy.grid, gy.block, 0, st, Pt, u, v, w, rho, rfl, mu, chi, rho_n, dt,
-                       t1, vs, by, byf, r[1], dg[1], flag);
-    hipLaunchKernelGGL((k_momentum<2, true>), gz.grid, gz.block, 0, st, Pt, u, v, w, rho, rfl, mu, chi, rho_n, dt,
-                       t1, ws, bz, bzf, r[2], dg[2], flag);
-    return;
-  }
-  hipLaunchKernelGGL((k_momentum<0, false>), gx.grid, gx.block, 0, st, Pt, u, v, w, rho, rfl, mu, chi, rho_n, dt,
-                     t1, us, bx, bxf, r[0], dg[0], flag);
-  hipLaunchKernelGGL((k_momentum<1, false>), gy.grid, gy.block, 0, st, Pt, u, v, w, rho, rfl, mu, chi, rho_n, dt,
-                     t1, vs, by, byf, r[1], dg[1], flag);
-  hipLaunchKernelGGL((k_momentum<2, false>), gz.grid, gz.block, 0, st, Pt, u, v, w, rho, rfl, mu, chi, rho_n, dt,
-                     t1, ws, bz, bzf, r[2], dg[2], flag);
+  double* const o[3] = {us, vs, ws};
+  double* const be[3] = {bx, by, bz};
+  float* const bf[3] = {bxf, byf, bzf};
+  auto comp = [&](auto c, auto cons) {
+    constexpr int C = decltype(c)::value;
+    constexpr bool CONS = decltype(cons)::value;
+    if (pairs_pay(n)) {
+      const Geo g = geo3((n.nx + 1) / 2, n.ny + (C == 1), n.nz + (C == 2));
+      hipLaunchKernelGGL((k_momentum_pair<C, CONS>), g.grid, g.block, 0, st, Pt, u, v, w, rho, rfl, mu, chi, rho_n, dt, t1,
+                         o[C], be[C], bf[C], r[C], dg[C], flag);
+      return;
+    }
+    const Geo g = geo3(n.nx + (C == 0), n.ny + (C == 1), n.nz + (C == 2));
+    hipLaunchKernelGGL((k_momentum<C, CONS>), g.grid, g.block, 0, st, Pt, u, v, w, rho, rfl, mu, chi, rho_n, dt, t1, o[C],
+                       be[C], bf[C], r[C], dg[C], flag);
+  };
+  auto all = [&](auto cons) {
+    comp(std::integral_constant<int, 0>{}, cons);
+    comp(std::integral_constant<int, 1>{}, cons);
+    comp(std::integral_constant<int, 2>{}, cons);
+  };
+  if (rho_n)
+    all(std::true_type{});
+  else
+    all(std::false_type{});
 }
 
 void launch_cn_sweep(const Phys& P, const double* u, const double* v, const double* w, const double* mu,
                      double* const* rhs, double* const* diag, double* uo, double* vo, double* wo, double* part,
                      double* out2, hipStream_t st) {
   const Dims n = P.n;
-  Geo gx = geo3(n.nx + 1, n.ny, n.nz);
-  Geo gy = geo3(n.nx, n.ny + 1, n.nz);
-  Geo gz = geo3(n.nx, n.ny, n.nz + 1);
-  const size_t bx = (size_t)gx.grid.x * gx.grid.y * gx.grid.z, by = (size_t)gy.grid.x * gy.grid.y * gy.grid.z;
-  const size_t bz = (size_t)gz.grid.x * gz.grid.y * gz.grid.z;
-  hipLaunchKernelGGL(k_cn_sweep<0>, gx.grid, gx.block, 0, st, P, u, v, w, mu, rhs[0], diag[0], uo, part);
-  hipLaunchKernelGGL(k_cn_sweep<1>, gy.grid, gy.block, 0, st, P, u, v, w, mu, rhs[1], diag[1], vo,
-                     part ? part + 2 * bx : nullptr);
-  hipLaunchKernelGGL(k_cn_sweep<2>, gz.grid, gz.block, 0, st, P, u, v, w, mu, rhs[2], diag[2], wo,
-                     part ? part + 2 * (bx + by) : nullptr);
+  size_t blocks = 0;
+  auto sweep = [&](auto c, double* o) {
+    constexpr int C = decltype(c)::value;
+    const bool pair = pairs_pay(n);
+    const Geo g = geo3(pair ? (n.nx + 1) / 2 : n.nx + (C == 0), n.ny + (C == 1), n.nz + (C == 2));
+    hipLaunchKernelGGL((pair ? k_cn_sweep<C, V2> : k_cn_sweep<C, double>), g.grid, g.block, 0, st, P, u, v, w, mu, rhs[C],
+                       diag[C], o, part ? part + 2 * blocks : nullptr);
+    blocks += (size_t)g.grid.x * g.grid.y * g.grid.z;
+  };
+  sweep(std::integral_constant<int, 0>{}, uo);
+  sweep(std::integral_constant<int, 1>{}, vo);
+  sweep(std::integral_constant<int, 2>{}, wo);
   if (part)
-    hipLaunchKernelGGL(k_max_finalize<2>, dim3(1), dim3(1024), 0, st, part, (int)(bx + by + bz), out2);
+    hipLaunchKernelGGL(k_max_finalize<2>, dim3(1), dim3(1024), 0, st, part, (int)blocks, out2);
 }
 
 int cn_part_blocks(const Dims& n) {
