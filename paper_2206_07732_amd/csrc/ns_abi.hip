@@ -71,8 +71,10 @@ struct ns_ctx {
     const void* c;
     int flag;
     hipGraphExec_t exec;
+    int ndot;
   } gs[16];           // recorded CG segments, keyed by kind and vectors
   int ngs;
+  int ndot;           // partials of <r, z> the last segment left unsummed (0: none, it is in scal)
   ns_net* net;        // learned guess (not owned)
   struct {
     double gain;      // CG iterations the learned guess saves over p_prev (trial average)
@@ -876,6 +878,7 @@ ns_status issue(ns_ctx* X, int kind, const void* a, const void* b, const void* c
       const auto& g = X->gs[q];
       if (g.kind == kind && g.a == a && g.b == b && g.c == c && g.flag == flag) {
         HIPCHK(X, hipGraphLaunch(g.exec, X->st));
+        X->ndot = g.ndot;
         return NS_OK;
       }
     }
@@ -895,7 +898,7 @@ ns_status issue(ns_ctx* X, int kind, const void* a, const void* b, const void* c
       }
       X->st = run;
       if (e == hipSuccess) {
-        X->gs[X->ngs++] = {kind, a, b, c, flag, exec};
+        X->gs[X->ngs++] = {kind, a, b, c, flag, exec, X->ndot};
         HIPCHK(X, hipGraphLaunch(exec, X->st));
         return NS_OK;
       }
@@ -991,17 +994,17 @@ ns_status pcg(ns_ctx* X, ns_stats* stats) {
   // segments: z = M r then rho = <r, z>; zn = M r then beta and rho;
   // then d = z + beta d, q = A d, alpha, x += alpha d, r -= alpha q, ||r||^2
   const bool split = use_split(X);   // the layout of r, z, d and q
+  const bool fold = !split && cs.hpart && cg_folds(n);   // beta and alpha are formed by the kernels that use them
   // split: the running solution, in the finest level's own b, which a cycle
   // on the split vectors leaves alone
   double* xs = split ? L0.b : nullptr;
   auto precond = [&](int kind, int mode, double* zz) {
     return issue(X, kind, zz, nullptr, nullptr, 0, [&] {
       // the product comes with the cycle's last kernel when it can give it
-      const int np = precond_launch(X, X->r, zz, true, split);
-      if (np > 0)
-        launch_finalize_dot(cs, np, mode, X->st);
-      else
-        launch_dot(n, X->r, zz, cs, mode, X->st);
+      int np = precond_launch(X, X->r, zz, true, split);
+      if (np > 0 && !fold) launch_finalize_dot(cs, np, mode, X->st);
+      if (np == 0) np = launch_dot(n, X->r, zz, cs, mode, X->st, fold);
+      X->ndot = fold ? np : 0;
     });
   };
   auto precond_rho = [&](double* zz) { return precond(SEG_PRECOND_RHO, FIN_RHO, zz); };
@@ -1015,8 +1018,9 @@ ns_status pcg(ns_ctx* X, ns_stats* stats) {
   bool xpend = false;
   auto dir_update = [&](const double* zz, const double* dold, double* dnew, int first) {
     launch_dir_spmv(n, h, L0.bx, L0.by, L0.bz, zz, dold, dnew, X->q, first, cs, X->st,
-                    X->timed_kernel == NS_TIME_SPMV ? &X->kt : nullptr, !xpend ? nullptr : split ? xs : x, face_tab(L0, L0.bx), split);
-    launch_cg_update(n, X->q, X->r, cs, X->st);
+                    X->timed_kernel == NS_TIME_SPMV ? &X->kt : nullptr, !xpend ? nullptr : split ? xs : x, face_tab(L0, L0.bx), split,
+                    X->ndot);
+    launch_cg_update(n, X->q, X->r, cs, X->st, fold);
     xpend = true;
     HIPCHK(X, hipGetLastError());
     return NS_OK;

@@ -152,7 +152,8 @@ enum ScalIdx {
   S_CNDU = 13,  // Crank-Nicolson: largest change of the last sweep
   S_CNU = 14,   //   and the largest |u*| it produced
   S_ZQ = 15,    // <z, q> of the last direction update
-  S_COUNT = 16
+  S_RHON = 16,  // <r, z> of the iteration under way, where the update's kernels sum it (cg_folds)
+  S_COUNT = 17
 };
 
 // Event pairs recorded with selected dispatches (profiling aid).
@@ -385,7 +386,10 @@ int launch_resid_norm(const Dims& n, double h, const double* bx, const double* b
                       const double* x, double* r, const CgScratch& cs, int mode, hipStream_t st,
                       const FaceTab<double>& ft = FaceTab<double>{}, bool split = false, double* xs = nullptr);
 // <r, z> (one layout for both), as rho (FIN_RHO) or for beta (FIN_BETA)
-void launch_dot(const Dims& n, const double* r, const double* z, const CgScratch& cs, int mode, hipStream_t st);
+bool cg_folds(const Dims& n);
+// returns the partials' count (fold: left unsummed)
+int launch_dot(const Dims& n, const double* r, const double* z, const CgScratch& cs, int mode, hipStream_t st,
+               bool fold);
 // the same from its partials, already in cs.partials
 void launch_finalize_dot(const CgScratch& cs, int nparts, int mode, hipStream_t st);
 // d = z + beta d_old and q = A d; with x, also the previous iteration's
@@ -393,9 +397,9 @@ void launch_finalize_dot(const CgScratch& cs, int nparts, int mode, hipStream_t 
 void launch_dir_spmv(const Dims& n, double h, const double* bx, const double* by, const double* bz,
                      const double* zn, const double* dold, double* dnew, double* q, int first,
                      const CgScratch& cs, hipStream_t st, KTimer* kt = nullptr, double* x = nullptr,
-                     const FaceTab<double>& ft = FaceTab<double>{}, bool split = false);
+                     const FaceTab<double>& ft = FaceTab<double>{}, bool split = false, int ndot = 0);
 // r -= alpha q and ||r||^2; x += alpha d is left pending
-void launch_cg_update(const Dims& n, const double* q, double* r, const CgScratch& cs, hipStream_t st);
+void launch_cg_update(const Dims& n, const double* q, double* r, const CgScratch& cs, hipStream_t st, bool fold);
 // the pending x += alpha d; with xs, x = xs + alpha d from colour-split xs and d
 void launch_x_update(const Dims& n, const double* d, double* x, const CgScratch& cs, hipStream_t st,
                      const double* xs = nullptr);

@@ -219,6 +219,31 @@ __device__ __forceinline__ void block_sum(double (&v)[NV]) {
   __syncthreads();
 }
 
+// the totals of np partials of NV values, in every lane: each wavefront sums
+// them all, lane l partials l, l + 64, ..
+template <int NV>
+__device__ __forceinline__ void wave_totals(const double* __restrict__ p, int np, double (&t)[NV]) {
+  const int lane = block_tid() & 63;
+#pragma unroll
+  for (int q = 0; q < NV; ++q) t[q] = 0.0;
+#pragma unroll 1
+  for (int base = lane; base < np; base += 4 * 64) {
+    double a[4][NV];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int q = 0; q < NV; ++q) a[u][q] = p[NV * min(base + 64 * u, np - 1) + q];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int q = 0; q < NV; ++q) t[q] += base + 64 * u < np ? a[u][q] : 0.0;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+    for (int q = 0; q < NV; ++q) t[q] += __shfl_xor(t[q], off, 64);
+}
+
 // write the block's NV sums to partials[NV * slot + q] (thread 0); slot is
 // the block's tile index, so the partials lie in tile order
 template <int NV>
@@ -2826,18 +2851,22 @@ __global__ void __launch_bounds__(256) k_dot_rho(Dims n, const double* __restric
 // already loaded here), which the vector update then leaves out.  A wavefront is one x-row of
 // 64 cells (blockDim.x == 64), so the x neighbours of zn come from the
 // adjacent lanes and only a row's end lanes load them; every lane takes part
-// in the shuffles (c is 0 outside the grid).
+// in the shuffles (c is 0 outside the grid).  ndot > 0: <r, zn> is still in
+// ndot partials (dotp), which every wavefront sums for itself, and beta follows
+// here; the first block leaves the sum in S_RHON.
 __global__ void __launch_bounds__(256) k_dir_spmv(Dims n, double ih2, const double* __restrict__ bx,
                                                   const double* __restrict__ by,
                                                   const double* __restrict__ bz,
                                                   const double* __restrict__ zn,
                                                   const double* __restrict__ dold,
                                                   double* __restrict__ dnew, double* __restrict__ q,
-                                                  int first, const double* __restrict__ scal,
+                                                  int first, double* __restrict__ scal,
                                                   double* __restrict__ partials, double* __restrict__ x,
-                                                  int xupd, FaceTab<double> ft) {
+                                                  int xupd, FaceTab<double> ft, const double* __restrict__ dotp,
+                                                  int ndot) {
   CELL_INDEX;
   double v[2] = {0.0, 0.0};
+  double beta = 0.0;
   // Every load is issued before the shuffles wait for zc: the faces and the
   // y and z neighbours through in-range indices (a lane outside the grid
   // reads around cell 0), the row-end lanes' x neighbour, and d_old, q_old
@@ -2861,6 +2890,15 @@ __global__ void __launch_bounds__(256) k_dir_spmv(Dims n, double ih2, const doub
   FaceLd<double> F;
   F.load(n, ft, bx, by, bz, ju, ku, fx, fy, c);
   __builtin_amdgcn_sched_barrier(0);
+  if (ndot > 0) {
+    double t[1];
+    wave_totals<1>(dotp, ndot, t);
+    const double rho = scal[S_RHO];
+    beta = (t[0] - (rho - scal[S_ALPHA] * scal[S_ZQ])) / rho;   // (as k_finalize)
+    if (tl.lin == 0 && block_tid() == 0) scal[S_RHON] = t[0];
+  } else if (!first) {
+    beta = scal[S_BETA];
+  }
   double cw, ce, cs, cn, cd, cu;
   F.get(n, ii, cw, ce, cs, cn, cd, cu);
   const double zl = __shfl_up(zc, 1, 64), zr = __shfl_down(zc, 1, 64);
@@ -2874,7 +2912,6 @@ __global__ void __launch_bounds__(256) k_dir_spmv(Dims n, double ih2, const doub
     const double qz = ih2 * acc;
     double dc = zc, qc = qz;
     if (!first) {
-      const double beta = scal[S_BETA];
       dc = zc + beta * dol;
       qc = qz + beta * qol;
     }
@@ -2902,9 +2939,10 @@ __global__ void __launch_bounds__(256) k_dir_spmv_split(Dims n, double ih2, cons
                                                         const double* __restrict__ zn,
                                                         const double* __restrict__ dold,
                                                         double* __restrict__ dnew, double* __restrict__ q, int first,
-                                                        const double* __restrict__ scal,
+                                                        double* __restrict__ scal,
                                                         double* __restrict__ partials, double* __restrict__ x,
-                                                        int xupd, FaceTab<double> ft) {
+                                                        int xupd, FaceTab<double> ft,
+                                                        const double*, int) {
   constexpr int V = 2;
   WIDE_INDEX;
   const int par = (j + k) & 1;
@@ -3030,14 +3068,32 @@ __global__ void __launch_bounds__(256) k_x_update_split(Dims n, const double* __
 }
 
 // r -= alpha q; ||r||^2 (the matching x += alpha d is applied by the next
-// direction update, or by k_x_update before x is read)
+// direction update, or by k_x_update before x is read).  ndq > 0: <d, q> and
+// <z, q> are still in ndq partials, which every wavefront sums for itself; the
+// first block then leaves what the finalizing kernels would have in scal.
 __global__ void __launch_bounds__(256) k_cg_update(Dims n, const double* __restrict__ q, double* __restrict__ r,
-                                                   const double* __restrict__ scal,
-                                                   double* __restrict__ partials) {
+                                                   double* __restrict__ scal, double* __restrict__ partials,
+                                                   const double* __restrict__ dqp, int ndq) {
   CELL_INDEX;
   double v[1] = {0.0};
+  const double r0 = inside ? r[c] : 0.0, q0 = inside ? q[c] : 0.0;
+  double alpha;
+  if (ndq > 0) {
+    double t[2];
+    wave_totals<2>(dqp, ndq, t);
+    const double rho = scal[S_RHON];
+    alpha = rho / t[0];
+    if (tl.lin == 0 && block_tid() == 0) {
+      scal[S_RHO] = rho;
+      scal[S_DQ] = t[0];
+      scal[S_ZQ] = t[1];
+      scal[S_ALPHA] = alpha;
+    }
+  } else {
+    alpha = scal[S_ALPHA];
+  }
   if (inside) {
-    const double rc = r[c] - scal[S_ALPHA] * q[c];
+    const double rc = r0 - alpha * q0;
     r[c] = rc;
     v[0] = rc * rc;
   }
@@ -3605,37 +3661,49 @@ int launch_resid_norm(const Dims& n, double h, const double* bx, const double* b
   return np;
 }
 
-void launch_dot(const Dims& n, const double* r, const double* z, const CgScratch& cs, int mode, hipStream_t st) {
+// Where the direction update and the vector update sum the partials before
+// them for themselves instead of waiting for a finalizing launch each: up to
+// 512 partials (131072 cells), which a wavefront sums in a microsecond against
+// the launch's 3.3 to 4 us (256 x 1 x 64 steps 2.85 -> 2.65 ms, 640 x 1 x 96 3.55 -> 3.32)
+bool cg_folds(const Dims& n) { return cg_blocks(n) <= 512; }
+
+int launch_dot(const Dims& n, const double* r, const double* z, const CgScratch& cs, int mode, hipStream_t st,
+               bool fold) {
   Geo g = geo3(n.nx, n.ny, n.nz);
   hipLaunchKernelGGL(k_dot_rho, g.grid, g.block, 0, st, n, r, z, cs.partials);
-  finalize(cs, (int)(g.grid.x * g.grid.y * g.grid.z), mode, st);
+  const int np = (int)(g.grid.x * g.grid.y * g.grid.z);
+  if (!fold) finalize(cs, np, mode, st);
+  return np;
 }
 
 void launch_dir_spmv(const Dims& n, double h, const double* bx, const double* by, const double* bz,
                      const double* zn, const double* dold, double* dnew, double* q, int first,
-                     const CgScratch& cs, hipStream_t st, KTimer* kt, double* x, const FaceTab<double>& ft, bool split) {
+                     const CgScratch& cs, hipStream_t st, KTimer* kt, double* x, const FaceTab<double>& ft, bool split,
+                     int ndot) {
   // blockDim.x == 64: a wavefront per x-line
   const Geo g = split ? Geo{wide_grid(n, 2), dim3(64, 4)} : geo3(n.nx, n.ny, n.nz);
-  const int xupd = x ? 1 : 0;
+  const int xupd = x ? 1 : 0, np = (int)(g.grid.x * g.grid.y * g.grid.z);
+  // (folded: its partials go behind those of <r, z>, which its blocks read)
+  double* part = ndot > 0 ? cs.partials + 2 * (size_t)np : cs.partials;
   auto kern = split ? k_dir_spmv_split : k_dir_spmv;
   if (kt && kt->n < kt->cap) {
     (void)hipStreamSynchronize(st);
-    hipExtLaunchKernelGGL(kern, g.grid, g.block, 0, st, kt->ev[2 * kt->n], kt->ev[2 * kt->n + 1], 0,
-                          n, 1.0 / (h * h), bx, by, bz, zn, dold, dnew, q, first, (const double*)cs.scal,
-                          cs.partials, x, xupd, ft);
+    hipExtLaunchKernelGGL(kern, g.grid, g.block, 0, st, kt->ev[2 * kt->n], kt->ev[2 * kt->n + 1], 0, n, 1.0 / (h * h), bx,
+                          by, bz, zn, dold, dnew, q, first, cs.scal, part, x, xupd, ft, (const double*)cs.partials, ndot);
     ++kt->n;
   } else {
-    hipLaunchKernelGGL(kern, g.grid, g.block, 0, st, n, 1.0 / (h * h), bx, by, bz, zn, dold, dnew, q,
-                       first, (const double*)cs.scal, cs.partials, x, xupd, ft);
+    hipLaunchKernelGGL(kern, g.grid, g.block, 0, st, n, 1.0 / (h * h), bx, by, bz, zn, dold, dnew, q, first, cs.scal, part,
+                       x, xupd, ft, (const double*)cs.partials, ndot);
   }
-  finalize(cs, (int)(g.grid.x * g.grid.y * g.grid.z), FIN_ALPHA, st);
+  if (ndot == 0) finalize(cs, np, FIN_ALPHA, st);
 }
 
-void launch_cg_update(const Dims& n, const double* q, double* r, const CgScratch& cs, hipStream_t st) {
+void launch_cg_update(const Dims& n, const double* q, double* r, const CgScratch& cs, hipStream_t st, bool fold) {
   Geo g = geo3(n.nx, n.ny, n.nz);
-  hipLaunchKernelGGL(k_cg_update, g.grid, g.block, 0, st, n, q, r, (const double*)cs.scal,
-                     cs.hpart ? cs.hpart : cs.partials);
-  if (!cs.hpart) finalize(cs, (int)(g.grid.x * g.grid.y * g.grid.z), FIN_RR, st);
+  const int np = (int)(g.grid.x * g.grid.y * g.grid.z);
+  hipLaunchKernelGGL(k_cg_update, g.grid, g.block, 0, st, n, q, r, cs.scal, cs.hpart ? cs.hpart : cs.partials,
+                     (const double*)(cs.partials + 2 * (size_t)np), fold ? np : 0);
+  if (!cs.hpart) finalize(cs, np, FIN_RR, st);
 }
 
 void launch_x_update(const Dims& n, const double* d, double* x, const CgScratch& cs, hipStream_t st, const double* xs) {
