@@ -600,6 +600,21 @@ void build_hierarchy(ns_ctx* X) {
   for (int l = 1; l < X->L; ++l) {
     const Level& F = X->lev[l - 1];
     const Level& C = X->lev[l];
+    // (the tail's levels are few enough for the chain's arrays)
+    if (l >= tail_start<T>(X) && l < X->L - 1 && (long)C.n.nx * C.n.ny * C.n.nz <= kCoarsenChain) {
+      CoarsenChain<T> D{};
+      for (int q = l - 1; q < X->L; ++q, ++D.nl) {
+        const Level& V = X->lev[q];
+        D.n[D.nl] = V.n;
+        for (int d = 0; d < 3; ++d) D.f[D.nl][d] = V.f[d];
+        D.bx[D.nl] = LV<T>::bx(V);
+        D.by[D.nl] = LV<T>::by(V);
+        D.bz[D.nl] = LV<T>::bz(V);
+        D.invd[D.nl] = LV<T>::invd(V);
+      }
+      launch_coarsen_chain<T>(D, X->st);
+      break;
+    }
     launch_coarsen_level<T>(F, LV<T>::bx(F), LV<T>::by(F), LV<T>::bz(F), C, LV<T>::bx(C), LV<T>::by(C),
                             LV<T>::bz(C), LV<T>::invd(C), l < tail_start<T>(X), X->st);
   }

@@ -592,6 +592,59 @@ __global__ void __launch_bounds__(64 * kRW) k_reinit_march(Phys P, const double*
   }
 }
 
+// All of a 2-D tank's pseudo-steps (up to kR2 of them) in one launch: a block
+// takes a tile of 64 x 16 cells with a ring of as many cells as there are steps,
+// which each step leaves one cell less of, in two LDS planes; the sign of
+// sigma0 is taken once.  A step by itself is a 3 us launch (256 x 64 to 640 x
+// 96): five of them 14.7 -> 8.9 us.
+constexpr int kR2 = 5, kR2X = 64, kR2Z = 16, kR2Row = kR2X + 2 * kR2, kR2N = kR2Row * (kR2Z + 2 * kR2);
+constexpr int kR2T = 512, kR2C = (kR2N + kR2T - 1) / kR2T;
+__global__ void __launch_bounds__(kR2T) k_reinit2d(Phys P, const double* __restrict__ s0, const double* __restrict__ cur,
+                                                   double* __restrict__ nxt, double dtau, int steps) {
+  __shared__ double lds[2][kR2N];
+  const int nx = P.n.nx, nz = P.n.nz;
+  const int x0 = blockIdx.x * kR2X - kR2, z0 = blockIdx.y * kR2Z - kR2;
+  const double h = P.h, ih = 1.0 / h;
+  double sg[kR2C], sc[kR2C];
+  int gi[kR2C], gk[kR2C];
+#pragma unroll
+  for (int q = 0; q < kR2C; ++q) {
+    const int e = min((int)threadIdx.x + q * kR2T, kR2N - 1);
+    gi[q] = x0 + e % kR2Row;
+    gk[q] = z0 + e / kR2Row;
+    const int c = clampi(gi[q], 0, nx - 1) + nx * clampi(gk[q], 0, nz - 1);
+    const double a = s0[c];
+    sc[q] = cur[c];
+    sg[q] = a / sqrt(a * a + h * h);
+  }
+#pragma unroll
+  for (int q = 0; q < kR2C; ++q)
+    if ((int)threadIdx.x + q * kR2T < kR2N) lds[0][threadIdx.x + q * kR2T] = sc[q];
+  __syncthreads();
+#pragma unroll 1
+  for (int t = 0; t < steps; ++t) {
+    const double* b = lds[t & 1];
+#pragma unroll
+    for (int q = 0; q < kR2C; ++q) {
+      // (the ring's own edge reads itself: what it holds is not used)
+      const int e = min((int)threadIdx.x + q * kR2T, kR2N - 1);
+      const int w = gi[q] > 0 && e > 0 ? e - 1 : e, ea = gi[q] < nx - 1 && e < kR2N - 1 ? e + 1 : e;
+      const int d = gk[q] > 0 && e >= kR2Row ? e - kR2Row : e, up = gk[q] < nz - 1 && e < kR2N - kR2Row ? e + kR2Row : e;
+      sc[q] = reinit_cell(sc[q], sg[q], b[w], b[ea], sc[q], sc[q], b[d], b[up], dtau, ih);
+    }
+#pragma unroll
+    for (int q = 0; q < kR2C; ++q)
+      if ((int)threadIdx.x + q * kR2T < kR2N) lds[1 - (t & 1)][threadIdx.x + q * kR2T] = sc[q];
+    __syncthreads();
+  }
+#pragma unroll
+  for (int q = 0; q < kR2C; ++q) {
+    const int i = gi[q] - x0 - kR2, k = gk[q] - z0 - kR2;
+    if ((int)threadIdx.x + q * kR2T < kR2N && i >= 0 && i < kR2X && k >= 0 && k < kR2Z && gi[q] < nx && gk[q] < nz)
+      nxt[gi[q] + nx * gk[q]] = sc[q];
+  }
+}
+
 __global__ void k_copy(const double* __restrict__ a, double* __restrict__ b, size_t n) {
   size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q < n) b[q] = a[q];
@@ -779,7 +832,7 @@ __device__ __forceinline__ double mom_damp(const Phys& P, int k, double dt) {
 }
 
 template <int C, bool CONS>
-__global__ void __launch_bounds__(256) k_momentum(Phys P, const double* __restrict__ u,
+__device__ __forceinline__ void mom_point(const Phys& P, int i, int j, int k, const double* __restrict__ u,
                                                   const double* __restrict__ v,
                                                   const double* __restrict__ w,
                                                   const double* __restrict__ rho,
@@ -793,10 +846,6 @@ __global__ void __launch_bounds__(256) k_momentum(Phys P, const double* __restri
   const Dims n = P.n;
   constexpr int ci = (C == 0), cj = (C == 1), ck = (C == 2);
   const int mx = n.nx + ci, my = n.ny + cj, mz = n.nz + ck;
-  const Tile tl = xcd_tile();
-  const int i = tl.x * blockDim.x + threadIdx.x;
-  const int j = tl.y * blockDim.y + threadIdx.y;
-  const int k = tl.z * blockDim.z + threadIdx.z;
   if (i >= mx || j >= my || k >= mz) return;
   const size_t f = i + (size_t)mx * (j + (size_t)my * k);
   const bool wall = (C == 0) ? (i == 0 || i == n.nx) : (C == 1) ? (j == 0 || j == n.ny) : (k == 0);
@@ -824,6 +873,35 @@ __global__ void __launch_bounds__(256) k_momentum(Phys P, const double* __restri
     cn_rhs[f] = m.num;
     cn_diag[f] = m.den;
   }
+}
+// The three components in one launch: the first third of the planes of blocks
+// takes the x-faces, then the y- and the z-faces
+struct MomOut {
+  double* u[3];
+  double* beta[3];
+  float* betaf[3];
+  double* rhs[3];
+  double* diag[3];
+};
+template <bool CONS>
+__global__ void __launch_bounds__(256) k_momentum(Phys P, const double* __restrict__ u, const double* __restrict__ v,
+                                                  const double* __restrict__ w, const double* __restrict__ rho,
+                                                  const double* __restrict__ rfl, const double* __restrict__ mu,
+                                                  const double* __restrict__ chi, const double* __restrict__ rho_n,
+                                                  double dt, double t1, MomOut O, double* __restrict__ flag) {
+  const int nb = gridDim.z / 3, C = blockIdx.z / nb;
+  const int i = blockIdx.x * 64 + threadIdx.x;
+  const int j = blockIdx.y * blockDim.y + __builtin_amdgcn_readfirstlane(threadIdx.y);
+  const int k = (blockIdx.z - C * nb) * blockDim.z + __builtin_amdgcn_readfirstlane(threadIdx.z);
+  if (C == 0)
+    mom_point<0, CONS>(P, i, j, k, u, v, w, rho, rfl, mu, chi, rho_n, dt, t1, O.u[0], O.beta[0], O.betaf[0], O.rhs[0],
+                       O.diag[0], flag);
+  else if (C == 1)
+    mom_point<1, CONS>(P, i, j, k, u, v, w, rho, rfl, mu, chi, rho_n, dt, t1, O.u[1], O.beta[1], O.betaf[1], O.rhs[1],
+                       O.diag[1], flag);
+  else
+    mom_point<2, CONS>(P, i, j, k, u, v, w, rho, rfl, mu, chi, rho_n, dt, t1, O.u[2], O.beta[2], O.betaf[2], O.rhs[2],
+                       O.diag[2], flag);
 }
 
 // The same for larger grids, two faces along x per lane (V2): half the accesses,
@@ -1088,33 +1166,34 @@ __global__ void __launch_bounds__(256) k_rhs(Phys P, const double* __restrict__ 
 }
 
 // u^{n+1} = u* - dt beta grad_h p on non-wall faces of component C
-template <int C>
-__global__ void __launch_bounds__(256) k_correct(Phys P, const double* __restrict__ us,
-                                                 const double* __restrict__ p,
-                                                 const double* __restrict__ beta, double dt,
-                                                 double* __restrict__ u) {
+// A thread takes a cell's three lower faces (and, at a far wall or the top, the
+// face beyond), so p is read once for the three components and the step has one
+// launch for them: 512 x 256 x 256 601 -> 499 us, 256 x 1 x 64 8.2 -> 3.4.
+__global__ void __launch_bounds__(256) k_correct(Phys P, const double* __restrict__ us, const double* __restrict__ vs,
+                                                 const double* __restrict__ ws, const double* __restrict__ p,
+                                                 const double* __restrict__ bx, const double* __restrict__ by,
+                                                 const double* __restrict__ bz, double dt, double* __restrict__ u,
+                                                 double* __restrict__ v, double* __restrict__ w) {
   const Dims n = P.n;
-  constexpr int ci = (C == 0), cj = (C == 1), ck = (C == 2);
-  const int mx = n.nx + ci, my = n.ny + cj, mz = n.nz + ck;
   const Tile tl = xcd_tile();
-  const int i = tl.x * blockDim.x + threadIdx.x;
-  const int j = tl.y * blockDim.y + threadIdx.y;
-  const int k = tl.z * blockDim.z + threadIdx.z;
-  if (i >= mx || j >= my || k >= mz) return;
-  const size_t f = i + (size_t)mx * (j + (size_t)my * k);
-  const bool wall = (C == 0) ? (i == 0 || i == n.nx) : (C == 1) ? (j == 0 || j == n.ny) : (k == 0);
-  if (wall) {
-    u[f] = (C == 0 && i == 0 && P.gen_len > 0.0) ? us[f] : 0.0;   // a tank's inlet keeps its wave
-    return;
-  }
+  const int i = tl.x * 64 + threadIdx.x;
+  const int j = tl.y * blockDim.y + __builtin_amdgcn_readfirstlane(threadIdx.y);
+  const int k = tl.z * blockDim.z + __builtin_amdgcn_readfirstlane(threadIdx.z);
+  if (i >= n.nx || j >= n.ny || k >= n.nz) return;
+  const unsigned sxy = (unsigned)(n.nx * n.ny);
+  const unsigned c = i + (unsigned)n.nx * (j + n.ny * k);
+  const unsigned fu = i + (unsigned)(n.nx + 1) * (j + n.ny * k);
+  const unsigned fv = i + (unsigned)n.nx * (j + (n.ny + 1) * k);
+  const double pc = p[c], px = p[i > 0 ? c - 1 : c], py = p[j > 0 ? c - n.nx : c], pz = p[k > 0 ? c - sxy : c];
+  const double u0 = us[fu], v0 = vs[fv], w0 = ws[c], b0 = bx[fu], b1 = by[fv], b2 = bz[c];
   const double ih = 1.0 / P.h;
-  double grad;
-  if (C == 2 && k == n.nz) {
-    grad = -cv(p, n, i, j, k - 1) * (2.0 * ih);   // p = 0 half a cell above
-  } else {
-    grad = (cv(p, n, i, j, k) - cv(p, n, i - ci, j - cj, k - ck)) * ih;
-  }
-  u[f] = us[f] - dt * beta[f] * grad;
+  // walls: zero, but for a tank's inlet, which keeps its wave
+  u[fu] = i > 0 ? u0 - dt * b0 * ((pc - px) * ih) : P.gen_len > 0.0 ? u0 : 0.0;
+  v[fv] = j > 0 ? v0 - dt * b1 * ((pc - py) * ih) : 0.0;
+  w[c] = k > 0 ? w0 - dt * b2 * ((pc - pz) * ih) : 0.0;
+  if (i == n.nx - 1) u[fu + 1] = 0.0;
+  if (j == n.ny - 1) v[fv + n.nx] = 0.0;
+  if (k == n.nz - 1) w[c + sxy] = ws[c + sxy] - dt * bz[c + sxy] * (-pc * (2.0 * ih));   // p = 0 half a cell above
 }
 
 // The wave tank's relaxation zones after a step: phi <- a phi + (1 - a) target
@@ -1341,7 +1420,8 @@ static bool pairs_pay(const Dims& n) { return n.nx >= 2 && (long)n.nx * n.ny * n
 // whose many short wavefronts fill the chip better (128 x 64 x 64: advection
 // and five pseudo-steps 36 us against 43; 200 x 72 x 104: 98 against 80)
 static bool marches(const Dims& n) { return n.ny >= 4 && (long)n.nx * n.ny * n.nz >= (1L << 20); }
-int reinit_steps(const Dims& n) { return marches(n) ? 2 : 1; }
+// Pseudo-steps per launch
+int reinit_steps(const Dims& n) { return n.ny == 1 ? kR2 : marches(n) ? 2 : 1; }
 
 // Planes of a march: the fewest rounds of blocks over the chip's 512 places
 // (two blocks per compute unit) times a block's planes, four more being spent
@@ -1381,7 +1461,10 @@ static void reinit_march(const Phys& P, const double* s0, const double* cur, dou
 void launch_reinit(const Phys& P, const double* s0, const double* cur, double* nxt, double dtau, int steps,
                    hipStream_t st) {
   const bool first = s0 == cur;   // (sigma0 is then read once)
-  if (reinit_steps(P.n) == 1) {
+  if (P.n.ny == 1) {
+    hipLaunchKernelGGL(k_reinit2d, dim3((P.n.nx + kR2X - 1) / kR2X, (P.n.nz + kR2Z - 1) / kR2Z), dim3(kR2T), 0, st, P, s0,
+                       cur, nxt, dtau, steps);
+  } else if (reinit_steps(P.n) == 1) {
     Geo g = geo3(P.n.nx, P.n.ny, P.n.nz);
     hipLaunchKernelGGL(k_reinit, g.grid, g.block, 0, st, P, s0, cur, nxt, dtau);
   } else if (steps == 2) {
@@ -1434,18 +1517,22 @@ void launch_momentum(const Phys& P, const double* u, const double* v, const doub
   double* const o[3] = {us, vs, ws};
   double* const be[3] = {bx, by, bz};
   float* const bf[3] = {bxf, byf, bzf};
+  if (!pairs_pay(n)) {
+    MomOut O;
+    for (int c = 0; c < 3; ++c) O.u[c] = o[c], O.beta[c] = be[c], O.betaf[c] = bf[c], O.rhs[c] = r[c], O.diag[c] = dg[c];
+    Geo g = geo3(n.nx + 1, n.ny + (n.ny > 1), n.nz + 1);
+    g.grid.y = (n.ny + 1 + g.block.y - 1) / g.block.y;   // (the y-faces' rows)
+    g.grid.z *= 3;
+    hipLaunchKernelGGL(rho_n ? k_momentum<true> : k_momentum<false>, g.grid, g.block, 0, st, Pt, u, v, w, rho, rfl, mu, chi,
+                       rho_n, dt, t1, O, flag);
+    return;
+  }
   auto comp = [&](auto c, auto cons) {
     constexpr int C = decltype(c)::value;
     constexpr bool CONS = decltype(cons)::value;
-    if (pairs_pay(n)) {
-      const Geo g = geo3((n.nx + 1) / 2, n.ny + (C == 1), n.nz + (C == 2));
-      hipLaunchKernelGGL((k_momentum_pair<C, CONS>), g.grid, g.block, 0, st, Pt, u, v, w, rho, rfl, mu, chi, rho_n, dt, t1,
-                         o[C], be[C], bf[C], r[C], dg[C], flag);
-      return;
-    }
-    const Geo g = geo3(n.nx + (C == 0), n.ny + (C == 1), n.nz + (C == 2));
-    hipLaunchKernelGGL((k_momentum<C, CONS>), g.grid, g.block, 0, st, Pt, u, v, w, rho, rfl, mu, chi, rho_n, dt, t1, o[C],
-                       be[C], bf[C], r[C], dg[C], flag);
+    const Geo g = geo3((n.nx + 1) / 2, n.ny + (C == 1), n.nz + (C == 2));
+    hipLaunchKernelGGL((k_momentum_pair<C, CONS>), g.grid, g.block, 0, st, Pt, u, v, w, rho, rfl, mu, chi, rho_n, dt, t1,
+                       o[C], be[C], bf[C], r[C], dg[C], flag);
   };
   auto all = [&](auto cons) {
     comp(std::integral_constant<int, 0>{}, cons);
@@ -1504,12 +1591,8 @@ void launch_correct(const Phys& P, const double* us, const double* vs, const dou
                     const double* p, const double* bx, const double* by, const double* bz, double dt,
                     double* u, double* v, double* w, hipStream_t st) {
   const Dims n = P.n;
-  Geo gx = geo3(n.nx + 1, n.ny, n.nz);
-  hipLaunchKernelGGL(k_correct<0>, gx.grid, gx.block, 0, st, P, us, p, bx, dt, u);
-  Geo gy = geo3(n.nx, n.ny + 1, n.nz);
-  hipLaunchKernelGGL(k_correct<1>, gy.grid, gy.block, 0, st, P, vs, p, by, dt, v);
-  Geo gz = geo3(n.nx, n.ny, n.nz + 1);
-  hipLaunchKernelGGL(k_correct<2>, gz.grid, gz.block, 0, st, P, ws, p, bz, dt, w);
+  const Geo g = geo3(n.nx, n.ny, n.nz);
+  hipLaunchKernelGGL(k_correct, g.grid, g.block, 0, st, P, us, vs, ws, p, bx, by, bz, dt, u, v, w);
 }
 
 int diag_blocks(const Phys& P) {

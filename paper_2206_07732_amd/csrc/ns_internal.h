@@ -208,6 +208,19 @@ struct TailDesc {
   int oet, oeb;
 };
 
+// Coarsening of consecutive small levels in one launch (entry 0 is the level the
+// first of them is formed from)
+constexpr int kCoarsenChain = 2048;
+template <typename T>
+struct CoarsenChain {
+  int nl;
+  Dims n[kTailMaxLevels + 1];
+  int f[kTailMaxLevels + 1][3];
+  T *bx[kTailMaxLevels + 1], *by[kTailMaxLevels + 1], *bz[kTailMaxLevels + 1], *invd[kTailMaxLevels + 1];
+};
+template <typename T>
+void launch_coarsen_chain(const CoarsenChain<T>& D, hipStream_t st);
+
 // LDS entries of such a level's correction: two planes of one entry per pair,
 // with room for a plane of pairs before, between and after them (neighbours
 // through a wall read it, at a face coefficient of zero)

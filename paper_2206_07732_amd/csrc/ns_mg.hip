@@ -1907,15 +1907,10 @@ __device__ __forceinline__ T coarse_face_sum(int fx, int fy, int fz, const FaceI
 // (split) or natural.  A face shared by two cells is formed by both with the
 // same arithmetic, and written once.
 template <typename T>
-__global__ void __launch_bounds__(256) k_coarsen_level(Dims nf, int fx, int fy, int fz, const T* __restrict__ fbx,
-                                                       const T* __restrict__ fby, const T* __restrict__ fbz,
-                                                       Dims nc, T* __restrict__ cbx, T* __restrict__ cby,
-                                                       T* __restrict__ cbz, int split, T* __restrict__ invd) {
-  const Tile tl = xcd_tile();
-  const int I = tl.x * blockDim.x + threadIdx.x;
-  const int J = tl.y * blockDim.y + threadIdx.y;
-  const int K = tl.z * blockDim.z + threadIdx.z;
-  if (I >= nc.nx || J >= nc.ny || K >= nc.nz) return;
+__device__ __forceinline__ void coarsen_cell(const Dims& nf, int fx, int fy, int fz, const T* __restrict__ fbx,
+                                             const T* __restrict__ fby, const T* __restrict__ fbz, const Dims& nc,
+                                             T* __restrict__ cbx, T* __restrict__ cby, T* __restrict__ cbz, bool split,
+                                             T* __restrict__ invd, int I, int J, int K) {
   const FaceIn<T> fw = coarse_face_load<T, 0>(nf, fx, fy, fz, fbx, I, J, K);
   const FaceIn<T> fe = coarse_face_load<T, 0>(nf, fx, fy, fz, fbx, I + 1, J, K);
   const FaceIn<T> fs = coarse_face_load<T, 1>(nf, fx, fy, fz, fby, I, J, K);
@@ -1939,7 +1934,38 @@ __global__ void __launch_bounds__(256) k_coarsen_level(Dims nf, int fx, int fy, 
   cbz[c] = bd;
   if (K == nc.nz - 1) cbz[c + sxy] = bu;
   const T diag = bw + be + bs + bn + bd + (K == nc.nz - 1 ? (T)2 * bu : bu);
-  invd[lidx(nc, split_geo(nc), split != 0, I, J, K)] = (T)1 / diag;
+  invd[lidx(nc, split_geo(nc), split, I, J, K)] = (T)1 / diag;
+}
+template <typename T>
+__global__ void __launch_bounds__(256) k_coarsen_level(Dims nf, int fx, int fy, int fz, const T* __restrict__ fbx,
+                                                       const T* __restrict__ fby, const T* __restrict__ fbz,
+                                                       Dims nc, T* __restrict__ cbx, T* __restrict__ cby,
+                                                       T* __restrict__ cbz, int split, T* __restrict__ invd) {
+  const Tile tl = xcd_tile();
+  const int I = tl.x * blockDim.x + threadIdx.x;
+  const int J = tl.y * blockDim.y + threadIdx.y;
+  const int K = tl.z * blockDim.z + threadIdx.z;
+  if (I >= nc.nx || J >= nc.ny || K >= nc.nz) return;
+  coarsen_cell<T>(nf, fx, fy, fz, fbx, fby, fbz, nc, cbx, cby, cbz, split != 0, invd, I, J, K);
+}
+// The small coarse levels (kCoarsenChain cells at most, all in the tail) one
+// after the other in one workgroup, each from the one before: a launch of 3.4 us
+// per level otherwise
+template <typename T>
+__global__ void __launch_bounds__(1024) k_coarsen_chain(CoarsenChain<T> D) {
+#pragma unroll 1
+  for (int l = 1; l < D.nl; ++l) {
+    const Dims nc = D.n[l];
+    const float inx = 1.0f / (float)nc.nx, iny = 1.0f / (float)nc.ny;
+#pragma unroll 1
+    for (int c = threadIdx.x; c < nc.nx * nc.ny * nc.nz; c += 1024) {
+      const int r = (int)(((float)c + 0.5f) * inx), K = (int)(((float)r + 0.5f) * iny);
+      coarsen_cell<T>(D.n[l - 1], D.f[l - 1][0], D.f[l - 1][1], D.f[l - 1][2], D.bx[l - 1], D.by[l - 1], D.bz[l - 1], nc,
+                      D.bx[l], D.by[l], D.bz[l], false, D.invd[l], c - r * nc.nx, r - K * nc.ny, K);
+    }
+    __threadfence_block();
+    __syncthreads();
+  }
 }
 
 // ------------------------------------------------------- coarse-level tail
@@ -3459,6 +3485,10 @@ void launch_invdiag(const Level& L, const T* bx, const T* by, const T* bz, T* in
 }
 
 template <typename T>
+void launch_coarsen_chain(const CoarsenChain<T>& D, hipStream_t st) {
+  hipLaunchKernelGGL(k_coarsen_chain<T>, dim3(1), dim3(1024), 0, st, D);
+}
+template <typename T>
 void launch_coarsen_level(const Level& F, const T* fbx, const T* fby, const T* fbz, const Level& C, T* cbx,
                           T* cby, T* cbz, T* invd, bool split, hipStream_t st) {
   Geo g = geo3(C.n.nx, C.n.ny, C.n.nz);
@@ -3748,6 +3778,7 @@ void launch_apply_A(const Dims& n, double h, const double* bx, const double* by,
   template void launch_fill<T>(T*, size_t, hipStream_t);                                              \
   template void launch_face_tables<T>(const Dims&, const T*, const T*, const T*, T*, T*, T*, hipStream_t); \
   template void launch_vcycle_tail<T>(const TailDesc<T>&, size_t, hipStream_t);                       \
+  template void launch_coarsen_chain<T>(const CoarsenChain<T>&, hipStream_t);                         \
   template void launch_tail_matrix<T>(const TailDesc<T>&, int, T*, hipStream_t);
 NSK_INST(double)
 NSK_INST(float)
