@@ -1361,10 +1361,11 @@ void forward_infer(ns_net* N, float* delta2) {
                   th + N->ohb, N->delta, delta2);
 }
 
-void forward(ns_net* N, float* delta2 = nullptr) {
-  if (!N->training) return forward_infer(N, delta2);
-  forward_train(N);
-  if (delta2) (void)hipMemcpyAsync(delta2, N->delta, N->v0 * sizeof(float), hipMemcpyDeviceToDevice, N->st);
+void forward(ns_net* N) {
+  if (N->training)
+    forward_train(N);
+  else
+    forward_infer(N, nullptr);
 }
 
 template <int CIN, int COUT>
@@ -1534,7 +1535,14 @@ ns_status ns_net_set_input(ns_net* N, const float* feat4) {
 
 ns_status ns_net_forward(ns_net* N, float* delta_out) {
   if (!N) return NS_EINVAL;
-  forward(N, delta_out);
+  if (!N->training) {
+    forward_infer(N, delta_out);
+  } else {
+    forward_train(N);
+    if (delta_out)
+      if (hipMemcpyAsync(delta_out, N->delta, N->v0 * sizeof(float), hipMemcpyDeviceToDevice, N->st) != hipSuccess)
+        return nfail(N, NS_EHIP, "copy failed");
+  }
   return hipGetLastError() == hipSuccess ? NS_OK : nfail(N, NS_EHIP, "launch failed");
 }
 
