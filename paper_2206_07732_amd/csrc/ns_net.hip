@@ -22,6 +22,7 @@
 #include <cstdint>
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "ns_internal.h"
@@ -36,11 +37,8 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);   // round to nearest, ties to even
-  return (uint16_t)(u >> 16);
-}
+// round to nearest, ties to even
+__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 struct VDims {
@@ -116,17 +114,40 @@ __device__ __forceinline__ void pool_tile(const uint16_t* stg, const VDims& d, i
   *reinterpret_cast<u32x4*>(P + ((long)gx + (long)(d.nx / 2) * (gy + (long)(d.ny / 2) * gz)) * ps + po + 8 * g) = o;
 }
 
-// the sum of the 16 lanes of a row (in the order of an exclusive-or butterfly)
-template <int N>
-__device__ __forceinline__ float ror16(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xF, 0xF, false));
+// lane r ^ X of a row of 16 lanes
+template <int X>
+__device__ __forceinline__ float xor16(float v) {
+  static_assert(X == 8 || X == 4 || X == 2 || X == 1, "one bit");
+  const int u = __float_as_int(v);
+  if constexpr (X == 8) return __int_as_float(__builtin_amdgcn_update_dpp(0, u, 0x128, 0xF, 0xF, false));   // row_ror:8
+  if constexpr (X == 4) {   // row_shl:4 into the even quads, row_shr:4 into the odd ones
+    const int t = __builtin_amdgcn_update_dpp(0, u, 0x104, 0xF, 0x5, false);
+    return __int_as_float(__builtin_amdgcn_update_dpp(t, u, 0x114, 0xF, 0xA, false));
+  }
+  if constexpr (X == 2) return __int_as_float(__builtin_amdgcn_update_dpp(0, u, 0x4E, 0xF, 0xF, false));   // quad_perm
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, u, 0xB1, 0xF, 0xF, false));
 }
-__device__ __forceinline__ float sum16(float v) {
-  v += ror16<8>(v);
-  v += ror16<4>(v);
-  v += ror16<2>(v);
-  v += ror16<1>(v);
-  return v;
+// N values' sums over the 16 lanes of a row: lane r gets that of value r % N.
+// Each step halves the values a lane carries, so 16 of them cost 15 exchanges;
+// every sum is that of an exclusive-or butterfly.
+template <int N>
+__device__ __forceinline__ float sums16(float (&v)[N], int r) {
+  static_assert(N == 16 || N == 8, "one row's lanes");
+  auto half = [&](auto x, int n) {
+    constexpr int X = decltype(x)::value;
+    const bool hi = r & X;
+#pragma unroll
+    for (int q = 0; q < n; ++q) v[q] = (hi ? v[q + n] : v[q]) + xor16<X>(hi ? v[q] : v[q + n]);
+  };
+  if constexpr (N == 16)
+    half(std::integral_constant<int, 8>{}, 8);
+  else
+#pragma unroll
+    for (int q = 0; q < N; ++q) v[q] += xor16<8>(v[q]);
+  half(std::integral_constant<int, 4>{}, 4);
+  half(std::integral_constant<int, 2>{}, 2);
+  half(std::integral_constant<int, 1>{}, 1);
+  return v[0];
 }
 
 template <int CIN, int COUT, int EPI, int M, int NB, bool POOL>
@@ -252,11 +273,12 @@ __global__ void __launch_bounds__(256) k_conv(VDims d, const uint16_t* __restric
   constexpr bool store = EPI != 2;   // (the head's layer keeps no activation)
   uint16_t* stg = reinterpret_cast<uint16_t*>(&tile[0][0]) + wave * 16 * M * CB;
   const int z = z0 + wave;
+  constexpr int HR = M < 4 ? M : 4;   // rows whose head values are summed together
+  float hs[4 * HR];
 #pragma unroll
   for (int m = 0; m < M; ++m) {
     const int y = y0 + m;
     const long row = (long)d.nx * (y + (long)d.ny * z);
-    float hs[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < NB; ++t) {
       const int cl = t * 16 + r, co = g0 + cl;
@@ -272,23 +294,17 @@ __global__ void __launch_bounds__(256) k_conv(VDims d, const uint16_t* __restric
           stg[(m * 16 + 4 * kg + i) * CB + cl] = q;
         else if (store && x < d.nx && y < d.ny && z < d.nz)
           Y[(row + x) * ys + yo + co] = q;
-        if (EPI == 2) hs[i] = wh * bf2f(q);
+        if (EPI == 2) hs[m % HR * 4 + i] = wh * bf2f(q);
       }
     }
-    if (EPI == 2) {
-      // sum the 16 channels: the 16 lanes of one row group
-#pragma unroll
-      for (int i = 0; i < 4; ++i) hs[i] = sum16(hs[i]);
-      if (r == 0 && y < d.ny && z < d.nz) {
-        const float b0 = hb[0];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int x = x0 + 4 * kg + i;
-          if (x < d.nx) {
-            delta[row + x] = hs[i] + b0;
-            if (delta2) delta2[row + x] = hs[i] + b0;
-          }
-        }
+    if (EPI == 2 && m % HR == HR - 1) {
+      // sum the 16 channels, the 16 lanes of a row: lane r gets row r / 4's voxel r % 4
+      const float h = sums16<4 * HR>(hs, r) + hb[0];
+      const int yr = y - (HR - 1) + r / 4 % HR, x = x0 + 4 * kg + r % 4;
+      if (r < 4 * HR && x < d.nx && yr < d.ny && z < d.nz) {
+        const long v = x + (long)d.nx * (yr + (long)d.ny * z);
+        delta[v] = h;
+        if (delta2) delta2[v] = h;
       }
     }
   }
