@@ -64,11 +64,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense BF16 matrix peak, published
 # HBM bytes per launch of the dominant kernel from two rocprofv3 --pmc
 # passes: FETCH_SIZE x its copy-calibrated factor (1.9998) + WRITE_SIZE,
 # medians over the run's dispatches (the finest-level colour pass at
-# 512x256x256 with the line tables, 606; the fused sweep there, reading
+# 512x256x256 with the line tables, 192; the fused sweep there, reading
 # every face, 336).  Valid for those kernels as they are now and for that
 # workload only; None elsewhere.
 TRAFFIC_BYTES_PER_LAUNCH = {
-    ("k_gs<double, true>", "c5"): 545528840,
+    ("k_gs_wide<double, 2>", "c5"): 551326605,
     ("k_gs_rb_fine<double, 13>", "c5"): 2027212498,
 }
 
@@ -85,10 +85,16 @@ SWEEP_BYTES_PER_CELL_FP64 = 48.0
 # fused sweep where the library uses it (large 3-D grids), else one colour
 # pass
 # with --precision mixed, the FP32 instances of the same kernels (half the bytes)
-SMOOTHER_KERNELS_FP32 = {True: ("k_gs_rb_fine<float, 13> (one red-black sweep, finest level)", 1.0),
-                         False: ("k_gs<float, true> (one red-black colour pass, finest level)", 0.5)}
-SMOOTHER_KERNELS = {True: ("k_gs_rb_fine<double, 13> (one red-black sweep, finest level)", 1.0),
-                    False: ("k_gs<double, true> (one red-black colour pass, finest level)", 0.5)}
+def smoother_kernel_of(wl, mixed, fused):
+    t, hx = ("float" if mixed else "double"), wl.nx // 2
+    if fused:
+        return f"k_gs_rb_fine<{t}, 13> (one red-black sweep, finest level)", 1.0
+    # large levels with long rows take several cell pairs per lane
+    v = 0
+    if wl.ny >= 4 and wl.nx % 2 == 0 and wl.nx * wl.ny * wl.nz >= 1 << 20:
+        v = next((k for k in ((4, 2) if mixed else (2,)) if hx % k == 0 and hx // k >= 48), 0)
+    kernel = f"k_gs_wide<{t}, {v}>" if v else f"k_gs<{t}, true>"
+    return f"{kernel} (one red-black colour pass, finest level)", 0.5
 
 
 def log(*a):
@@ -176,7 +182,7 @@ def run_gpu(args):
     reps = 100
     tables = line_table_fractions(S) if S.face_tables() else None
     fused = S.fine_sweep()
-    smoother_kernel, sweeps_per_launch = (SMOOTHER_KERNELS_FP32 if mixed else SMOOTHER_KERNELS)[fused]
+    smoother_kernel, sweeps_per_launch = smoother_kernel_of(wl, mixed, fused)
     sweep_bytes = SWEEP_BYTES_PER_CELL_FP64 / (2 if mixed else 1)
     avg_ms = S.time_kernel(ns.TIME_SMOOTH0, reps)
     S.timing_enable(ns.TIME_SMOOTH0, 4096)
