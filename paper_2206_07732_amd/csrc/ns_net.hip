@@ -688,14 +688,28 @@ __global__ void __launch_bounds__(12 * CI) k_wgrad(VDims d, const uint16_t* __re
 }
 
 // out[q] = sum over b of part[b n + q], b = 0 .. nblk - 1: 32 values per block,
-// eight threads per value (b modulo 8, in order) whose sums are added in order
+// eight threads per value (b modulo 8, in order) whose sums are added in order.
+// Bound by the latency of a thread's up to 32 loads, so eight are in flight at
+// once, in the same order of additions: 256 partials of 20.8 k values 9.2 -> 4.8 us
+// (median of the six sums of a training step at 128 x 64 x 64).
 __global__ void __launch_bounds__(256) k_part_reduce(const float* __restrict__ part, int nblk, int n,
                                                      float* __restrict__ out) {
   __shared__ float sm[8][33];
   const int c = threadIdx.x & 31, w = threadIdx.x >> 5, q = blockIdx.x * 32 + c;
   float s = 0.f;
   if (q < n)
-    for (int b = w; b < nblk; b += 8) s += part[(size_t)b * n + q];
+  {
+    const float* p = part + q;
+    int b = w;
+    for (; b + 56 < nblk; b += 64) {
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = p[(size_t)(b + 8 * i) * n];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) s += v[i];
+    }
+    for (; b < nblk; b += 8) s += p[(size_t)b * n];
+  }
   sm[w][c] = s;
   __syncthreads();
   if (w == 0 && q < n) {
