@@ -779,43 +779,61 @@ __device__ __forceinline__ u32x4 pack8(const float (&f)[8]) {
 }
 __device__ __forceinline__ u32x4 ld8(const uint16_t* __restrict__ p) { return *reinterpret_cast<const u32x4*>(p); }
 
-// d5 = ddelta w_c (a_c > 0)
-__global__ void k_head_bwd(long nv, const float* __restrict__ dd, const uint16_t* __restrict__ a,
-                           const float* __restrict__ w, uint16_t* __restrict__ d5) {
-  const long q = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= nv * 2) return;
-  float av[8], o[8];
-  unpack8(ld8(a + 8 * q), av);
-  const float g = dd[q >> 1];
+// d5 = ddelta w_c (a_c > 0), and per block the partials of the head's gradient,
+// (sum ddelta a_c for c < 16, sum ddelta), from the same read of a.  A thread
+// keeps to one half of the channels (its stride is even); lanes of one half are
+// added by exchanges, the block's waves in order.  Bound by the bytes of a and d5
+// with few waves per block's tail: four loads of a thread are in flight.
+// As two kernels, the second one thread's 256 sums long: 9.8 + 7.0 us at
+// 128 x 64 x 64, this one 8.9 us.
+__global__ void __launch_bounds__(256) k_head_bwd(long nv, const float* __restrict__ dd,
+                                                  const uint16_t* __restrict__ a, const float* __restrict__ w,
+                                                  uint16_t* __restrict__ d5, float* __restrict__ part) {
+  __shared__ float sm[4][17];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane & 1;
+  const long n = 2 * nv, step = 256L * gridDim.x;
+  float wv[8], s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, sd = 0.f;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = av[e] > 0.f ? g * w[8 * (int)(q & 1) + e] : 0.f;
-  *reinterpret_cast<u32x4*>(d5 + 8 * q) = pack8(o);
-}
-
-// per-block partials of (sum ddelta a_c for c < 16, sum ddelta)
-__global__ void __launch_bounds__(256) k_head_wgrad_part(long nv, const float* __restrict__ dd,
-                                                         const uint16_t* __restrict__ a, int vox_per_block,
-                                                         float* __restrict__ part) {
-  __shared__ float sm[256][17];
-  const long v0 = (long)blockIdx.x * vox_per_block;
-  const long v1 = v0 + vox_per_block < nv ? v0 + vox_per_block : nv;
-  float s[17];
+  for (int e = 0; e < 8; ++e) wv[e] = w[8 * g + e];
+  for (long q0 = (long)blockIdx.x * 256 + threadIdx.x; q0 < n; q0 += 4 * step) {
+    u32x4 in[4];
+    float gv[4];
 #pragma unroll
-  for (int c = 0; c < 17; ++c) s[c] = 0.f;
-  for (long v = v0 + threadIdx.x; v < v1; v += 256) {
-    const float g = dd[v];
+    for (int u = 0; u < 4; ++u) {
+      const long q = q0 + u * step < n ? q0 + u * step : q0;   // (past the end: loaded, not used)
+      in[u] = ld8(a + 8 * q);
+      gv[u] = dd[q >> 1];
+    }
 #pragma unroll
-    for (int c = 0; c < 16; ++c) s[c] += g * bf2f(a[v * 16 + c]);
-    s[16] += g;
+    for (int u = 0; u < 4; ++u) {
+      const long q = q0 + u * step;
+      if (q >= n) break;
+      float av[8], o[8];
+      unpack8(in[u], av);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        o[e] = av[e] > 0.f ? gv[u] * wv[e] : 0.f;
+        s[e] += gv[u] * av[e];
+      }
+      sd += gv[u];
+      *reinterpret_cast<u32x4*>(d5 + 8 * q) = pack8(o);
+    }
   }
 #pragma unroll
-  for (int c = 0; c < 17; ++c) sm[threadIdx.x][c] = s[c];
+  for (int m = 2; m < 64; m <<= 1) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s[e] += __shfl_xor(s[e], m);
+    sd += __shfl_xor(sd, m);
+  }
+  if (lane < 2) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sm[wave][8 * g + e] = s[e];
+    if (lane == 0) sm[wave][16] = sd;
+  }
   __syncthreads();
-  if (threadIdx.x < 17) {
-    float t = 0.f;
-    for (int q = 0; q < 256; ++q) t += sm[q][threadIdx.x];
-    part[(size_t)blockIdx.x * 17 + threadIdx.x] = t;
-  }
+  if (threadIdx.x < 17)
+    part[(size_t)blockIdx.x * 17 + threadIdx.x] =
+        ((sm[0][threadIdx.x] + sm[1][threadIdx.x]) + sm[2][threadIdx.x]) + sm[3][threadIdx.x];
 }
 
 // d (coarse, dense C) = (sum over the 8 children of dC[child][oo + c]) (a > 0)
@@ -1136,7 +1154,9 @@ struct NetCarve {
   }
 };
 
-constexpr int kHeadVox = 4096;   // voxels per block of the head's weight gradient
+// blocks of the head's backward kernel: two per compute unit, of at least 1024
+// voxels (eight 16-byte pieces a thread)
+int head_blocks(long v0) { return (int)std::min<long>((v0 + 1023) / 1024, 512); }
 
 // Blocks of a layer's weight gradient (per group of input channels): enough
 // to fill the chip's 256 compute units with one block each, few enough that
@@ -1219,7 +1239,7 @@ size_t net_layout(ns_net* N, int nx, int ny, int nz, int training, char* base) {
       const size_t nb = (size_t)wgrad_blocks(nx >> sh, ny >> sh, nz >> sh, kCin[l], kCout[l]);
       wpart_elems = std::max(wpart_elems, nb * (27 * (size_t)kCout[l] * kCin[l] + kCout[l]));
     }
-    wpart_elems = std::max(wpart_elems, (size_t)((v0 + kHeadVox - 1) / kHeadVox) * 17);
+    wpart_elems = std::max(wpart_elems, (size_t)head_blocks(v0) * 17);
     wpart = cv.take<float>(wpart_elems);
   }
   if (N) {
@@ -1415,10 +1435,9 @@ void backward(ns_net* N) {
   const uint16_t *a1 = N->C1, *a2 = N->C2;
   // head
   {
-    const int nb = (int)((N->v0 + kHeadVox - 1) / kHeadVox);
-    hipLaunchKernelGGL(k_head_wgrad_part, dim3(nb), dim3(256), 0, st, N->v0, N->dd, N->a5, kHeadVox, N->wpart);
+    const int nb = head_blocks(N->v0);
+    hipLaunchKernelGGL(k_head_bwd, dim3(nb), dim3(256), 0, st, N->v0, N->dd, N->a5, th + N->ohw, N->d5, N->wpart);
     hipLaunchKernelGGL(k_part_reduce, dim3(1), dim3(256), 0, st, N->wpart, nb, 17, N->g + N->ohw);
-    hipLaunchKernelGGL(k_head_bwd, g1(N->v0 * 2), dim3(256), 0, st, N->v0, N->dd, N->a5, th + N->ohw, N->d5);
   }
   // layer 5: input [a1, up(a4)] (48), output 16
   wgrad<48, 16>(N, N->res0, a1, 16, 16, N->a4, 32, N->d5, 4);
