@@ -538,17 +538,20 @@ __global__ void __launch_bounds__(256) k_conv_in(VDims d, const u32x2* __restric
 // tensors are channels-last, so a tile of 16 x 4 x 2 voxels is staged in LDS
 // transposed, 16 x-consecutive voxels of one channel per row: a fragment is
 // then one 16-byte read, and the three dx taps come from that read and its two
-// edge voxels by shifts.  Each of the 3 x CI/16 waves owns one dz plane of taps
-// for 16 input channels and keeps its 9 x COUT/16 accumulators in registers
-// over all the block's tiles, so the tile is read from memory once for all 27
-// taps and only one partial per block is written; the next tile's loads are
-// in flight while this one is multiplied.  What it replaced had one tap per
+// edge voxels by shifts.  A block takes 16 input channels (blockIdx.y picks
+// them): each of its three waves owns one dz plane of taps and keeps its
+// 9 x COUT/16 accumulators in registers over all the block's tiles, so the tile
+// is read from memory once for all 27 taps and only one partial per block is
+// written; the next tile's loads are in flight while this one is multiplied.
+// A layer of more input channels has several such blocks on a unit, which wait
+// at their barriers at different times: as one block of nine waves the 48 -> 16
+// layer took 63.0 us at 128 x 64 x 64, as three of three 56.7, though each reads
+// dY (the 96 -> 32 layer 27.4 and 27.6).  What it replaced had one tap per
 // block, read X and dY 27 times with 2-byte gathers and summed the bias in a
 // kernel of its own: at 128 x 64 x 64 the 48 -> 16 layer took 538 + 62 us and
 // the five layers 1.9 ms of a 2.5 ms training step.
-// CI: input channels per block (blockIdx.y picks the group).  X is, as in
-// k_conv, the concatenation of XA (channels [0, ca)) and a half-resolution
-// XB read through nearest upsampling.
+// X is, as in k_conv, the concatenation of XA (channels [0, ca)) and a
+// half-resolution XB read through nearest upsampling.
 constexpr int kWX = 16, kWY = 4, kWZ = 2;                 // output voxels of a tile
 constexpr int kWRows = (kWY + 2) * (kWZ + 2);             // halo rows of a channel
 // dwords: a halo row holds x = 0..16 in elements 0..16 and x = -1 in element
@@ -556,12 +559,15 @@ constexpr int kWRows = (kWY + 2) * (kWZ + 2);             // halo rows of a chan
 // that 16 lanes reading 16 bytes of 16 channels meet no bank conflict
 constexpr int kWRow = 12, kWChan = kWRows * kWRow + 4, kWdY = kWX * kWY * kWZ / 2 + 4;
 
-template <int CIN, int COUT, int CI>
-__global__ void __launch_bounds__(12 * CI) k_wgrad(VDims d, const uint16_t* __restrict__ XA, int sa, int ca,
+constexpr int kWCI = 16;   // input channels of a block
+
+template <int CIN, int COUT>
+__global__ void __launch_bounds__(12 * kWCI) k_wgrad(VDims d, const uint16_t* __restrict__ XA, int sa, int ca,
                                                    const uint16_t* __restrict__ XB, int sb,
                                                    const uint16_t* __restrict__ dY, int ntx, int nty, int tiles,
                                                    float* __restrict__ part) {
-  static_assert(CIN % CI == 0 && CI % 16 == 0 && COUT % 16 == 0, "channels in multiples of 16");
+  static_assert(CIN % 16 == 0 && COUT % 16 == 0, "channels in multiples of 16");
+  constexpr int CI = kWCI;
   constexpr int NT = 12 * CI, NO = COUT / 16, GX = CI / 8, GY = COUT / 8;
   constexpr int IX = kWRows * 10 * GX, SX = (IX + NT - 1) / NT;          // staged pieces of X: rows x 10 voxel pairs
   constexpr int IY = kWY * kWZ * 8 * GY, SY = (IY + NT - 1) / NT;        // of dY
@@ -569,7 +575,7 @@ __global__ void __launch_bounds__(12 * CI) k_wgrad(VDims d, const uint16_t* __re
   __shared__ uint32_t ly[COUT * kWdY];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 15, kg = lane >> 4;
-  const int dz = wave % 3, ti = wave / 3;
+  const int dz = wave;
   const int c0 = (int)blockIdx.y * CI;
   const int cnx = d.nx >> 1, cny = d.ny >> 1;
   const u32x4 zero = {0u, 0u, 0u, 0u};
@@ -633,9 +639,9 @@ __global__ void __launch_bounds__(12 * CI) k_wgrad(VDims d, const uint16_t* __re
 #pragma unroll
     for (int q = 0; q < 9; ++q) acc[q / 3][q % 3][o] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  const bool bias = dz == 1 && ti == 0 && blockIdx.y == 0;   // this wave also sums dY itself
+  const bool bias = dz == 1 && blockIdx.y == 0;   // this wave also sums dY itself
   const bf16x8 ones = as_bf16x8(u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u});
-  const uint32_t* xw = lx + (16 * ti + r) * kWChan;
+  const uint32_t* xw = lx + r * kWChan;
   int t = blockIdx.x;
   if (t < tiles) fetch(t);
   for (; t < tiles; t += gridDim.x) {
@@ -682,7 +688,7 @@ __global__ void __launch_bounds__(12 * CI) k_wgrad(VDims d, const uint16_t* __re
     for (int i = 0; i < 4; ++i) {
       const int co = 16 * o + 4 * kg + i;
 #pragma unroll
-      for (int q = 0; q < 9; ++q) out[(size_t)(co * 27 + dz * 9 + q) * CIN + c0 + 16 * ti + r] = acc[q / 3][q % 3][o][i];
+      for (int q = 0; q < 9; ++q) out[(size_t)(co * 27 + dz * 9 + q) * CIN + c0 + r] = acc[q / 3][q % 3][o][i];
       if (bias && r == 0) out[27 * COUT * CIN + co] = accb[o][i];
     }
 }
@@ -1158,23 +1164,19 @@ struct NetCarve {
 // voxels (eight 16-byte pieces a thread)
 int head_blocks(long v0) { return (int)std::min<long>((v0 + 1023) / 1024, 512); }
 
-// Blocks of a layer's weight gradient (per group of input channels): enough
+// Blocks of a layer's weight gradient per 16 input channels: enough
 // to fill the chip's 256 compute units with one block each, few enough that
-// the partials, written and read once, stay within 24 MB.  The 16 -> 16 layer's
-// blocks are three waves, which leave a unit idle at each barrier: it takes two
+// the partials, written and read once, stay within 24 MB.  The 16 -> 16 layer has
+// no second block on a unit to work while one waits at a barrier: it takes two
 // blocks a unit where each still has four tiles (its partials are the smallest,
 // so the room is the same): 128 x 64 x 64 38.0 -> 25.4 us.
 int wgrad_tiles(int nx, int ny, int nz) {
   return (nx + kWX - 1) / kWX * ((ny + kWY - 1) / kWY) * ((nz + kWZ - 1) / kWZ);
 }
-// input channels per block: all of them, unless their accumulators (36 COUT/16
-// registers a wave) and the next tile's loads exceed what a block of 12 CI
-// threads has per thread (168 registers at 576 threads, 256 at 384)
-constexpr int wgrad_group(int cin, int cout) { return cin == 96 ? 32 : cout == 64 ? 16 : cin; }
 int wgrad_blocks(int nx, int ny, int nz, int cin, int cout) {
   const long most = (24L << 20) / (4L * (27L * cin * cout + cout)), tiles = wgrad_tiles(nx, ny, nz);
-  if (cin == 16 && cout == 16) return (int)std::max(std::min(tiles, 256L), std::min(tiles / 4, 512L));
-  return (int)std::min<long>(std::min<long>(tiles, 256 / (cin / wgrad_group(cin, cout))), most);
+  const long two = cin == 16 && cout == 16 ? std::min(tiles / 4, 512L) : 0;
+  return (int)std::min(std::max(std::min(tiles, 256L), two), most);
 }
 
 size_t net_layout(ns_net* N, int nx, int ny, int nz, int training, char* base) {
@@ -1425,9 +1427,8 @@ void forward(ns_net* N) {
 template <int CIN, int COUT>
 void wgrad(ns_net* N, VDims d, const uint16_t* XA, int sa, int ca, const uint16_t* XB, int sb, const uint16_t* dY,
            int layer) {
-  constexpr int CI = wgrad_group(CIN, COUT);
   const int nb = wgrad_blocks(d.nx, d.ny, d.nz, CIN, COUT), n = 27 * COUT * CIN + COUT;
-  hipLaunchKernelGGL((k_wgrad<CIN, COUT, CI>), dim3(nb, CIN / CI), dim3(12 * CI), 0, N->st, d, XA, sa, ca, XB, sb, dY,
+  hipLaunchKernelGGL((k_wgrad<CIN, COUT>), dim3(nb, CIN / kWCI), dim3(12 * kWCI), 0, N->st, d, XA, sa, ca, XB, sb, dY,
                      (d.nx + kWX - 1) / kWX, (d.ny + kWY - 1) / kWY, wgrad_tiles(d.nx, d.ny, d.nz), N->wpart);
   // (a layer's biases follow its weights in the gradient)
   hipLaunchKernelGGL(k_part_reduce, g1(n, 32), dim3(256), 0, N->st, N->wpart, nb, n, N->g + N->ow[layer]);
