@@ -1418,8 +1418,13 @@ static bool pairs_pay(const Dims& n) { return n.nx >= 2 && (long)n.nx * n.ny * n
 
 // Where a lane marches up a column: from 2^20 cells on; below it a cell per lane,
 // whose many short wavefronts fill the chip better (128 x 64 x 64: advection
-// and five pseudo-steps 36 us against 43; 200 x 72 x 104: 98 against 80)
-static bool marches(const Dims& n) { return n.ny >= 4 && (long)n.nx * n.ny * n.nz >= (1L << 20); }
+// and five pseudo-steps 36 us against 43; 200 x 72 x 104: 98 against 80).  A
+// plane's values are at byte offsets of 32 bits, so its largest array must stay
+// below 2^29 entries (23171 x 23171 x 2 is a valid grid)
+static bool marches(const Dims& n) {
+  return n.ny >= 4 && (long)n.nx * n.ny * n.nz >= (1L << 20) &&
+         std::max((long)(n.nx + 1) * n.ny, (long)n.nx * (n.ny + 1)) < (1L << 29);
+}
 // Pseudo-steps per launch
 int reinit_steps(const Dims& n) { return n.ny == 1 ? kR2 : marches(n) ? 2 : 1; }
 
