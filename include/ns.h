@@ -263,7 +263,8 @@ ns_status ns_pcg_solve(ns_ctx* ctx, ns_stats* stats);
 ns_status ns_apply_A(ns_ctx* ctx, const double* x, double* y);
 
 /* z = M r: one V-cycle of the current hierarchy (rebuilt from the level-0
- * beta) in the precision of params.prec (r, z: device, cells). */
+ * beta) in the precision of params.prec (r, z: device, cells; they may be the
+ * same array, or overlap). */
 ns_status ns_vcycle(ns_ctx* ctx, const double* r, double* z);
 
 /* Device pointer and element count of an internal array. */

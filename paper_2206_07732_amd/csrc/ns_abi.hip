@@ -10,6 +10,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <new>
 
 #include "ns_internal.h"
@@ -1788,6 +1789,14 @@ ns_status ns_vcycle(ns_ctx* X, const double* r, double* z) {
   launch_d2f(L0.by, L0.byf, X->nv, X->st);
   launch_d2f(L0.bz, L0.bzf, X->nw, X->st);
   prepare_hierarchy(X);
+  // A 2-D level's visit up reads r for its tiles' rings while other blocks store
+  // z: where the caller's arrays overlap, it reads a copy (in the finest level's
+  // own b, which these visits leave alone).  Every other cycle has read r for
+  // the last time before z is first stored.
+  if (X->P.prec == NS_PREC_FP64 && use_2d<double>(X, 0) && std::less<>{}(r, z + X->nc) && std::less<>{}(z, r + X->nc)) {
+    launch_copy(r, L0.b, X->nc, X->st);
+    r = L0.b;
+  }
   precond_launch(X, r, z);   // caller pointers: launched, never recorded
   HIPCHK(X, hipGetLastError());
   return NS_OK;
