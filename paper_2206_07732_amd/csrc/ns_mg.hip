@@ -2240,17 +2240,21 @@ struct RegLevel {
       co[q] = ti + V.nc.nx * ((j >> (V.fy - 1)) + V.nc.ny * (k >> (V.fz - 1)));
       if (k == g.nz - 1) top |= 1u << q;
       const int row = (g.nx + 1) * (j + g.ny * k);
-      fm[q] = V.bx[row + 2 * ti + 1];   // (past an odd row's end: the wall face, zero)
+      const T xm = V.bx[row + 2 * ti + 1];   // (past an odd row's end: the wall face)
+      fm[q] = 2 * ti + 1 < g.nx ? xm : (T)0;
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         const int o = (j + k + c) & 1, i = min(2 * ti + o, g.nx - 1);
         if (tid + q * kTailThreads < P && 2 * ti + o < g.nx) ok |= 1u << (2 * q + c);
         if (o) odd |= 1u << (2 * q + c);
         const int fy = i + g.nx * (j + (g.ny + 1) * k), cc = i + g.nx * j + sxy * k;
-        f[q][c][0] = V.bx[row + (o ? i + 1 : i)];
-        f[q][c][1] = V.by[fy];
-        f[q][c][2] = V.by[fy + g.nx];
-        f[q][c][3] = V.bz[cc];
+        // (a wall face is zero here whatever a caller's array holds: the entry
+        // beyond it is another row's)
+        const T xo = V.bx[row + (o ? i + 1 : i)], ys = V.by[fy], yn = V.by[fy + g.nx], zd = V.bz[cc];
+        f[q][c][0] = (o ? i + 1 < g.nx : i > 0) ? xo : (T)0;
+        f[q][c][1] = j > 0 ? ys : (T)0;
+        f[q][c][2] = j < g.ny - 1 ? yn : (T)0;
+        f[q][c][3] = k > 0 ? zd : (T)0;
         f[q][c][4] = V.bz[cc + sxy];
         id[q][c] = V.id[cc];
         b[q][c] = V.b[cc];
@@ -2628,8 +2632,12 @@ struct Tile2d {
       fm[q] = ok ? fm[q] : (T)0;
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) f[q][c][d] = ok ? f[q][c][d] : (T)0;
+        // (a wall face is zero here whatever a caller's array holds: the entry
+        // beyond it is not the cell's own)
+        const int i = col(q, c), o = (int)(odd >> (2 * q + c) & 1u);
+        f[q][c][0] = ok && (o ? i + 1 < nx : i > 0) ? f[q][c][0] : (T)0;
+        f[q][c][1] = ok && row(q) > 0 ? f[q][c][1] : (T)0;
+        f[q][c][2] = ok ? f[q][c][2] : (T)0;
         id[q][c] = ok ? id[q][c] : (T)0;
         b[q][c] = ok ? (T)bb[q][c] : (T)0;
       }
