@@ -220,18 +220,20 @@ int tail_matrix_level(const Level* lev, int L, int l) {
   return L;
 }
 
-// LDS elements of a tail whose first level l is held in registers: its
-// correction's planes; of the levels below the pack (face coefficients, 1/D), b
-// and e; the matrix product's and the residual's scratch; without a matrix,
-// the coarsest level's planes
-size_t tail_top_elems(const Level* lev, int L, int l) {
-  const Dims n = lev[l].n;
-  size_t tot = pad4(reg_planes(n));
-  if (l == L - 1) return tot;
-  tot += kTailThreads + tail_pack_elems(lev, L, l + 1) + pad4((size_t)n.nx * n.ny * n.nz);
-  for (int q = l + 1; q < L; ++q) tot += 2 * pad4((size_t)lev[q].n.nx * lev[q].n.ny * lev[q].n.nz);
-  if (tail_matrix_level(lev, L, l + 1) == L) tot += pad4(reg_planes(lev[L - 1].n));
-  return tot;
+// LDS bytes of a tail from level l down, w bytes an element.  Its first level in
+// registers: its correction's planes; of the levels below the pack (face
+// coefficients, 1/D), b and e, and the residual's scratch; the coarsest level's
+// planes, for a cycle without the matrix.  A matrix: its level's b and e and the
+// product's partial sums.
+size_t tail_lds_bytes(const Level* lev, int L, int l, size_t w) {
+  auto cells = [&](int q) { return pad4((size_t)lev[q].n.nx * lev[q].n.ny * lev[q].n.nz); };
+  size_t tot = pad4(reg_planes(lev[l].n));
+  if (l < L - 1) {
+    tot += tail_pack_elems(lev, L, l + 1) + cells(l) + pad4(reg_planes(lev[L - 1].n));
+    for (int q = l + 1; q < L; ++q) tot += 2 * cells(q);
+  }
+  if (tail_matrix_level(lev, L, l) == l) tot = std::max(tot, 2 * cells(l));
+  return (tot + kTailThreads) * w;
 }
 
 // Whether a visit's smoothing is the 2-D launches' (k_pre2d, k_post2d)
@@ -249,7 +251,7 @@ int plan_tail(const Level* lev, int L, bool tank2d, size_t w, size_t* bytes, boo
     auto below = [&](int q) { return (size_t)((lev[q].n.nx + 1) / 2) * lev[q].n.ny * lev[q].n.nz; };
     if (l < L - 1 && (below(l + 1) > 2 * (size_t)kTailThreads || below(L - 1) > (size_t)kTailThreads)) continue;
     *top = tail_matrix_level(lev, L, l) != l;
-    *bytes = (*top ? tail_top_elems(lev, L, l) : 2 * pad4((size_t)n.nx * n.ny * n.nz) + kTailThreads) * w;
+    *bytes = tail_lds_bytes(lev, L, l, w);
     const size_t per = w == sizeof(double) ? tail_top_pairs<double>() : tail_top_pairs<float>();
     // A level that k_pre2d and k_post2d take joins the tail at one pair per
     // thread: 320 x 1 x 64 (its 160 x 32 first coarse level as launches) 1.41
@@ -519,10 +521,10 @@ size_t tail_bytes(const ns_ctx* X) {
 }
 
 // The tail's launch: the cycle from its first level l0 down, to the level from
-// which it is a matrix where there is one.  bytes 0: that matrix is formed, l0
-// being its level.
+// which it is a matrix where there is one (matrix: it has been formed), else by
+// passes throughout.  bytes 0: that matrix is formed, l0 being its level.
 template <typename T>
-void launch_tail(ns_ctx* X, int l0, const T* b, T* e, size_t bytes) {
+void launch_tail(ns_ctx* X, int l0, const T* b, T* e, size_t bytes, bool matrix) {
   TailDesc<T> D{};
   const int lm = sizeof(T) == 8 ? X->mlev64 : X->mlev32;
   T* M;
@@ -531,7 +533,7 @@ void launch_tail(ns_ctx* X, int l0, const T* b, T* e, size_t bytes) {
   else
     M = X->mat32;
   const bool form = bytes == 0;
-  const bool top = !form && (sizeof(T) == 8 ? X->top64 : X->top32);
+  const bool top = !form && ((sizeof(T) == 8 ? X->top64 : X->top32) || !matrix);
   if (top) {
     const Level& V = X->lev[l0];
     D.top = 1;
@@ -544,7 +546,7 @@ void launch_tail(ns_ctx* X, int l0, const T* b, T* e, size_t bytes) {
     D.tid = LV<T>::invd(V);
     ++l0;   // the levels of the LDS image
   }
-  D.M = !form && lm < X->L ? M : nullptr;
+  D.M = !form && matrix && lm < X->L ? M : nullptr;
   D.nl = (D.M ? lm + 1 : X->L) - l0;
   D.nu_pre = X->P.nu_pre;
   D.nu_post = X->P.nu_post;
@@ -595,7 +597,7 @@ void launch_tail(ns_ctx* X, int l0, const T* b, T* e, size_t bytes) {
 // coarse coefficients of every level from level 0, and 1/D of every level
 // (the tail stages it), in precision T: one launch per level
 template <typename T>
-void build_hierarchy(ns_ctx* X) {
+void build_hierarchy(ns_ctx* X, bool matrix) {
   const Level& V0 = X->lev[0];
   launch_invdiag<T>(V0, LV<T>::bx(V0), LV<T>::by(V0), LV<T>::bz(V0), LV<T>::invd(V0), 0 < tail_start<T>(X), X->st);
   for (int l = 1; l < X->L; ++l) {
@@ -619,8 +621,8 @@ void build_hierarchy(ns_ctx* X) {
     launch_coarsen_level<T>(F, LV<T>::bx(F), LV<T>::by(F), LV<T>::bz(F), C, LV<T>::bx(C), LV<T>::by(C),
                             LV<T>::bz(C), LV<T>::invd(C), l < tail_start<T>(X), X->st);
   }
-  if ((sizeof(T) == 8 ? X->mlev64 : X->mlev32) < X->L)
-    launch_tail<T>(X, sizeof(T) == 8 ? X->mlev64 : X->mlev32, nullptr, nullptr, 0);
+  if (matrix && (sizeof(T) == 8 ? X->mlev64 : X->mlev32) < X->L)
+    launch_tail<T>(X, sizeof(T) == 8 ? X->mlev64 : X->mlev32, nullptr, nullptr, 0, true);
   // the first coarse level's line tables, in the cycle's precision, where
   // its passes run outside the tail and it is large enough for them to pay
   if (X->face_tabs && X->L > 1 && 1 < tail_start<T>(X) && face_tables_pay(X->lev[1].n)) {
@@ -670,12 +672,12 @@ T* corr(const ns_ctx* X, int l) {
 }
 
 template <typename T>
-void vcycle(ns_ctx* X, int l, const T* b0, T* e0, CgReq* dq = nullptr, const double* b0d = nullptr) {
+void vcycle(ns_ctx* X, int l, bool matrix, const T* b0, T* e0, CgReq* dq = nullptr, const double* b0d = nullptr) {
   const ns_params& P = X->P;
   const Level& L = X->lev[l];
   hipStream_t st = X->st;
   if (l == tail_start<T>(X)) {
-    launch_tail<T>(X, l, l == 0 ? b0 : LV<T>::b(L), l == 0 ? e0 : LV<T>::e(L), tail_bytes<T>(X));
+    launch_tail<T>(X, l, l == 0 ? b0 : LV<T>::b(L), l == 0 ? e0 : LV<T>::e(L), tail_bytes<T>(X), matrix);
     return;
   }
   if (use_2d<T>(X, l)) {
@@ -688,14 +690,14 @@ void vcycle(ns_ctx* X, int l, const T* b0, T* e0, CgReq* dq = nullptr, const dou
     if (l > 0) {
       const T* b = LV<T>::b(L);
       launch_pre2d<T, T>(L, fx, fz, id, b, w, csplit, LV<T>::b(C), st);
-      vcycle<T>(X, l + 1, nullptr, nullptr);
+      vcycle<T>(X, l + 1, matrix, nullptr, nullptr);
       launch_post2d<T, T, T>(L, fx, fz, id, b, w, csplit, corr<T>(X, l + 1), corr<T>(X, l), nullptr, nullptr, st);
       return;
     }
     auto both = [&](auto* b) {
       using TB = std::remove_cv_t<std::remove_pointer_t<decltype(b)>>;
       launch_pre2d<T, TB>(L, fx, fz, id, b, w, csplit, LV<T>::b(C), st);
-      vcycle<T>(X, 1, nullptr, nullptr);
+      vcycle<T>(X, 1, matrix, nullptr, nullptr);
       if (dq && dq->dots)
         dq->nparts = launch_post2d<T, TB, double>(L, fx, fz, id, b, w, csplit, corr<T>(X, 1), dq->z, dq->r, X->partials, st);
       else
@@ -809,7 +811,7 @@ void vcycle(ns_ctx* X, int l, const T* b0, T* e0, CgReq* dq = nullptr, const dou
   const Level& C = X->lev[l + 1];
   const bool csplit = (l + 1) < tail_start<T>(X);   // (a 2-D level's next one is 2-D: use_2d)
   launch_resid_restrict<T>(L, bx, by, bz, b, e, C, LV<T>::b(C), csplit, st);
-  vcycle<T>(X, l + 1, nullptr, nullptr);
+  vcycle<T>(X, l + 1, matrix, nullptr, nullptr);
   // post-smoothing: (prolongation + black) fused, then red, then black, red
   // pairs; at level 0 the last red pass writes e0
   if (P.nu_post > 0 && rb && P.nu_post >= 2) {
@@ -857,10 +859,10 @@ bool use_split(const ns_ctx* X) {
 // the cycle's last kernel also leaves the partials of r z in X->partials when
 // it can; returns how many (0: not fused, or not asked).  split: r and z are
 // colour-split (use_split).
-int precond_launch(ns_ctx* X, const double* r, double* z, bool dots = false, bool split = false) {
+int precond_launch(ns_ctx* X, const double* r, double* z, bool matrix, bool dots = false, bool split = false) {
   CgReq dq{r, z, dots, split, 0};
   if (X->P.prec == NS_PREC_FP64) {
-    vcycle<double>(X, 0, r, z, &dq);
+    vcycle<double>(X, 0, matrix, r, z, &dq);
     return dots ? dq.nparts : 0;
   }
   // FP32 cycle: its first kernel reads r itself, rounding it to FP32, where
@@ -869,7 +871,7 @@ int precond_launch(ns_ctx* X, const double* r, double* z, bool dots = false, boo
   Level& L0 = X->lev[0];
   const bool direct = tail_start<float>(X) > 0 && X->P.nu_pre > 0;
   if (!direct) launch_d2f(r, L0.bfn, X->nc, X->st);
-  vcycle<float>(X, 0, L0.bfn, L0.efn, &dq, direct ? r : nullptr);
+  vcycle<float>(X, 0, matrix, L0.bfn, L0.efn, &dq, direct ? r : nullptr);
   if (dq.nparts > 0) return dots ? dq.nparts : 0;
   if (dots) return launch_f2d_dots(L0.efn, z, X->nc, r, X->partials, X->st);
   launch_f2d(L0.efn, z, X->nc, X->st);
@@ -945,12 +947,13 @@ void build_face_tables(ns_ctx* X) {
   }
 }
 
-void prepare_hierarchy(ns_ctx* X) {
+// (matrix: with the tail's matrix, which a solve's cycles share)
+void prepare_hierarchy(ns_ctx* X, bool matrix) {
   build_face_tables(X);
   if (X->P.prec == NS_PREC_FP64)
-    build_hierarchy<double>(X);
+    build_hierarchy<double>(X, matrix);
   else
-    build_hierarchy<float>(X);
+    build_hierarchy<float>(X, matrix);
 }
 
 // Totals of a reduction the host reads: summed here, in block order, from the
@@ -1017,7 +1020,7 @@ ns_status pcg(ns_ctx* X, ns_stats* stats) {
   auto precond = [&](int kind, int mode, double* zz) {
     return issue(X, kind, zz, nullptr, nullptr, 0, [&] {
       // the product comes with the cycle's last kernel when it can give it
-      int np = precond_launch(X, X->r, zz, true, split);
+      int np = precond_launch(X, X->r, zz, true, true, split);
       if (np > 0 && !fold) launch_finalize_dot(cs, np, mode, X->st);
       if (np == 0) np = launch_dot(n, X->r, zz, cs, mode, X->st, fold);
       X->ndot = fold ? np : 0;
@@ -1045,7 +1048,7 @@ ns_status pcg(ns_ctx* X, ns_stats* stats) {
     if (xpend) launch_x_update(n, dcur, x, cs, X->st, xs);
     xpend = false;
   };
-  prepare_hierarchy(X);
+  prepare_hierarchy(X, true);
   X->nres = launch_resid_norm(n, h, L0.bx, L0.by, L0.bz, X->b, x, X->r, cs, FIN_RESID0, st, face_tab(L0, L0.bx), split,
                               xs);
   HIPCHK(X, hipEventRecord(X->ev_rr, st));
@@ -1788,7 +1791,9 @@ ns_status ns_vcycle(ns_ctx* X, const double* r, double* z) {
   launch_d2f(L0.bx, L0.bxf, X->nu, X->st);
   launch_d2f(L0.by, L0.byf, X->nv, X->st);
   launch_d2f(L0.bz, L0.bzf, X->nw, X->st);
-  prepare_hierarchy(X);
+  // One cycle does not earn the tail's matrix (16 x 1 x 16: 59 us with it, 37
+  // without): its levels run by passes.
+  prepare_hierarchy(X, false);
   // A 2-D level's visit up reads r for its tiles' rings while other blocks store
   // z: where the caller's arrays overlap, it reads a copy (in the finest level's
   // own b, which these visits leave alone).  Every other cycle has read r for
@@ -1797,7 +1802,7 @@ ns_status ns_vcycle(ns_ctx* X, const double* r, double* z) {
     launch_copy(r, L0.b, X->nc, X->st);
     r = L0.b;
   }
-  precond_launch(X, r, z);   // caller pointers: launched, never recorded
+  precond_launch(X, r, z, false);   // caller pointers: launched, never recorded
   HIPCHK(X, hipGetLastError());
   return NS_OK;
 }

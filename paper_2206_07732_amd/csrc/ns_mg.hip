@@ -2421,6 +2421,10 @@ __device__ __forceinline__ void tail_levels(const TailDesc<T>& D, T* sm, int tid
     const int sxy = n.nx * n.ny;
     const T h2 = D.h2[l];
     const TailArrays<T> A{sm + D.obx[l], sm + D.oby[l], sm + D.obz[l], sm + D.oid[l], sm + D.ob[l], sm + D.oe[l]};
+    if (bottom && n.nx <= 2 && n.ny == 1 && n.nz == 1) {
+      tail_coarsest_row<T>(A, n.nx == 2, h2, D.coarse_sweeps, tid);
+      continue;
+    }
     if constexpr (REG) {
       if (bottom) {
         RegLevel<T, 1> t({n, n, 1, 1, h2, A.bx, A.by, A.bz, A.id, A.b, sm + D.oeb, nullptr}, tid);
@@ -2430,10 +2434,6 @@ __device__ __forceinline__ void tail_levels(const TailDesc<T>& D, T* sm, int tid
         __syncthreads();
         continue;
       }
-    }
-    if (bottom && n.nx <= 2 && n.ny == 1 && n.nz == 1) {
-      tail_coarsest_row<T>(A, n.nx == 2, h2, D.coarse_sweeps, tid);
-      continue;
     }
     TailPairs tp;
     tail_decode(n, tid, nthr, tp);
