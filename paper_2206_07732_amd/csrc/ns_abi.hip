@@ -233,7 +233,7 @@ size_t tail_lds_bytes(const Level* lev, int L, int l, size_t w) {
     for (int q = l + 1; q < L; ++q) tot += 2 * cells(q);
   }
   if (tail_matrix_level(lev, L, l) == l) tot = std::max(tot, 2 * cells(l));
-  return (tot + kTailThreads) * w;
+  return tot * w + kTailThreads * sizeof(double);
 }
 
 // Whether a visit's smoothing is the 2-D launches' (k_pre2d, k_post2d)
@@ -583,7 +583,7 @@ void launch_tail(ns_ctx* X, int l0, const T* b, T* e, size_t bytes, bool matrix)
   } else {
     D.ors = D.nl > 1 ? take((size_t)D.n[0].nx * D.n[0].ny * D.n[0].nz) : 0;
   }
-  D.omv = take(kTailThreads);
+  D.omv = take(kTailThreads * sizeof(double) / sizeof(T));
   D.pack = D.nl > 0 ? LV<T>::bx(X->lev[l0]) : nullptr;   // (the pack of a level starts with its bx)
   if (form) {
     launch_tail_matrix<T>(D, off, M, X->st);

@@ -2095,7 +2095,9 @@ struct TailLoads {
 // one colour pass.  Every load of the thread's cells is issued before the
 // arithmetic starts (the scheduling barrier keeps the compiler from
 // interleaving them with the sums, which would wait on each pair in turn).
-template <typename T>
+// DIVIDE: the quotient by the diagonal, rounded, for one correction of the product
+// with 1/D (which an FP32 cycle's matrix has in FP32 only).
+template <typename T, bool DIVIDE>
 __device__ __forceinline__ void tail_pass(const Dims& n, const TailPairs& tp, const TailArrays<T>& A, T h2, int colour,
                                           bool from_zero) {
   const int sxy = n.nx * n.ny;
@@ -2108,7 +2110,12 @@ __device__ __forceinline__ void tail_pass(const Dims& n, const TailPairs& tp, co
       const T with_up = num + l.f[5] * l.v[5];
       num = x.top ? num : with_up;
     }
-    return num * l.id;
+    T v = num * l.id;
+    if constexpr (DIVIDE) {
+      const T diag = l.f[0] + l.f[1] + l.f[2] + l.f[3] + l.f[4] + (x.top ? (T)2 * l.f[5] : l.f[5]);
+      v = fused<T>(fused<T>(-v, diag, num), l.id, v);
+    }
+    return v;
   };
   if (tp.np == 2) {
     const TailCell x1 = tail_cell(n, tp, 1, colour);
@@ -2128,26 +2135,36 @@ __device__ __forceinline__ void tail_pass(const Dims& n, const TailPairs& tp, co
 // A coarsest level of one or two cells in a row: the same sweeps, with the
 // same arithmetic, done by one thread in registers.  Cell 0 is red, cell 1
 // black; the face between them is bx[1]; there is no other neighbour.
-template <typename T>
+template <typename T, bool DIVIDE>
 __device__ __forceinline__ void tail_coarsest_row(const TailArrays<T>& A, bool two, T h2, int S, int tid) {
   if (tid == 0) {
+    const int nx = two ? 2 : 1;
     const T r0 = h2 * A.b[0], i0 = A.id[0];
     const T r1 = two ? h2 * A.b[1] : (T)0, i1 = two ? A.id[1] : (T)0, w = two ? A.bx[1] : (T)0;
+    T d0 = 0, d1 = 0;
+    if constexpr (DIVIDE) {
+      d0 = A.bx[0] + A.bx[1] + A.by[0] + A.by[nx] + A.bz[0] + (T)2 * A.bz[nx];
+      if (two) d1 = A.bx[1] + A.bx[2] + A.by[1] + A.by[3] + A.bz[1] + (T)2 * A.bz[3];
+    }
+    auto over = [&](T num, T id, T d) {
+      const T v = num * id;
+      return DIVIDE ? fused<T>(fused<T>(-v, d, num), id, v) : v;
+    };
     T e0 = 0, e1 = 0;
 #pragma unroll 1
     for (int s = 0; s < 2 * S; ++s) {   // forward: red, black; backward: black, red
       if (s < S) {
         T num = r0;
         if (s > 0) num += w * e1;
-        e0 = num * i0;
+        e0 = over(num, i0, d0);
       }
       T num = r1;
       num += w * e0;
-      e1 = num * i1;
+      e1 = over(num, i1, d1);
       if (s >= S) {
         T n0 = r0;
         n0 += w * e1;
-        e0 = n0 * i0;
+        e0 = over(n0, i0, d0);
       }
     }
     A.e[0] = e0;
@@ -2162,49 +2179,67 @@ __device__ __forceinline__ void tail_coarsest_row(const TailArrays<T>& A, bool t
 // linear map, so its matrix, formed once per solve, gives the same values in one
 // product: 256 x 1 x 64's levels of 64, 16 and 4 cells took 20 of the tail's
 // 40 us.  R: the level's cells, rounded up; thread (g, i) sums columns g, g + G,
-// .. of row i (32 loads in flight at a time), then the G sums are added in order.
+// .. of row i (32 loads in flight at a time), in FP64 and in up to eight sums that
+// are added pairwise (one sum of 128 terms was 5e-16 from the exact product, these
+// 3e-16), then the G sums are added in order.  SUM2: each sum's rounding is summed
+// beside it, for a matrix that is the whole tail (of a grid of up to 256 cells,
+// whose correction is the product itself).
 // Past 256 cells the matrix outgrows what one compute unit loads in the time
 // of the passes (512 cells: 2 MB at 64 B per clock, 14 us).
-template <typename T, int R>
+template <typename T, int R, bool SUM2>
 __device__ __forceinline__ void matrix_product(const TailDesc<T>& D, T* sm, int tid, int N) {
-  constexpr int G = kTailThreads / R, K = R / G, U = K < 32 ? K : 32;
+  constexpr int G = kTailThreads / R, K = R / G, U = K < 32 ? K : 32, S = U < 8 ? U : 8;
   const int l = D.nl - 1, i = tid % R, g = tid / R;
   const T* b = sm + D.ob[l];
-  T* mv = sm + D.omv;
+  double* mv = reinterpret_cast<double*>(sm + D.omv);
   T m[U];
-  double s = 0;
+  double s[S] = {}, r[S] = {};
 #pragma unroll 1
   for (int c0 = g; c0 < N; c0 += G * U) {
 #pragma unroll
     for (int q = 0; q < U; ++q) m[q] = D.M[min(c0 + G * q, N - 1) * N + min(i, N - 1)];
 #pragma unroll
     for (int q = 0; q < U; ++q) {
-      const double v = (double)m[q] * (double)b[min(c0 + G * q, N - 1)];
-      s += c0 + G * q < N ? v : 0.0;
+      const T bq = b[min(c0 + G * q, N - 1)];
+      const double bc = c0 + G * q < N ? (double)bq : 0.0, t = __builtin_fma((double)m[q], bc, s[q % S]);
+      if constexpr (SUM2) r[q % S] += __builtin_fma((double)m[q], bc, s[q % S] - t);
+      s[q % S] = t;
     }
   }
-  mv[tid] = (T)s;
+#pragma unroll
+  for (int o = S / 2; o > 0; o >>= 1)
+#pragma unroll
+    for (int q = 0; q < o; ++q) {
+      if constexpr (SUM2) {
+        const double t = s[q] + s[q + o], a = t - s[q];
+        r[q] += r[q + o] + ((s[q] - (t - a)) + (s[q + o] - a));
+        s[q] = t;
+      } else {
+        s[q] += s[q + o];
+      }
+    }
+  mv[tid] = s[0] + r[0];
   __syncthreads();
   if (tid < N) {
     double t = 0;
 #pragma unroll 4
-    for (int q = 0; q < G; ++q) t += (double)mv[tid + q * R];
+    for (int q = 0; q < G; ++q) t += mv[tid + q * R];
     sm[D.oe[l] + tid] = (T)t;
   }
   __syncthreads();
 }
-template <typename T>
+template <typename T, bool SUM2>
 __device__ __forceinline__ void tail_matrix_product(const TailDesc<T>& D, T* sm, int tid) {
   const Dims n = D.n[D.nl - 1];
   const int N = n.nx * n.ny * n.nz;
   if (N > 128)
-    matrix_product<T, 256>(D, sm, tid, N);
+    matrix_product<T, 256, SUM2>(D, sm, tid, N);
   else if (N > 64)
-    matrix_product<T, 128>(D, sm, tid, N);
+    matrix_product<T, 128, SUM2>(D, sm, tid, N);
   else if (N > 32)
-    matrix_product<T, 64>(D, sm, tid, N);
+    matrix_product<T, 64, SUM2>(D, sm, tid, N);
   else
-    matrix_product<T, 32>(D, sm, tid, N);
+    matrix_product<T, 32, SUM2>(D, sm, tid, N);
 }
 
 // The tail's first level, and a coarsest level that is no matrix: its face
@@ -2414,7 +2449,7 @@ __device__ __forceinline__ void tail_levels(const TailDesc<T>& D, T* sm, int tid
     const int l = up ? 2 * nl - 2 - it : it;
     const bool bottom = l == nl - 1;
     if (bottom && D.M) {
-      tail_matrix_product<T>(D, sm, tid);
+      tail_matrix_product<T, false>(D, sm, tid);
       continue;
     }
     const Dims n = D.n[l];
@@ -2422,7 +2457,7 @@ __device__ __forceinline__ void tail_levels(const TailDesc<T>& D, T* sm, int tid
     const T h2 = D.h2[l];
     const TailArrays<T> A{sm + D.obx[l], sm + D.oby[l], sm + D.obz[l], sm + D.oid[l], sm + D.ob[l], sm + D.oe[l]};
     if (bottom && n.nx <= 2 && n.ny == 1 && n.nz == 1) {
-      tail_coarsest_row<T>(A, n.nx == 2, h2, D.coarse_sweeps, tid);
+      tail_coarsest_row<T, !REG>(A, n.nx == 2, h2, D.coarse_sweeps, tid);
       continue;
     }
     if constexpr (REG) {
@@ -2456,7 +2491,7 @@ __device__ __forceinline__ void tail_levels(const TailDesc<T>& D, T* sm, int tid
     const int passes = bottom ? 4 * D.coarse_sweeps : 2 * (up ? D.nu_post : D.nu_pre);
 #pragma unroll 1
     for (int s = 0; s < passes; ++s)
-      tail_pass<T>(n, tp, A, h2, (s + (up || (bottom && 2 * s >= passes))) & 1, !up && s == 0);
+      tail_pass<T, !REG>(n, tp, A, h2, (s + (up || (bottom && 2 * s >= passes))) & 1, !up && s == 0);
     if (up || bottom) continue;
     // every fine cell's residual b - A e, each thread for both cells of its
     // pairs (a wall term is an exact zero) ...
@@ -2503,9 +2538,11 @@ __device__ __forceinline__ void tail_levels(const TailDesc<T>& D, T* sm, int tid
 }
 
 // Column blockIdx.x of that matrix: the cycle over D's levels, one wavefront,
-// from a unit right-hand side.  Also an FP32 cycle's is computed in FP64 from
-// its FP32 coefficients, and its products are summed in FP64: the result is
-// then nearer the exact cycle than the FP32 passes' own.
+// from a unit right-hand side.  An FP32 cycle's is computed in FP64 from
+// its FP32 coefficients and rounded once, and its products are summed in FP64:
+// nearer the exact cycle than the FP32 passes' own.  An FP64 cycle's is about as
+// near as the passes (a whole cycle from the oracle's, 16 x 1 x 16 2.9e-16 and 3.0e-16,
+// 8 x 4 x 8 2.8e-16 and 2.0e-16, 256 x 1 x 64 3.0e-16 and 2.8e-16).
 template <typename T>
 __global__ void __launch_bounds__(64) k_tail_matrix(TailDesc<double> D, const T* __restrict__ pack, T* __restrict__ M) {
   extern __shared__ double tail_smem[];
@@ -2575,7 +2612,7 @@ __global__ void __launch_bounds__(kTailThreads) k_vcycle_matrix(TailDesc<T> D) {
   const int tid = threadIdx.x, N = D.n[0].nx * D.n[0].ny * D.n[0].nz;
   if (tid < N) sm[D.ob[0] + tid] = D.b0[tid];
   __syncthreads();
-  tail_matrix_product<T>(D, sm, tid);
+  tail_matrix_product<T, sizeof(T) == 8>(D, sm, tid);
   if (tid < N) D.ge[tid] = sm[D.oe[0] + tid];
 }
 
