@@ -75,6 +75,7 @@ struct ns_ctx {
     int ndot;
   } gs[16];           // recorded CG segments, keyed by kind and vectors
   int ngs;
+  bool settled;       // the last solve's guess met its tolerance
   int ndot;           // partials of <r, z> the last segment left unsummed (0: none, it is in scal)
   ns_net* net;        // learned guess (not owned)
   struct {
@@ -947,9 +948,8 @@ void build_face_tables(ns_ctx* X) {
   }
 }
 
-// (matrix: with the tail's matrix, which a solve's cycles share)
+// the levels' coefficients (matrix: and the tail's matrix, which a solve's cycles share)
 void prepare_hierarchy(ns_ctx* X, bool matrix) {
-  build_face_tables(X);
   if (X->P.prec == NS_PREC_FP64)
     build_hierarchy<double>(X, matrix);
   else
@@ -1048,14 +1048,22 @@ ns_status pcg(ns_ctx* X, ns_stats* stats) {
     if (xpend) launch_x_update(n, dcur, x, cs, X->st, xs);
     xpend = false;
   };
-  prepare_hierarchy(X, true);
+  build_face_tables(X);
   X->nres = launch_resid_norm(n, h, L0.bx, L0.by, L0.bz, X->b, x, X->r, cs, FIN_RESID0, st, face_tab(L0, L0.bx), split,
                               xs);
   HIPCHK(X, hipEventRecord(X->ev_rr, st));
-  // first direction d = z = M r, rho = <r, z>, queued before the host has
-  // seen ||b|| and ||r||; unused if b = 0 or the guess already converges
-  ns_status s = precond_rho(z);
-  if (s != NS_OK) return s;
+  // the levels and the first direction d = z = M r, rho = <r, z>, queued before
+  // the host has seen ||b|| and ||r||; unused if b = 0 or the guess already
+  // converges.  Where the last solve's guess did, this one's probably does, and
+  // they wait for the host: repeated at rest, projection_solve takes 31 us at 16 x
+  // 1 x 16 where queueing them took 88, and 43 at 128 x 64 x 64 against 174
+  ns_status s = NS_OK;
+  auto first_direction = [&] {
+    prepare_hierarchy(X, true);
+    return precond_rho(z);
+  };
+  const bool wait = X->settled;
+  if (!wait && (s = first_direction()) != NS_OK) return s;
   HIPCHK(X, hipEventSynchronize(X->ev_rr));
   if (X->host[S_FLAGS] != 0.0)
     return fail(X, NS_EUNSTABLE, "a carried face density came out <= 0: the step's outflow Courant number is "
@@ -1063,7 +1071,9 @@ ns_status pcg(ns_ctx* X, ns_stats* stats) {
   const double bb = host_total(X, 2, 1, S_BB);
   double rr = host_total(X, 2, 0, S_RR);
   if (!std::isfinite(bb) || !std::isfinite(rr)) return fail(X, NS_ENAN, "non-finite right-hand side or guess");
+  X->settled = rr <= P.rtol * P.rtol * bb;
   if (bb == 0.0) {
+    X->settled = true;
     launch_fill<double>(x, X->nc, st);
     S.converged = 1;
     if (stats) *stats = S;
@@ -1073,6 +1083,7 @@ ns_status pcg(ns_ctx* X, ns_stats* stats) {
   const double tol2 = P.rtol * P.rtol * bb;
   S.rel_resid0 = S.rel_resid = std::sqrt(rr) / bnorm;
   bool conv = rr <= tol2;
+  if (wait && !conv && (s = first_direction()) != NS_OK) return s;
   double true_rr = rr;   // ||b - A x||^2 of the latest confirmed test
   double rr_prev = 0.0;  // ||r||^2 one iteration back (0: none since the last (re)start)
   int it = 0;
@@ -1793,6 +1804,7 @@ ns_status ns_vcycle(ns_ctx* X, const double* r, double* z) {
   launch_d2f(L0.bz, L0.bzf, X->nw, X->st);
   // One cycle does not earn the tail's matrix (16 x 1 x 16: 59 us with it, 37
   // without): its levels run by passes.
+  build_face_tables(X);
   prepare_hierarchy(X, false);
   // A 2-D level's visit up reads r for its tiles' rings while other blocks store
   // z: where the caller's arrays overlap, it reads a copy (in the finest level's
