@@ -879,8 +879,9 @@ __device__ __forceinline__ void mom_point(const Phys& P, int i, int j, int k, co
     cn_diag[f] = m.den;
   }
 }
-// The three components in one launch: the first third of the planes of blocks
-// takes the x-faces, then the y- and the z-faces
+// The three components in one launch: the first third of the blocks along x
+// takes the x-faces, then the y- and the z-faces (along x, where a launch may
+// have 2^31 blocks: three times a tall tank's planes would pass the 65536 of z)
 struct MomOut {
   double* u[3];
   double* beta[3];
@@ -894,10 +895,10 @@ __global__ void __launch_bounds__(256) k_momentum(Phys P, const double* __restri
                                                   const double* __restrict__ rfl, const double* __restrict__ mu,
                                                   const double* __restrict__ chi, const double* __restrict__ rho_n,
                                                   double dt, double t1, MomOut O, double* __restrict__ flag) {
-  const int nb = gridDim.z / 3, C = blockIdx.z / nb;
-  const int i = blockIdx.x * 64 + threadIdx.x;
+  const int nb = gridDim.x / 3, C = blockIdx.x / nb;
+  const int i = (blockIdx.x - C * nb) * 64 + threadIdx.x;
   const int j = blockIdx.y * blockDim.y + __builtin_amdgcn_readfirstlane(threadIdx.y);
-  const int k = (blockIdx.z - C * nb) * blockDim.z + __builtin_amdgcn_readfirstlane(threadIdx.z);
+  const int k = blockIdx.z * blockDim.z + __builtin_amdgcn_readfirstlane(threadIdx.z);
   if (C == 0)
     mom_point<0, CONS>(P, i, j, k, u, v, w, rho, rfl, mu, chi, rho_n, dt, t1, O.u[0], O.beta[0], O.betaf[0], O.rhs[0],
                        O.diag[0], flag);
@@ -1532,7 +1533,7 @@ void launch_momentum(const Phys& P, const double* u, const double* v, const doub
     for (int c = 0; c < 3; ++c) O.u[c] = o[c], O.beta[c] = be[c], O.betaf[c] = bf[c], O.rhs[c] = r[c], O.diag[c] = dg[c];
     Geo g = geo3(n.nx + 1, n.ny + (n.ny > 1), n.nz + 1);
     g.grid.y = (n.ny + 1 + g.block.y - 1) / g.block.y;   // (the y-faces' rows)
-    g.grid.z *= 3;
+    g.grid.x *= 3;
     hipLaunchKernelGGL(rho_n ? k_momentum<true> : k_momentum<false>, g.grid, g.block, 0, st, Pt, u, v, w, rho, rfl, mu, chi,
                        rho_n, dt, t1, O, flag);
     return;
