@@ -910,6 +910,22 @@ __global__ void __launch_bounds__(256) k_momentum(Phys P, const double* __restri
                        O.diag[2], flag);
 }
 
+// One component, its tiles in the XCD order: larger grids of short rows
+template <int C, bool CONS>
+__global__ void __launch_bounds__(256) k_momentum_face(Phys P, const double* __restrict__ u,
+                                                       const double* __restrict__ v, const double* __restrict__ w,
+                                                       const double* __restrict__ rho, const double* __restrict__ rfl,
+                                                       const double* __restrict__ mu, const double* __restrict__ chi,
+                                                       const double* __restrict__ rho_n, double dt, double t1,
+                                                       double* __restrict__ out, double* __restrict__ beta,
+                                                       float* __restrict__ betaf, double* __restrict__ cn_rhs,
+                                                       double* __restrict__ cn_diag, double* __restrict__ flag) {
+  const Tile tl = xcd_tile();
+  mom_point<C, CONS>(P, tl.x * blockDim.x + threadIdx.x, tl.y * blockDim.y + threadIdx.y,
+                     tl.z * blockDim.z + threadIdx.z, u, v, w, rho, rfl, mu, chi, rho_n, dt, t1, out, beta, betaf,
+                     cn_rhs, cn_diag, flag);
+}
+
 // The same for larger grids, two faces along x per lane (V2): half the accesses,
 // which bound the one-face form (55 to 59 of them per face, the address unit busy
 // 85% of the time), and the rows' arithmetic on scalars.  256 x 128 x 128, the
@@ -1043,52 +1059,67 @@ __global__ void __launch_bounds__(256) k_cn_sweep(Phys P, const double* __restri
                                                   const double* __restrict__ rhs,
                                                   const double* __restrict__ diag, double* __restrict__ out,
                                                   double* __restrict__ part) {
-  constexpr bool PAIR = std::is_same_v<T, V2>;
   const Dims n = P.n;
   constexpr int ci = (C == 0), cj = (C == 1), ck = (C == 2);
   const int mx = n.nx + ci, my = n.ny + cj, mz = n.nz + ck;
+  const double* uc = (C == 0) ? u : (C == 1) ? v : w;
   const Tile tl = xcd_tile();
-  const int i = (PAIR ? 2 : 1) * (tl.x * 64 + threadIdx.x);
-  const int j = tl.y * blockDim.y + __builtin_amdgcn_readfirstlane(threadIdx.y);
-  const int k = tl.z * blockDim.z + __builtin_amdgcn_readfirstlane(threadIdx.z);
   double du = 0.0, um = 0.0;
-  if (i < (PAIR ? n.nx : mx) && j < my && k < mz) {
-    const unsigned f = (unsigned)(i + mx * (j + my * k));
-    const double* uc = (C == 0) ? u : (C == 1) ? v : w;
-    const bool two = PAIR && i + 1 < n.nx;
-    const T uf = fvt<C, T, 0>(uc, n, i, j, k);
-    double dg[2] = {diag[f], two ? diag[f + 1] : 0.0};
-    auto update = [&](double u0, double d0, double r0, double L, double a) {
-      const double nv = (r0 + 0.5 * (L + a * u0)) / (d0 + 0.5 * a);
-      if (d0 == 0.0) return u0;
-      du = fmax(du, fabs(nv - u0));
-      um = fmax(um, fabs(nv));
-      return nv;
-    };
-    if (dg[0] != 0.0 || dg[1] != 0.0) {
-      const double ih = 1.0 / P.h;
-      T L{}, a{};
-      sweep_dir<C, 0, T>(uc, u, mu, n, i, j, k, uf, ih, L, a);
-      sweep_dir<C, 1, T>(uc, v, mu, n, i, j, k, uf, ih, L, a);
-      sweep_dir<C, 2, T>(uc, w, mu, n, i, j, k, uf, ih, L, a);
-      if constexpr (PAIR) {
+  if constexpr (std::is_same_v<T, double>) {
+    const int i = tl.x * blockDim.x + threadIdx.x;
+    const int j = tl.y * blockDim.y + threadIdx.y;
+    const int k = tl.z * blockDim.z + threadIdx.z;
+    if (i < mx && j < my && k < mz) {
+      const size_t f = i + (size_t)mx * (j + (size_t)my * k);
+      const double uf = uc[f], dg = diag[f];
+      double nv = uf;
+      if (dg != 0.0) {
+        const double ih = 1.0 / P.h;
+        double L = 0.0, a = 0.0;
+        sweep_dir<C, 0, T>(uc, u, mu, n, i, j, k, uf, ih, L, a);
+        sweep_dir<C, 1, T>(uc, v, mu, n, i, j, k, uf, ih, L, a);
+        sweep_dir<C, 2, T>(uc, w, mu, n, i, j, k, uf, ih, L, a);
+        nv = (rhs[f] + 0.5 * (L + a * uf)) / (dg + 0.5 * a);
+        du = fabs(nv - uf);
+        um = fabs(nv);
+      }
+      out[f] = nv;
+    }
+  } else {
+    const int i = 2 * (tl.x * 64 + threadIdx.x);
+    const int j = tl.y * blockDim.y + __builtin_amdgcn_readfirstlane(threadIdx.y);
+    const int k = tl.z * blockDim.z + __builtin_amdgcn_readfirstlane(threadIdx.z);
+    if (i < n.nx && j < my && k < mz) {
+      const unsigned f = (unsigned)(i + mx * (j + my * k));
+      const bool two = i + 1 < n.nx;
+      const T uf = fvt<C, T, 0>(uc, n, i, j, k);
+      const double dg[2] = {diag[f], two ? diag[f + 1] : 0.0};
+      auto update = [&](double u0, double d0, double r0, double L, double a) {
+        const double nv = (r0 + 0.5 * (L + a * u0)) / (d0 + 0.5 * a);
+        if (d0 == 0.0) return u0;
+        du = fmax(du, fabs(nv - u0));
+        um = fmax(um, fabs(nv));
+        return nv;
+      };
+      if (dg[0] != 0.0 || dg[1] != 0.0) {
+        const double ih = 1.0 / P.h;
+        T L{}, a{};
+        sweep_dir<C, 0, T>(uc, u, mu, n, i, j, k, uf, ih, L, a);
+        sweep_dir<C, 1, T>(uc, v, mu, n, i, j, k, uf, ih, L, a);
+        sweep_dir<C, 2, T>(uc, w, mu, n, i, j, k, uf, ih, L, a);
         const double nx = update(uf.x, dg[0], rhs[f], L.x, a.x);
         if (two)
           *reinterpret_cast<V2Mem*>(out + f) = V2Mem{nx, update(uf.y, dg[1], rhs[f + 1], L.y, a.y)};
         else
           out[f] = nx;
       } else {
-        out[f] = update(uf, dg[0], rhs[f], L, a);
+        out[f] = uf.x;
+        if (two) out[f + 1] = uf.y;
       }
-    } else if constexpr (PAIR) {
-      out[f] = uf.x;
-      if (two) out[f + 1] = uf.y;
-    } else {
-      out[f] = uf;
-    }
-    if (PAIR && C == 0 && i + 2 >= n.nx) {
-      const unsigned fw = f + (two ? 2u : 1u);
-      out[fw] = uc[fw];
+      if (C == 0 && i + 2 >= n.nx) {
+        const unsigned fw = f + (two ? 2u : 1u);
+        out[fw] = uc[fw];
+      }
     }
   }
   if (!part) return;
@@ -1417,10 +1448,16 @@ __global__ void __launch_bounds__(1024) k_diag_finalize(const double* __restrict
 }  // namespace
 
 // ------------------------------------------------------------------ launchers
+// Grids past the predictor's one launch of a face per lane: 64 x 40 x 40 (102400
+// cells) 23.2 us against 26.6 with two faces, 1024 x 1 x 208 (212992) 26.2 against
+// 25.2, 96 x 48 x 56 40.8 against 35.8
+static bool large(const Dims& n) { return (long)n.nx * n.ny * n.nz >= 3L << 16; }
 // Where the predictor and its Crank-Nicolson sweeps take two faces along x per
-// lane: 64 x 40 x 40 (102400 cells) 23.2 us against 26.6 with two, 1024 x 1 x 208
-// (212992) 26.2 against 25.2, 96 x 48 x 56 40.8 against 35.8
-static bool pairs_pay(const Dims& n) { return n.nx >= 2 && (long)n.nx * n.ny * n.nz >= 3L << 16; }
+// lane: in rows of 64 cells on, whose x-faces fill more than one wavefront; below,
+// two faces per lane leave more of one idle and save no wavefront (64 x 128 x 128
+// 136 us against 88 with two, 63 x 128 x 128 78 against 88, 16 x 128 x 128 75
+// against 97)
+static bool pairs_pay(const Dims& n) { return n.nx >= 64 && large(n); }
 
 // Where a lane marches up a column: from 2^20 cells on; below it a cell per lane,
 // whose many short wavefronts fill the chip better (128 x 64 x 64: advection
@@ -1528,7 +1565,7 @@ void launch_momentum(const Phys& P, const double* u, const double* v, const doub
   double* const o[3] = {us, vs, ws};
   double* const be[3] = {bx, by, bz};
   float* const bf[3] = {bxf, byf, bzf};
-  if (!pairs_pay(n)) {
+  if (!large(n)) {
     MomOut O;
     for (int c = 0; c < 3; ++c) O.u[c] = o[c], O.beta[c] = be[c], O.betaf[c] = bf[c], O.rhs[c] = r[c], O.diag[c] = dg[c];
     Geo g = geo3(n.nx + 1, n.ny + (n.ny > 1), n.nz + 1);
@@ -1541,8 +1578,9 @@ void launch_momentum(const Phys& P, const double* u, const double* v, const doub
   auto comp = [&](auto c, auto cons) {
     constexpr int C = decltype(c)::value;
     constexpr bool CONS = decltype(cons)::value;
-    const Geo g = geo3((n.nx + 1) / 2, n.ny + (C == 1), n.nz + (C == 2));
-    hipLaunchKernelGGL((k_momentum_pair<C, CONS>), g.grid, g.block, 0, st, Pt, u, v, w, rho, rfl, mu, chi, rho_n, dt, t1,
+    const bool pair = pairs_pay(n);
+    const Geo g = geo3(pair ? (n.nx + 1) / 2 : n.nx + (C == 0), n.ny + (C == 1), n.nz + (C == 2));
+    hipLaunchKernelGGL((pair ? k_momentum_pair<C, CONS> : k_momentum_face<C, CONS>), g.grid, g.block, 0, st, Pt, u, v, w, rho, rfl, mu, chi, rho_n, dt, t1,
                        o[C], be[C], bf[C], r[C], dg[C], flag);
   };
   auto all = [&](auto cons) {
