@@ -1459,37 +1459,68 @@ static bool large(const Dims& n) { return (long)n.nx * n.ny * n.nz >= 3L << 16; 
 // against 97)
 static bool pairs_pay(const Dims& n) { return n.nx >= 64 && large(n); }
 
-// Where a lane marches up a column: from 2^20 cells on; below it a cell per lane,
-// whose many short wavefronts fill the chip better (128 x 64 x 64: advection
-// and five pseudo-steps 36 us against 43; 200 x 72 x 104: 98 against 80).  A
-// plane's values are at byte offsets of 32 bits, so its largest array must stay
-// below 2^29 entries (23171 x 23171 x 2 is a valid grid)
+// Planes of a march: the fewest rounds of blocks over the chip's 512 places
+// (two blocks per compute unit) times a block's planes, four more being spent
+// on its start and the planes that only feed it (a block of all planes has none)
+static int march_planes(long cols, int nz, long* planes = nullptr) {
+  int best = nz;
+  long cost = -1;
+  for (int c = 1; c <= std::max(1, std::min(nz / 4, 1024)); ++c) {
+    const int kz = (nz + c - 1) / c;
+    const long t = ((cols * ((nz + kz - 1) / kz) + 511) / 512) * (kz + 4);
+    if (cost < 0 || t < cost) cost = t, best = kz;
+  }
+  if (planes) *planes = best == nz ? (cols + 511) / 512 * (nz + 1) : cost;
+  return best;
+}
+static long march_cols(const Dims& n, int ring) {
+  const int lanes = 64 - 2 * ring, rows = kRW * kRR - 2 * ring;
+  return (long)((n.nx + lanes - 1) / lanes) * ((n.ny + rows - 1) / rows);
+}
+
+// Where a lane may march up a column: a plane's values are at byte offsets of 32
+// bits, so its largest array must stay below 2^29 entries (23171 x 23171 x 2 is
+// a valid grid)
 static bool marches(const Dims& n) {
   return n.ny >= 4 && (long)n.nx * n.ny * n.nz >= (1L << 20) &&
          std::max((long)(n.nx + 1) * n.ny, (long)n.nx * (n.ny + 1)) < (1L << 29);
 }
-// Pseudo-steps per launch
-int reinit_steps(const Dims& n) { return n.ny == 1 ? kR2 : marches(n) ? 2 : 1; }
-
-// Planes of a march: the fewest rounds of blocks over the chip's 512 places
-// (two blocks per compute unit) times a block's planes, four more being spent
-// on its start and the planes that only feed it
-static int march_planes(int cols, int nz) {
-  int best = nz;
-  long cost = -1;
-  for (int c = 1; c <= std::max(1, nz / 4); ++c) {
-    const int kz = (nz + c - 1) / c;
-    const long t = (((long)cols * ((nz + kz - 1) / kz) + 511) / 512) * (kz + 4);
-    if (cost < 0 || t < cost) cost = t, best = kz;
-  }
-  return best;
+// lanes of the one-cell forms' 64 x 4 tiles
+static double cell_lanes(const Dims& n) { return 256.0 * ((n.nx + 63) / 64) * ((n.ny + 3) / 4) * n.nz; }
+// The advection marches from 13 x 2^17 such lanes on, in blocks that ny fills by
+// more than half: below, a cell per lane's many short wavefronts fill the chip better
+// (186 x 96 x 64, 1.18 million lanes, 15.3 us against 20.0; 176 x 112 x 80, 1.72 million,
+// 20.6 against 20.1)
+static bool advect_marches(const Dims& n) { return marches(n) && n.ny > 8 && cell_lanes(n) >= (13L << 17); }
+// The reinitialisation's form: two pseudo-steps per launch, marched (two), and a
+// single one marched or by a cell per lane, by what each is expected to take (us).  A round of
+// blocks takes 2.65 us a plane with two steps, in tiles of 62 x 14 cells, and
+// 1.5 with one, in 64 x 16, or the time of its 24 bytes per cell at 4.3 TB/s; a
+// cell per lane 3.5 and 6.2 per 2^20 lanes in tiles of 64 x 4.  Within 15% of
+// the times measured on 26 grids of 1 to 33 million cells, and the choice the
+// best one or within 6% of it: two steps 19, 21, 33 and 38 us on 64 x 128 x 128 (two
+// blocks across a row of 64), 200 x 72 x 104, 512 x 4 x 512 and 64 x 512 x 64, two
+// launches of one 18, 26, 33 and 24, of a cell per lane 19, 29, 19 and 31.
+struct ReinitForm {
+  bool two, march;
+};
+static ReinitForm reinit_form(const Dims& n) {
+  if (!marches(n)) return {false, false};
+  long p1, p2;
+  march_planes(march_cols(n, 0), n.nz, &p1);
+  march_planes(march_cols(n, 1), n.nz, &p2);
+  const double cells = (double)n.nx * n.ny * n.nz;
+  const double one = 3.5 + 6.2 * cell_lanes(n) / (1 << 20), march = std::max(1.5 * p1, cells * 24.0 / 4.3e6);
+  return {2.65 * p2 - 2.0 < 1.95 * std::min(one, march), march < one};
 }
+// Pseudo-steps per launch
+int reinit_steps(const Dims& n) { return n.ny == 1 ? kR2 : reinit_form(n).two ? 2 : 1; }
 
 void launch_advect(const Phys& P, const double* s, const double* u, const double* v, const double* w,
                    double dt, double* out, hipStream_t st) {
   const Dims n = P.n;
-  if (marches(n)) {
-    const int gx = (n.nx + 63) / 64, gy = (n.ny + kRW * kRR - 1) / (kRW * kRR), kz = march_planes(gx * gy, n.nz);
+  if (advect_marches(n)) {
+    const int gx = (n.nx + 63) / 64, gy = (n.ny + kRW * kRR - 1) / (kRW * kRR), kz = march_planes(march_cols(n, 0), n.nz);
     hipLaunchKernelGGL(k_advect_march, dim3(gx, gy, (n.nz + kz - 1) / kz), dim3(64, kRW), 0, st, P, s, u, v, w, dt, out, kz);
     return;
   }
@@ -1501,7 +1532,7 @@ template <int STEPS, bool FIRST>
 static void reinit_march(const Phys& P, const double* s0, const double* cur, double* nxt, double dtau, hipStream_t st) {
   constexpr int H = STEPS - 1, rows = kRW * kRR - 2 * H, lanes = 64 - 2 * H;
   const Dims n = P.n;
-  const int gx = (n.nx + lanes - 1) / lanes, gy = (n.ny + rows - 1) / rows, kz = march_planes(gx * gy, n.nz);
+  const int gx = (n.nx + lanes - 1) / lanes, gy = (n.ny + rows - 1) / rows, kz = march_planes(march_cols(n, H), n.nz);
   hipLaunchKernelGGL((k_reinit_march<STEPS, FIRST>), dim3(gx, gy, (n.nz + kz - 1) / kz), dim3(64, kRW), 0, st, P, s0, cur,
                      nxt, dtau, kz);
 }
@@ -1512,13 +1543,13 @@ void launch_reinit(const Phys& P, const double* s0, const double* cur, double* n
   if (P.n.ny == 1) {
     hipLaunchKernelGGL(k_reinit2d, dim3((P.n.nx + kR2X - 1) / kR2X, (P.n.nz + kR2Z - 1) / kR2Z), dim3(kR2T), 0, st, P, s0,
                        cur, nxt, dtau, steps);
-  } else if (reinit_steps(P.n) == 1) {
-    Geo g = geo3(P.n.nx, P.n.ny, P.n.nz);
-    hipLaunchKernelGGL(k_reinit, g.grid, g.block, 0, st, P, s0, cur, nxt, dtau);
   } else if (steps == 2) {
     first ? reinit_march<2, true>(P, s0, cur, nxt, dtau, st) : reinit_march<2, false>(P, s0, cur, nxt, dtau, st);
-  } else {
+  } else if (reinit_form(P.n).march) {
     first ? reinit_march<1, true>(P, s0, cur, nxt, dtau, st) : reinit_march<1, false>(P, s0, cur, nxt, dtau, st);
+  } else {
+    Geo g = geo3(P.n.nx, P.n.ny, P.n.nz);
+    hipLaunchKernelGGL(k_reinit, g.grid, g.block, 0, st, P, s0, cur, nxt, dtau);
   }
 }
 
