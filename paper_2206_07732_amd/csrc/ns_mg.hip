@@ -24,6 +24,8 @@
 //     partials, so results are bitwise reproducible.
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "ns_internal.h"
 
 namespace nsk {
@@ -2260,7 +2262,9 @@ struct RegView {
   const T *bx, *by, *bz, *id, *b;
   T *planes, *rs;  // LDS: the correction (reg_planes entries), the residual scratch in natural order
 };
-template <typename T, int NP>
+// WAVE: a level of at most 64 pairs by the first wavefront alone, ordered by
+// wavefront-level fences instead of workgroup barriers.
+template <typename T, int NP, bool WAVE = false>
 struct RegLevel {
   RegView<T> V;
   T* e;      // the red plane; the black one is P + sz further
@@ -2271,6 +2275,15 @@ struct RegLevel {
   float rest[NP][2];
   unsigned ok, odd, top;   // per (pair, colour): exists; odd column; per pair: top row
 
+  __device__ __forceinline__ static void sync() {
+    if constexpr (WAVE) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+      __syncthreads();
+    }
+  }
   __device__ __forceinline__ int pair(int q) const {   // (the last pairs of the last thread groups repeat one)
     return q < NP - 1 ? tid + q * kTailThreads : min(tid + q * kTailThreads, P - 1);
   }
@@ -2317,8 +2330,8 @@ struct RegLevel {
     }
   }
   __device__ __forceinline__ void zero() {
-    for (int q = tid; q < 2 * P + 3 * sz; q += kTailThreads) e[q - sz] = (T)0;
-    __syncthreads();
+    for (int q = tid; q < 2 * P + 3 * sz; q += WAVE ? 64 : kTailThreads) e[q - sz] = (T)0;
+    sync();
   }
   template <int C>
   __device__ __forceinline__ T* plane() const { return C ? e + P + sz : e; }
@@ -2356,7 +2369,7 @@ struct RegLevel {
       }
       if (ok >> (2 * q + C) & 1u) plane<C>()[pair(q)] = quotient<T>(num, id[q][C], rest[q][C]);
     }
-    __syncthreads();
+    sync();
   }
 
   template <int C>
@@ -2462,10 +2475,16 @@ __device__ __forceinline__ void tail_levels(const TailDesc<T>& D, T* sm, int tid
     }
     if constexpr (REG) {
       if (bottom) {
-        RegLevel<T, 1> t({n, n, 1, 1, h2, A.bx, A.by, A.bz, A.id, A.b, sm + D.oeb, nullptr}, tid);
-        t.zero();
-        t.smooth(4 * D.coarse_sweeps, false, true);
-        t.store(A.e);
+        auto sweeps = [&](auto wave) {
+          RegLevel<T, 1, decltype(wave)::value> t({n, n, 1, 1, h2, A.bx, A.by, A.bz, A.id, A.b, sm + D.oeb, nullptr}, tid);
+          t.zero();
+          t.smooth(4 * D.coarse_sweeps, false, true);
+          t.store(A.e);
+        };
+        if ((n.nx + 1) / 2 * n.ny * n.nz > 64)
+          sweeps(std::false_type{});
+        else if (tid < 64)
+          sweeps(std::true_type{});
         __syncthreads();
         continue;
       }
