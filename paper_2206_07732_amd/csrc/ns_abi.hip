@@ -596,7 +596,8 @@ void launch_tail(ns_ctx* X, int l0, const T* b, T* e, size_t bytes, bool matrix)
 }
 
 // coarse coefficients of every level from level 0, and 1/D of every level
-// (the tail stages it), in precision T: one launch per level
+// (the tail stages it), in precision T: one launch per level, and one for all the
+// small ones (launch_coarsen_chain).  matrix: also the tail's matrix
 template <typename T>
 void build_hierarchy(ns_ctx* X, bool matrix) {
   const Level& V0 = X->lev[0];
@@ -656,9 +657,6 @@ struct CgReq {
   int nparts;
 };
 
-// b0d: an FP32 cycle's finest-level right-hand side in FP64 (natural), read
-// by its first kernel in place of b0 (the levels below the finest, the
-// tail, and a cycle without pre-smoothing read b0)
 // Whether level l's visits are the 2-D launches (their vectors are natural)
 template <typename T>
 bool use_2d(const ns_ctx* X, int l) {
@@ -672,6 +670,10 @@ T* corr(const ns_ctx* X, int l) {
   return LV<T>::e(X->lev[l]) + (use_2d<T>(X, l) ? (size_t)n.nx * n.nz : 0);
 }
 
+// The cycle from level l down.  matrix: the tail's matrix is formed.  b0d: an
+// FP32 cycle's finest-level right-hand side in FP64 (natural), read by its first
+// kernel in place of b0 (the levels below the finest, the tail, and a cycle
+// without pre-smoothing read b0)
 template <typename T>
 void vcycle(ns_ctx* X, int l, bool matrix, const T* b0, T* e0, CgReq* dq = nullptr, const double* b0d = nullptr) {
   const ns_params& P = X->P;

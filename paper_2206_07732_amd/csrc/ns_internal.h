@@ -174,7 +174,8 @@ constexpr size_t kTailLdsBytes = 160 * 1024;   // gfx950: 160 KB of LDS per work
 
 // The cycle from the first coarse level of at most this many cells down is one
 // linear map of that level's right-hand side; a solve forms its matrix once and
-// the tail multiplies by it.
+// the tail multiplies by it.  Larger ones outgrow a compute unit's loads (at
+// matrix_product); smaller limits were not timed.
 constexpr int kTailMatrixCells = 256;
 
 template <typename T>
@@ -194,7 +195,8 @@ struct TailDesc {
   const T* b0;                              // the first level's right-hand side and correction
   T* ge;
   // the matrix of the last level's cycle (column-major, null: the tail goes
-  // down to the coarsest level) and kTailThreads scratch entries for its product
+  // down to the coarsest level) and the LDS offset of its product's
+  // kTailThreads FP64 partial sums
   const T* M;
   int omv;
   // the first level held in registers (top; else it is the image's one level,
@@ -398,9 +400,11 @@ bool cg_split(const Dims& n);
 int launch_resid_norm(const Dims& n, double h, const double* bx, const double* by, const double* bz, const double* b,
                       const double* x, double* r, const CgScratch& cs, int mode, hipStream_t st,
                       const FaceTab<double>& ft = FaceTab<double>{}, bool split = false, double* xs = nullptr);
-// <r, z> (one layout for both), as rho (FIN_RHO) or for beta (FIN_BETA)
+// whether the next kernel sums the partials of r z and d q itself, without a
+// finalizing launch between
 bool cg_folds(const Dims& n);
-// returns the partials' count (fold: left unsummed)
+// <r, z> (one layout for both), as rho (FIN_RHO) or for beta (FIN_BETA); returns
+// the partials' count (fold: left unsummed)
 int launch_dot(const Dims& n, const double* r, const double* z, const CgScratch& cs, int mode, hipStream_t st,
                bool fold);
 // the same from its partials, already in cs.partials

@@ -16,8 +16,10 @@
 //     the black cells read their red neighbours plus the parent correction,
 //     and the red cells are left for the red pass that follows, which
 //     overwrites them without reading them;
-//   * all levels from about a thousand cells down run in one workgroup out of
-//     LDS;
+//   * the levels from 4096 cells (FP32 6144) down run in one workgroup, the
+//     first out of registers, those below out of LDS, and the cycle from 256
+//     cells down is a product with its matrix;
+//   * a 2-D level's visit is one launch down and one up;
 //   * the direction update d = z + beta d is folded into the operator
 //     application, which carries q = A d by its recurrence A z + beta q;
 //     every CG reduction ends in one fixed-order pass over the per-block
@@ -1972,10 +1974,12 @@ __global__ void __launch_bounds__(1024) k_coarsen_chain(CoarsenChain<T> D) {
 
 // ------------------------------------------------------- coarse-level tail
 // Every level from the first tail level down to the coarsest runs in one
-// workgroup with coefficients, 1/D, right-hand sides and corrections held in
-// LDS, so a smoothing pass costs a barrier instead of a launch.  Each thread
-// decodes its cell pairs once per level visit, and a pass is its loads and its
-// arithmetic.
+// workgroup, so a smoothing pass costs a barrier instead of a launch: the first
+// level (and without a matrix the coarsest) in registers (RegLevel), the ones
+// between with coefficients, 1/D, right-hand sides and corrections in LDS, and
+// from the first level of at most kTailMatrixCells down a product with the
+// cycle's matrix.  Each thread decodes its cell pairs once per level visit, and a
+// pass is its loads and its arithmetic.
 //
 // A launch runs every instruction of this kernel a few times at most, on a
 // compute unit whose instruction cache holds none of them: with each level's
@@ -1989,7 +1993,7 @@ __global__ void __launch_bounds__(1024) k_coarsen_chain(CoarsenChain<T> D) {
 // zero and the passes add it unconditionally; only the open top face, whose
 // coefficient is not zero, is dropped by a select.
 // t / n for 0 <= t < 8192 with inv = 1.0f / n, exact ((t + 1/2) / n is at least
-// 1/(2n) from a whole number, and the product's error below 2^-11 / n): an
+// 1/(2n) from a whole number, and the product's error below 2^-10 / n): an
 // integer division by a number that is not a constant takes some thirty
 // instructions
 __device__ __forceinline__ int tail_div(int t, float inv) { return (int)(((float)t + 0.5f) * inv); }
@@ -2819,8 +2823,9 @@ __global__ void __launch_bounds__(kT2Threads) k_pre2d(int nx, int nz, T h2, cons
 }
 
 // Up: prolongation of the next level's correction ec, two post-smoothing
-// sweeps, and the result to out (natural; FP64 z of the CG loop, or the level's
-// own e, which no other block's ring reads by then: out is not e).  With r
+// sweeps, and the result to out (natural: the FP64 z of the CG loop, or the
+// second half of a coarse level's vector).  out is another buffer than e, whose
+// values the rings of tiles that run later still read.  With r
 // (the CG residual) also the per-block sums of r out.
 template <typename T, typename TB, typename TO>
 __global__ void __launch_bounds__(kT2Threads) k_post2d(int nx, int nz, T h2, const T* __restrict__ bx,
@@ -3339,8 +3344,10 @@ __global__ void __launch_bounds__(1024) k_finalize(const double* __restrict__ pa
 // fill most of a wavefront, and pay where the level has enough of them to keep
 // the chip busy: at 256 x 128 x 128 an FP64 colour pass takes 13.3 us against
 // 18.3 (FP32: 11.4 against 13.5), at 128 x 64 x 64, where a row fills half a
-// wavefront, 5.2 against 4.3 (FP32: 5.0 against 3.7).  FP32 takes four pairs
-// where such a row still fills a wavefront.
+// wavefront, 5.2 against 4.3 (FP32: 5.0 against 3.7).  At a million cells, where
+// the rule begins, eight FP64 iterations take 1990 us against 1955 on 384 x 52 x
+// 54 and less on the other shapes timed (256 x 64 x 64: 1425 against 1468).
+// FP32 takes four pairs where such a row still fills a wavefront.
 template <typename T>
 static int wide_pairs(const Dims& n) {
   const int hx = n.nx / 2;
